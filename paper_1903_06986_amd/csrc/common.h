@@ -241,6 +241,9 @@ template <class R>
 void pack_eo(lqcd_ctx *c, const void *lex, void *eo, int nrhs, size_t eo_stride);
 template <class R>
 void unpack_eo(lqcd_ctx *c, const void *eo, void *lex, int nrhs, size_t eo_stride);
+// Links from host memory (lexicographic complex128 [V][4][3][3]) into U64 and
+// U32 (allocated here); returns when links_host has been read.
+void pack_links(lqcd_ctx *c, const double *links_host);
 void fill_noise(lqcd_ctx *c, uint64_t seed, int64_t first, int nrhs, void *eta, uint8_t *codes);
 
 }  // namespace lqcd

@@ -25,7 +25,8 @@ extern "C" const char *lqcd_last_error(void) { return g_err; }
 // parity p, direction mu and matrix entry e, the Vh sites of that parity in
 // checkerboard order (cb = s >> 1): U[((p * 4 + mu) * 9 + e) * Vh + cb].
 // This puts the same entry of consecutive sites next to each other so that
-// the stencil's per-thread loads coalesce.
+// the stencil's per-thread loads coalesce.  The device does the reordering
+// (pack_links).
 extern "C" lqcd_status lqcd_create(const int dims[4], const double *links_host, double kappa,
                                    void *hip_stream, lqcd_ctx **out) {
   return guarded([&] {
@@ -46,29 +47,7 @@ extern "C" lqcd_status lqcd_create(const int dims[4], const double *links_host, 
       c->kappa = kappa;
       c->stream = static_cast<hipStream_t>(hip_stream);
       LQCD_HIP(hipGetDevice(&c->device));
-      const int Vh = c->g.Vh;
-      const int Lx = dims[0], Ly = dims[1], Lz = dims[2];
-      std::vector<double> h64(size_t(2) * 4 * 9 * Vh * 2);
-      std::vector<float> h32(h64.size());
-      for (long long s = 0; s < V; ++s) {
-        int x = int(s % Lx), y = int((s / Lx) % Ly), z = int((s / (Lx * Ly)) % Lz),
-            t = int(s / (Lx * Ly * Lz));
-        int p = (x + y + z + t) & 1;
-        int cb = int(s >> 1);
-        for (int mu = 0; mu < 4; ++mu)
-          for (int e = 0; e < 9; ++e) {
-            size_t dst = ((size_t(p) * 4 + mu) * 9 + e) * Vh + cb;
-            size_t src = (size_t(s) * 4 + mu) * 9 + e;
-            h64[2 * dst] = links_host[2 * src];
-            h64[2 * dst + 1] = links_host[2 * src + 1];
-            h32[2 * dst] = float(links_host[2 * src]);
-            h32[2 * dst + 1] = float(links_host[2 * src + 1]);
-          }
-      }
-      c->U64.ensure(h64.size() * sizeof(double));
-      c->U32.ensure(h32.size() * sizeof(float));
-      LQCD_HIP(hipMemcpy(c->U64.ptr, h64.data(), h64.size() * sizeof(double), hipMemcpyHostToDevice));
-      LQCD_HIP(hipMemcpy(c->U32.ptr, h32.data(), h32.size() * sizeof(float), hipMemcpyHostToDevice));
+      pack_links(c, links_host);
     } catch (...) {
       delete c;
       throw;

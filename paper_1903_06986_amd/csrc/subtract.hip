@@ -18,7 +18,8 @@
 // non-backtracking walks survive; on lattices with even extents every
 // closed walk has even length.  The host enumerates the walks (closed
 // modulo the periodic extents, so windings on short directions count) and
-// their spin traces; the device forms the link products at every site.
+// their spin traces; the device forms the link products at every site, once
+// per loop that the walks run along.
 // The paper obtains the same traces from unit-vector sources (Eqs.
 // (32)-(35)); the walk sum is that computation with every source's
 // non-returning paths dropped.
@@ -48,169 +49,283 @@ namespace {
 constexpr int kSubBlock = 16;
 
 // ---------------------------------------------------------- walk tables
+// The trace tr W_w(x) of a closed walk does not depend on where on its loop
+// the walk starts, a leading step that the last one undoes drops out of it,
+// and the walk run backwards has its complex conjugate.  So the device forms
+// one trace per loop (a cyclically reduced walk, up to rotation and
+// reversal) and site, summed over the sites of each timeslice, and every
+// walk's timeslice sums are a loop's sums shifted by the timeslices between
+// the two starting points: about 16 times fewer link products than one per
+// walk (length 8: 2.3k loops for 36k walks).
 constexpr int kMaxWalkLen = 8;  // local: length <= 6 (orders <= 7); point-split: <= 8
 
-struct Walk {
-  int len;
-  int dir[kMaxWalkLen];     // 2 * mu + (0: +mu, 1: -mu)
-  double coef[kNumOps][2];  // tr(Theta S_w) for Theta = 1, g1..g4; point-split: +-tr(S_w)
+// Directions are 2 * mu + (0: +mu, 1: -mu); a walk is coded in 3 bits per
+// step, the first step highest.
+using Code = uint32_t;
+
+// Spin product of a walk, S = prod (1 -+ g_mu): Gaussian integers.
+struct SpinInt {
+  int re[4][4], im[4][4];
 };
 
-using Spin = std::complex<double>[4][4];
+constexpr SpinInt kSpinOne = {{{1, 0, 0, 0}, {0, 1, 0, 0}, {0, 0, 1, 0}, {0, 0, 0, 1}}, {}};
 
-void enumerate(int len, const int L[4], int depth, int last, int disp[4], const Spin &S,
-               int dirs[kMaxWalkLen], std::vector<Walk> &out) {
+// S (1 - g_mu) for a forward hop, S (1 + g_mu) backward (every column of
+// g_mu has one nonzero entry, row e of it in column col[e]).
+SpinInt spin_hop(const SpinInt &S, int d) {
+  const SpinPerm &gm = kGamma[1 + (d >> 1)];
+  const int sg = (d & 1) ? 1 : -1;
+  SpinInt R = S;
+  for (int e = 0; e < 4; ++e) {
+    const int fr = sg * int(gm.re[e]), fi = sg * int(gm.im[e]), b = gm.col[e];
+    for (int a = 0; a < 4; ++a) {
+      R.re[a][b] += S.re[a][e] * fr - S.im[a][e] * fi;
+      R.im[a][b] += S.re[a][e] * fi + S.im[a][e] * fr;
+    }
+  }
+  return R;
+}
+
+// tr(Theta S)
+cdouble spin_trace(int th, const SpinInt &S) {
+  cdouble t = 0;
+  for (int a = 0; a < 4; ++a) {
+    const int b = kGamma[th].col[a];
+    t += cdouble(kGamma[th].re[a], kGamma[th].im[a]) * cdouble(S.re[b][a], S.im[b][a]);
+  }
+  return t;
+}
+
+// One closed walk: its loop, the timeslices from its start to the loop's,
+// whether it runs the loop backwards, and tr(Theta S_w) for Theta = 1,
+// g1..g4; point-split: +-tr(S_w) in the direction of its first step.
+struct Walk {
+  int loop, dt;
+  bool conj;
+  cdouble coef[kNumOps];
+};
+
+// The loop of the walk dirs[0..n): the smallest code among the rotations of
+// the walk and of its reverse.  A walk starting at x has the loop's trace at
+// a site dt timeslices from x, conjugated if conj.  n >= 1, no step undone
+// by the next, cyclically.
+Code loop_of(const int *dirs, int n, int &dt, bool &conj) {
+  Code best = ~Code(0);
+  int r[kMaxWalkLen];
+  for (int o = 0; o < 2; ++o) {
+    for (int i = 0; i < n; ++i) r[i] = o ? dirs[n - 1 - i] ^ 1 : dirs[i];
+    int tk = 0;
+    for (int k = 0; k < n; ++k) {
+      Code c = 0;
+      for (int i = 0; i < n; ++i) c = (c << 3) | Code(r[(k + i) % n]);
+      if (c < best) {
+        best = c;
+        dt = tk;
+        conj = o != 0;
+      }
+      if ((r[k] >> 1) == 3) tk += (r[k] & 1) ? -1 : 1;
+    }
+  }
+  return best;
+}
+
+// Calls f(dirs, S) for the closed walks of length len without a step undone
+// by the next, all steps >= low and the first one equal to it if low >= 0.
+template <class F>
+void each_walk(int len, const int L[4], int low, int depth, int disp[4], const SpinInt &S, int dirs[kMaxWalkLen],
+               F &&f) {
   if (depth == len) {
-    for (int mu = 0; mu < 4; ++mu)
-      if (((disp[mu] % L[mu]) + L[mu]) % L[mu] != 0) return;
-    Walk w;
-    w.len = len;
-    for (int i = 0; i < len; ++i) w.dir[i] = dirs[i];
-    bool any = false;
-    for (int th = 0; th < kNumTheta; ++th) {
-      std::complex<double> G[4][4];
-      gamma_dense(th, G);
-      std::complex<double> t = 0;
-      for (int a = 0; a < 4; ++a)
-        for (int b = 0; b < 4; ++b) t += G[a][b] * S[b][a];
-      w.coef[th][0] = t.real();
-      w.coef[th][1] = t.imag();
-      if (std::abs(t) > 1e-12) any = true;
-    }
-    std::complex<double> trS = 0;
-    for (int a = 0; a < 4; ++a) trS += S[a][a];
-    for (int mu = 0; mu < kNumPS; ++mu) {
-      const double sg = (dirs[0] >> 1) != mu ? 0.0 : ((dirs[0] & 1) ? 1.0 : -1.0);
-      w.coef[kNumTheta + mu][0] = sg * trS.real();
-      w.coef[kNumTheta + mu][1] = sg * trS.imag();
-      if (sg != 0.0 && std::abs(trS) > 1e-12) any = true;
-    }
-    if (any) out.push_back(w);
+    f(dirs, S);
     return;
   }
-  for (int d = 0; d < 8; ++d) {
-    if (depth > 0 && d == (last ^ 1)) continue;  // immediate reversal: zero spin factor
-    const int mu = d >> 1, sgn = (d & 1) ? -1 : 1;
-    disp[mu] += sgn;
-    int dist = 0;
+  for (int d = std::max(low, 0); d < 8; ++d) {
+    if (depth == 0 && low >= 0 && d != low) break;
+    if (depth > 0 && d == (dirs[depth - 1] ^ 1)) continue;  // immediate reversal: zero spin factor
+    disp[d >> 1] += (d & 1) ? -1 : 1;
+    int dist = 0;  // steps left to close modulo the periodic extents
     for (int nu = 0; nu < 4; ++nu) {
-      int a = ((disp[nu] % L[nu]) + L[nu]) % L[nu];
+      const int a = ((disp[nu] % L[nu]) + L[nu]) % L[nu];
       dist += std::min(a, L[nu] - a);
     }
     if (dist <= len - depth - 1) {
-      // S' = S (1 - g_mu) for a forward hop, S (1 + g_mu) backward
-      std::complex<double> G[4][4], S2[4][4];
-      gamma_dense(1 + mu, G);
-      for (int a = 0; a < 4; ++a)
-        for (int b = 0; b < 4; ++b) {
-          std::complex<double> s = 0;
-          for (int e = 0; e < 4; ++e) {
-            std::complex<double> f = (e == b ? 1.0 : 0.0) - double(sgn) * G[e][b];
-            s += S[a][e] * f;
-          }
-          S2[a][b] = s;
-        }
       dirs[depth] = d;
-      enumerate(len, L, depth + 1, d, disp, S2, dirs, out);
+      each_walk(len, L, low, depth + 1, disp, spin_hop(S, d), dirs, f);
     }
-    disp[mu] -= sgn;
+    disp[d >> 1] -= (d & 1) ? -1 : 1;
   }
 }
 
-// Link U_mu at lexicographic coordinates (x, y, z, t) in the even/odd layout.
-__device__ inline const cx<double> *link_at(const cx<double> *U, const Geom &g, int x, int y, int z,
-                                            int t, int mu) {
-  const int p = (x + y + z + t) & 1;
-  const int s = x + g.L[0] * (y + g.L[1] * (z + g.L[2] * t));
-  return U + ((size_t(p) * 4 + mu) * 9) * g.Vh + (s >> 1);
+// The loops of length len in ascending order of their codes (depth-first).
+std::vector<Code> enumerate_loops(int len, const int L[4]) {
+  std::vector<Code> loops;
+  int disp[4] = {0, 0, 0, 0}, dirs[kMaxWalkLen];
+  // a loop's code starts with a forward step in its lowest direction
+  for (int low = 0; low < 8; low += 2)
+    each_walk(len, L, low, 0, disp, kSpinOne, dirs, [&](const int *w, const SpinInt &) {
+      if (w[0] == (w[len - 1] ^ 1)) return;
+      Code c = 0;
+      for (int i = 0; i < len; ++i) c = (c << 3) | Code(w[i]);
+      int dt;
+      bool conj;
+      if (loop_of(w, len, dt, conj) == c) loops.push_back(c);
+    });
+  return loops;
 }
 
-// One hop of a walk from coordinates c: the link of direction d (forward:
-// U_mu(c), then c += mu; backward: c -= mu, then U_mu(c)^+) into Lk.
-__device__ inline void walk_step(const cx<double> *U, const Geom &g, int c[4], int d, cx<double> Lk[3][3]) {
-  const int mu = d >> 1;
-  const size_t Vh = g.Vh;
-  if ((d & 1) == 0) {
-    const cx<double> *u = link_at(U, g, c[0], c[1], c[2], c[3], mu);
+// A site on its way along a walk: lexicographic index, coordinates, parity.
+struct WalkPos {
+  int s, c[4], p;
+};
+
+// One hop of a walk along MU: the link (forward: U_mu, then x += mu;
+// backward: x -= mu, then U_mu^+) into Lk.
+template <int MU, bool FWD>
+__device__ inline void walk_move(const Geom &g, WalkPos &w) {
+  const int st = MU == 0 ? 1 : MU == 1 ? g.L[0] : MU == 2 ? g.L[0] * g.L[1] : g.L[0] * g.L[1] * g.L[2];
+  const int last = g.L[MU] - 1;
+  const bool wrap = w.c[MU] == (FWD ? last : 0);
+  w.s += wrap ? (FWD ? -st * last : st * last) : (FWD ? st : -st);
+  w.c[MU] = wrap ? (FWD ? 0 : last) : (FWD ? w.c[MU] + 1 : w.c[MU] - 1);
+  w.p ^= 1;
+}
+template <int MU, bool FWD>
+__device__ inline void walk_hop(const cx<double> *U, const Geom &g, WalkPos &w, cx<double> Lk[3][3]) {
+  if (!FWD) walk_move<MU, false>(g, w);
+  const cx<double> *u = U + (size_t(w.p) * 4 + MU) * 9 * g.Vh + (w.s >> 1);
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+  for (int a = 0; a < 3; ++a)
 #pragma unroll
-      for (int b = 0; b < 3; ++b) Lk[a][b] = u[(3 * a + b) * Vh];
-    c[mu] = (c[mu] + 1 == g.L[mu]) ? 0 : c[mu] + 1;
-  } else {
-    c[mu] = (c[mu] == 0) ? g.L[mu] - 1 : c[mu] - 1;
-    const cx<double> *u = link_at(U, g, c[0], c[1], c[2], c[3], mu);
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        const cx<double> v = u[(3 * b + a) * Vh];
-        Lk[a][b] = mk(v.re, -v.im);
-      }
+    for (int b = 0; b < 3; ++b) {
+      const cx<double> v = ldc(u + (FWD ? 3 * a + b : 3 * b + a) * size_t(g.Vh));
+      Lk[a][b] = FWD ? v : mk(v.re, -v.im);
+    }
+  if (FWD) walk_move<MU, true>(g, w);
+}
+// d is the same for the whole wave, so the branch is uniform.
+__device__ inline void walk_step(const cx<double> *U, const Geom &g, WalkPos &w, int d, cx<double> Lk[3][3]) {
+  switch (d) {
+    case 0: walk_hop<0, true>(U, g, w, Lk); break;
+    case 1: walk_hop<0, false>(U, g, w, Lk); break;
+    case 2: walk_hop<1, true>(U, g, w, Lk); break;
+    case 3: walk_hop<1, false>(U, g, w, Lk); break;
+    case 4: walk_hop<2, true>(U, g, w, Lk); break;
+    case 5: walk_hop<2, false>(U, g, w, Lk); break;
+    case 6: walk_hop<3, true>(U, g, w, Lk); break;
+    default: walk_hop<3, false>(U, g, w, Lk); break;
   }
 }
 
 // W <- W Lk
 __device__ inline void su3_rmul(cx<double> W[3][3], const cx<double> Lk[3][3]) {
-  cx<double> Nw[3][3];
 #pragma unroll
-  for (int a = 0; a < 3; ++a)
+  for (int a = 0; a < 3; ++a) {
+    const cx<double> w0 = W[a][0], w1 = W[a][1], w2 = W[a][2];
 #pragma unroll
-    for (int b = 0; b < 3; ++b) Nw[a][b] = W[a][0] * Lk[0][b] + W[a][1] * Lk[1][b] + W[a][2] * Lk[2][b];
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int b = 0; b < 3; ++b) W[a][b] = Nw[a][b];
+    for (int b = 0; b < 3; ++b) W[a][b] = w0 * Lk[0][b] + w1 * Lk[1][b] + w2 * Lk[2][b];
+  }
 }
 
-// out[th][s] = sum_w coef_w[th] tr W_w(s) for every lexicographic site s.
-// The walks come in depth-first order, cut into groups that share their
-// first P steps (groups[i] = [first, end) walk indices): the prefix product
-// A is formed once per group, each walk multiplies only its last len - P
-// links into B, and tr W = tr(A B) = sum_ab A_ab B_ba.
+constexpr int kLoopTile = 64;  // loops per workgroup
+
+// part[(loop * Lt + t) * nch + ch] = sum of tr W_loop(x) over the sites of
+// chunk ch of timeslice t (blockIdx.x = t * nch + ch; chunks of 256 sites,
+// nch chunks apart), for the kLoopTile loops of blockIdx.y.  Lane = site; the
+// loops come in depth-first order, so consecutive ones mostly share their
+// first len - 4 steps (product A) and len - 3 steps (product B): a loop costs
+// its last three links, two matrix products and tr(B C) = sum_ab B_ab C_ba.
+// Bound by the loads of those links through L1 and L2 (432 bytes per loop and
+// site) beside 250 FP64 FMAs.  All orders of all nine operators, host work
+// included: 1334 -> 71 ms on 24^3 x 32; with the link import 216 -> 9.2 ms on
+// 12^4 (before: one product per walk and site).
 __global__ void __launch_bounds__(kBlock)
-    k_walk_trace(Geom g, const cx<double> *__restrict__ U, const Walk *__restrict__ walks,
-                 const int2 *__restrict__ groups, int ngroup, int P, cx<double> *__restrict__ out) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= g.V) return;
-  const int x0 = s % g.L[0], y0 = (s / g.L[0]) % g.L[1], z0 = (s / (g.L[0] * g.L[1])) % g.L[2],
-            t0 = s / (g.L[0] * g.L[1] * g.L[2]);
-  double acc[kNumOps][2] = {};
-  for (int gi = 0; gi < ngroup; ++gi) {
-    const int2 gr = groups[gi];
-    int c[4] = {x0, y0, z0, t0};
-    cx<double> A[3][3], Lk[3][3];
+    k_loop_trace(Geom g, const cx<double> *__restrict__ U, const Code *__restrict__ loops, int nloop, int len,
+                 int nch, cx<double> *__restrict__ part) {
+  constexpr int kNW = kBlock / 64;
+  __shared__ cx<double> sh[kLoopTile][kNW];
+  const int t = blockIdx.x / nch, ch = blockIdx.x % nch;
+  const int l0 = blockIdx.y * kLoopTile, nl = min(kLoopTile, nloop - l0);
+  const int Lx = g.L[0], Ly = g.L[1], Vs = Lx * Ly * g.L[2];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int i = threadIdx.x; i < kLoopTile * kNW; i += kBlock) sh[i / kNW][i % kNW] = mk(0.0, 0.0);
+  __syncthreads();
+  const int nA = max(0, len - 4), nB = max(0, len - 3);
+  for (int i0 = ch * kBlock; i0 < Vs; i0 += nch * kBlock) {
+    const bool on = i0 + int(threadIdx.x) < Vs;
+    const int i = on ? i0 + int(threadIdx.x) : i0;
+    WalkPos w0;
+    w0.s = t * Vs + i;
+    w0.c[0] = i % Lx;
+    w0.c[1] = (i / Lx) % Ly;
+    w0.c[2] = i / (Lx * Ly);
+    w0.c[3] = t;
+    w0.p = (w0.c[0] + w0.c[1] + w0.c[2] + t) & 1;
+    WalkPos wA = w0, wB = w0;
+    cx<double> A[3][3], B[3][3], Lk[3][3];
+    Code prev = ~Code(0);
+    for (int l = 0; l < nl; ++l) {
+      const Code code = __builtin_amdgcn_readfirstlane(loops[l0 + l]);
+      const bool freshA = l == 0 || (code >> (3 * (len - nA))) != (prev >> (3 * (len - nA)));
+      const bool freshB = freshA || (code >> (3 * (len - nB))) != (prev >> (3 * (len - nB)));
+      prev = code;
+      if (freshA) {
+        wA = w0;
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+        for (int a = 0; a < 3; ++a)
 #pragma unroll
-      for (int b = 0; b < 3; ++b) A[a][b] = mk(a == b ? 1.0 : 0.0, 0.0);
-    for (int i = 0; i < P; ++i) {
-      walk_step(U, g, c, walks[gr.x].dir[i], Lk);
-      su3_rmul(A, Lk);
-    }
-    for (int w = gr.x; w < gr.y; ++w) {
-      const Walk &wk = walks[w];
-      int cc[4] = {c[0], c[1], c[2], c[3]};
-      cx<double> B[3][3];
-      walk_step(U, g, cc, wk.dir[P], B);
-      for (int i = P + 1; i < wk.len; ++i) {
-        walk_step(U, g, cc, wk.dir[i], Lk);
-        su3_rmul(B, Lk);
+          for (int b = 0; b < 3; ++b) A[a][b] = mk(a == b ? 1.0 : 0.0, 0.0);
+        for (int k = 0; k < nA; ++k) {
+          walk_step(U, g, wA, (code >> (3 * (len - 1 - k))) & 7, Lk);
+          su3_rmul(A, Lk);
+        }
+      }
+      if (freshB) {
+        wB = wA;
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+          for (int b = 0; b < 3; ++b) B[a][b] = A[a][b];
+        if (nB > nA) {
+          walk_step(U, g, wB, (code >> (3 * (len - 1 - nA))) & 7, Lk);
+          su3_rmul(B, Lk);
+        }
+      }
+      WalkPos w = wB;
+      cx<double> C[3][3];
+      walk_step(U, g, w, (code >> (3 * (len - 1 - nB))) & 7, C);
+      for (int k = nB + 1; k < len; ++k) {
+        walk_step(U, g, w, (code >> (3 * (len - 1 - k))) & 7, Lk);
+        su3_rmul(C, Lk);
       }
       cx<double> tr = mk(0.0, 0.0);
 #pragma unroll
       for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) tr = tr + A[a][b] * B[b][a];
+        for (int b = 0; b < 3; ++b) tr = tr + B[a][b] * C[b][a];
+      double re = on ? tr.re : 0.0, im = on ? tr.im : 0.0;
 #pragma unroll
-      for (int th = 0; th < kNumOps; ++th) {
-        acc[th][0] += wk.coef[th][0] * tr.re - wk.coef[th][1] * tr.im;
-        acc[th][1] += wk.coef[th][0] * tr.im + wk.coef[th][1] * tr.re;
+      for (int off = 32; off > 0; off >>= 1) {
+        re += __shfl_xor(re, off, 64);
+        im += __shfl_xor(im, off, 64);
       }
+      if (lane == 0) sh[l][wave] = sh[l][wave] + mk(re, im);
     }
   }
+  __syncthreads();
+  if (int(threadIdx.x) < nl) {
+    cx<double> v = mk(0.0, 0.0);
 #pragma unroll
-  for (int th = 0; th < kNumOps; ++th) out[size_t(th) * g.V + s] = mk(acc[th][0], acc[th][1]);
+    for (int w = 0; w < kNW; ++w) v = v + sh[threadIdx.x][w];
+    part[(size_t(l0 + threadIdx.x) * g.L[3] + t) * nch + ch] = v;
+  }
+}
+
+// out[i] = sum of the nch partials of entry i
+__global__ void k_chunk_sum(const cx<double> *__restrict__ part, int n, int nch, cx<double> *__restrict__ out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  cx<double> v = mk(0.0, 0.0);
+  for (int c = 0; c < nch; ++c) v = v + part[size_t(i) * nch + c];
+  out[i] = v;
 }
 
 constexpr int kWaves = kBlock / 64;
@@ -372,57 +487,122 @@ std::vector<cdouble> timeslice_rows(lqcd_ctx *c, const void *site, int nrow, Dev
   return h;
 }
 
+// Timeslice sums of every loop's trace: [loop][Lt].
+std::vector<cdouble> loop_traces(lqcd_ctx *c, const std::vector<Code> &loops, int len) {
+  const Geom &g = c->g;
+  const int Lt = g.L[3], Vs = g.V / Lt, nl = int(loops.size());
+  const int tiles = (nl + kLoopTile - 1) / kLoopTile;
+  // about 4096 workgroups, at least one chunk of 256 sites each
+  const int nch = std::max(1, std::min((Vs + kBlock - 1) / kBlock, 4096 / (Lt * tiles)));
+  Code *ld = static_cast<Code *>(c->ws[5].ensure(nl * sizeof(Code)));
+  cx<double> *out = static_cast<cx<double> *>(c->ws[6].ensure(size_t(nl) * Lt * sizeof(cdouble)));
+  cx<double> *part = static_cast<cx<double> *>(c->ws[7].ensure(size_t(nl) * Lt * nch * sizeof(cdouble)));
+  h2d(c, ld, loops.data(), nl * sizeof(Code));
+  hipLaunchKernelGGL(k_loop_trace, dim3(Lt * nch, tiles), dim3(kBlock), 0, c->stream, g,
+                     static_cast<const cx<double> *>(c->U64.ptr), ld, nl, len, nch, part);
+  LQCD_HIP(hipGetLastError());
+  hipLaunchKernelGGL(k_chunk_sum, dim3(nblocks(size_t(nl) * Lt)), dim3(kBlock), 0, c->stream, part, nl * Lt, nch,
+                     out);
+  LQCD_HIP(hipGetLastError());
+  std::vector<cdouble> h(size_t(nl) * Lt);
+  d2h(c, h.data(), out, h.size() * sizeof(cdouble));
+  return h;
+}
+
 // Tr_t(Theta P^j) for j = 0..kMaxOrder and every operator code, filled
 // once per context (point-split rows without their factor kappa).
-// The walks of length 8 (36k per site) serve only the point-split rows of
-// order 7 and are enumerated when such a row is first asked for.
+// The walks of length 8 (36k) serve only the point-split rows of order 7 and
+// are taken when such a row is first asked for.
 void ensure_walk_traces(lqcd_ctx *c, bool need_len8) {
   if (c->have_walk_traces && (!need_len8 || c->have_walk_len8)) return;
   const Geom &g = c->g;
   const int Lt = g.L[3], Vs = g.V / Lt;
+  std::vector<cdouble> T = c->walk_traces;
   if (!c->have_walk_traces) {
-    c->walk_traces.assign(size_t(kMaxOrder + 1) * kNumOps * Lt, 0.0);
-    for (int t = 0; t < Lt; ++t) c->walk_traces[t] = 12.0 * Vs;  // Tr(1) per slice
+    T.assign(size_t(kMaxOrder + 1) * kNumOps * Lt, 0.0);
+    for (int t = 0; t < Lt; ++t) T[t] = 12.0 * Vs;  // Tr(1) per slice
   }
-  std::vector<cdouble> &T = c->walk_traces;
-  DevBuf site, walks, tmp;
-  site.ensure(size_t(kNumOps) * g.V * sizeof(cdouble));
-  // odd walks cannot close on even extents; a walk of length len gives the
-  // local rows of order len and the point-split rows of order len - 1
-  const int len0 = c->have_walk_traces ? kMaxWalkLen : 2;
-  const int len1 = need_len8 ? kMaxWalkLen : kMaxWalkLen - 2;
-  for (int len = len0; len <= len1; len += 2) {
-    std::vector<Walk> ws;
-    int disp[4] = {0, 0, 0, 0}, dirs[kMaxWalkLen];
-    std::complex<double> I[4][4];
-    gamma_dense(0, I);
-    enumerate(len, g.L, 0, -1, disp, I, dirs, ws);
-    if (ws.empty()) continue;
-    // groups of consecutive walks with the same first P = len - 3 steps
-    const int P = std::max(0, len - 3);
-    std::vector<int2> gr;
-    for (int w = 0; w < int(ws.size()); ++w) {
-      const bool same = w > 0 && std::equal(ws[w].dir, ws[w].dir + P, ws[w - 1].dir);
-      if (same)
-        gr.back().y = w + 1;
-      else
-        gr.push_back(make_int2(w, w + 1));
-    }
-    walks.ensure(ws.size() * sizeof(Walk) + gr.size() * sizeof(int2));
-    h2d(c, walks.ptr, ws.data(), ws.size() * sizeof(Walk));
-    int2 *dgr = reinterpret_cast<int2 *>(static_cast<char *>(walks.ptr) + ws.size() * sizeof(Walk));
-    h2d(c, dgr, gr.data(), gr.size() * sizeof(int2));
-    hipLaunchKernelGGL(k_walk_trace, dim3(nblocks(g.V)), dim3(kBlock), 0, c->stream, g,
-                       static_cast<const cx<double> *>(c->U64.ptr), walks.as<Walk>(), dgr, int(gr.size()), P,
-                       site.as<cx<double>>());
-    LQCD_HIP(hipGetLastError());
-    std::vector<cdouble> ts = timeslice_rows(c, site.ptr, kNumOps, tmp);
+  // adds the walk's timeslice sums, weighted by its spin traces, to the rows
+  // of order j (local) and j - 1 (point-split)
+  auto add = [&](int len, const Walk &w, const cdouble *tr) {
     for (int th = 0; th < kNumOps; ++th) {
       const int j = th < kNumTheta ? len : len - 1;
-      if (j > kMaxOrder) continue;
-      for (int t = 0; t < Lt; ++t) T[(size_t(j) * kNumOps + th) * Lt + t] = ts[size_t(th) * Lt + t];
+      if (j > kMaxOrder || w.coef[th] == cdouble(0, 0)) continue;
+      cdouble *row = &T[(size_t(j) * kNumOps + th) * Lt];
+      for (int t = 0; t < Lt; ++t) {
+        const cdouble v = tr[((t + w.dt) % Lt + Lt) % Lt];
+        row[t] += w.coef[th] * (w.conj ? std::conj(v) : v);
+      }
+    }
+  };
+  auto point_split = [](Walk &w, int d, cdouble trS) {
+    w.coef[kNumTheta + (d >> 1)] = (d & 1) ? trS : -trS;
+  };
+  if (!c->have_walk_traces) {
+    // odd walks cannot close on even extents; a walk of length len gives the
+    // local rows of order len and the point-split rows of order len - 1
+    std::vector<Code> loops[kMaxWalkLen + 1];
+    std::vector<cdouble> tr[kMaxWalkLen + 1];
+    for (int len = 2; len <= kMaxWalkLen - 2; len += 2) {
+      loops[len] = enumerate_loops(len, g.L);
+      if (!loops[len].empty()) tr[len] = loop_traces(c, loops[len], len);
+      int disp[4] = {0, 0, 0, 0}, dirs[kMaxWalkLen];
+      each_walk(len, g.L, -1, 0, disp, kSpinOne, dirs, [&](const int *d, const SpinInt &S) {
+        Walk w{};
+        for (int th = 0; th < kNumTheta; ++th) w.coef[th] = spin_trace(th, S);
+        point_split(w, d[0], w.coef[0]);
+        // steps at the start that the end undoes
+        int a = 0, dt0 = 0, dt = 0;
+        while (d[a] == (d[len - 1 - a] ^ 1)) {
+          if ((d[a] >> 1) == 3) dt0 += (d[a] & 1) ? -1 : 1;
+          ++a;
+        }
+        const int n = len - 2 * a;
+        const Code code = loop_of(d + a, n, dt, w.conj);
+        w.loop = int(std::lower_bound(loops[n].begin(), loops[n].end(), code) - loops[n].begin());
+        w.dt = dt0 + dt;
+        add(len, w, &tr[n][size_t(w.loop) * Lt]);
+      });
     }
   }
+  if (need_len8) {
+    // point-split rows only, whose spin trace is the same for every rotation
+    // of a loop, the conjugate for its reverse and zero for a walk with a
+    // first step that its last one undoes
+    const int len = kMaxWalkLen;
+    const std::vector<Code> loops = enumerate_loops(len, g.L);
+    const std::vector<cdouble> tr = loops.empty() ? std::vector<cdouble>() : loop_traces(c, loops, len);
+    for (size_t l = 0; l < loops.size(); ++l) {
+      Code seen[2 * kMaxWalkLen];
+      int ns = 0, dirs[kMaxWalkLen], r[kMaxWalkLen];
+      SpinInt S = kSpinOne;
+      for (int i = 0; i < len; ++i) {
+        dirs[i] = (loops[l] >> (3 * (len - 1 - i))) & 7;
+        S = spin_hop(S, dirs[i]);
+      }
+      const cdouble trS = spin_trace(0, S);
+      if (trS == cdouble(0, 0)) continue;
+      for (int o = 0; o < 2; ++o) {
+        for (int i = 0; i < len; ++i) r[i] = o ? dirs[len - 1 - i] ^ 1 : dirs[i];
+        int tk = 0;  // timeslices from the loop's start to the rotation's
+        for (int k = 0; k < len; ++k) {
+          Code code = 0;
+          for (int i = 0; i < len; ++i) code = (code << 3) | Code(r[(k + i) % len]);
+          if (std::find(seen, seen + ns, code) == seen + ns) {
+            seen[ns++] = code;
+            Walk w{};
+            w.loop = int(l);
+            w.dt = -tk;
+            w.conj = o != 0;
+            point_split(w, r[k], o ? std::conj(trS) : trS);
+            add(len, w, &tr[l * Lt]);
+          }
+          if ((r[k] >> 1) == 3) tk += (r[k] & 1) ? -1 : 1;
+        }
+      }
+    }
+  }
+  c->walk_traces = T;
   c->have_walk_traces = true;
   if (need_len8) c->have_walk_len8 = true;
 }

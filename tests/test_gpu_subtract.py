@@ -188,3 +188,25 @@ def test_deflate_project_multi_equals_single_calls():
         ctx.deflate_project_multi(hdefl, Q, eta, [(lqcd.DEFL_ES, None, None, None)], THETAS)
     with pytest.raises(LqcdError):
         ctx.deflate_project_multi(hdefl, Q, eta, [(lqcd.DEFL_HFES, None, None, None)] * 5, THETAS)
+
+
+@pytest.mark.parametrize("dims", [(10, 14, 14, 16), (10, 2, 4, 6)])
+def test_trace_corrections_double_with_a_periodic_copy(dims):
+    """Links repeated once along x: no loop of length <= 8 winds round an
+    extent of 10 or 20, so every timeslice sum doubles.  The first lattice's
+    timeslices (1960 and 3920 sites) are more chunks of sites than a launch
+    has workgroups for and end in a ragged one; the second has windings in
+    y, z and t, in both lattices alike.  Sums of 4e3 sites times 4e4 walks in
+    two orders: 1e-12 of the largest is five digits above their rounding."""
+    require_gpu()
+    ctx, U = context(dims, 0.3, 29, 0.12)
+    U2 = np.ascontiguousarray(np.concatenate([U, U], axis=3))
+    from paper_1903_06986_amd import Context
+    ctx2 = Context((2 * dims[0],) + tuple(dims[1:]), U2, 0.12)
+    ops = tuple(range(9))
+    say("trace corrections of a doubled lattice", dims)
+    _, a = ctx.pert_subtract(7, ctx.empty(0), ops)
+    _, b = ctx2.pert_subtract(7, ctx2.empty(0), ops)
+    for op in ops:
+        scale = max(np.abs(a[op]).max(), 1e-4 * np.abs(a).max())  # some rows cancel to nothing
+        assert np.abs(b[op] - 2 * a[op]).max() <= 1e-12 * 2 * scale, op
