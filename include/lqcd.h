@@ -482,9 +482,9 @@ lqcd_status lqcd_timer_read(lqcd_ctx *ctx, int kclass, double *ms, double *bytes
  * the kept vectors of the last restart on every this-many-th step of a cycle
  * and on its last step (1..64, default 16).  LQCD_TUNE_ARNOLDI_STEPS: 1 to
  * 6 (default 4) Arnoldi steps per pass over the basis in the GMRES-Proj
- * cycles with a 16-bit basis (s > 1: the s powers (Mhat - 1)^k v_j,
+ * cycles on the even/odd system (s > 1: the s powers (Mhat - 1)^k v_j,
  * k = 1..s, are orthogonalised together, reading the basis once for all
- * of them; same Krylov space).  LQCD_TUNE_SSTEP_Z16: 0 (default) keeps
+ * of them; same Krylov space; FP64 and FP32 bases take at most 4).  LQCD_TUNE_SSTEP_Z16: 0 (default) keeps
  * those powers in FP32; 1 stores them in the basis's 16-bit form when the
  * basis is FP16 (half the bytes for the stencil and the Gram-Schmidt passes
  * that read them; the Arnoldi relation then carries their rounding; a BF16

@@ -788,25 +788,25 @@ constexpr int ilog2(int n) { return n <= 1 ? 0 : 1 + ilog2(n / 2); }
 // log2(NP) shuffles instead of 6 NP.  Afterwards lane l holds in v[0] the
 // total of value l >> (6 - log2 NP).  (Recursion over the step, so that
 // every index into v is a compile-time constant.)
-template <int CNT, int OFF, int NP>
-__device__ inline void wave_sum_multi_step(float (&v)[NP], int lane) {
+template <int CNT, int OFF, class T, int NP>
+__device__ inline void wave_sum_multi_step(T (&v)[NP], int lane) {
   if constexpr (CNT > 1) {
     const bool hi = (lane & OFF) != 0;
 #pragma unroll
     for (int k = 0; k < CNT / 2; ++k) {
-      const float give = hi ? v[k] : v[k + CNT / 2];
-      const float keep = hi ? v[k + CNT / 2] : v[k];
+      const T give = hi ? v[k] : v[k + CNT / 2];
+      const T keep = hi ? v[k + CNT / 2] : v[k];
       v[k] = keep + __shfl_xor(give, OFF, 64);
     }
-    wave_sum_multi_step<CNT / 2, OFF / 2, NP>(v, lane);
+    wave_sum_multi_step<CNT / 2, OFF / 2>(v, lane);
   } else {
 #pragma unroll
     for (int off = OFF; off > 0; off >>= 1) v[0] += __shfl_xor(v[0], off, 64);
   }
 }
-template <int NP>
-__device__ inline void wave_sum_multi(float (&v)[NP], int lane) {
-  wave_sum_multi_step<NP, 32, NP>(v, lane);
+template <class T, int NP>
+__device__ inline void wave_sum_multi(T (&v)[NP], int lane) {
+  wave_sum_multi_step<NP, 32>(v, lane);
 }
 
 // Accumulates the Gram matrix of the S vectors of one site (layout of
@@ -889,7 +889,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(S <
       cur = nx1;
       nx1 = nx2;
     }
-    wave_sum_multi<NP>(v, lane);
+    wave_sum_multi(v, lane);
     if (writer) my[2 * (wk * J + j) + wri] = v[0];
   }
   if (gpart) {
@@ -901,7 +901,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(S <
 #pragma unroll
     for (int q = 0; q < NQ; ++q) g[q] = 0.f;
     if (on) gram_site<S>(a, g);
-    wave_sum_multi<NQ>(g, lane);
+    wave_sum_multi(g, lane);
     const int gq = lane >> (6 - LQ);
     if ((lane & ((64 >> LQ) - 1)) == 0) gsh[wave][gq] = g[0];
     __syncthreads();
@@ -1045,6 +1045,285 @@ __global__ void __launch_bounds__(kBlock)
       for (int c = 0; c < 12; ++c) y[c] = y[c] + a[l][c] * fl;
     }
     (void)hstore_site<K>(out + m * out_vs, Vh, i, y);
+  }
+}
+
+// ------------------------------------------ s-step Arnoldi (plain basis)
+// The same block step on a basis of plain FP64 or FP32 vectors, every
+// product and sum in FP64: S vectors against one read of the basis.  A lane
+// holds U units of 16 bytes (one FP64 or two FP32 complex numbers) of the S
+// vectors and streams the same units of every basis vector, two vectors
+// ahead; the 2 S sums of a basis vector cost one exchange butterfly per wave.
+// Bound by the basis read: 2 / S of it per Arnoldi step where the one-step
+// form reads it twice.
+template <class R>
+struct Unit;
+template <>
+struct Unit<double> {
+  static constexpr int EV = 1;
+  typedef double raw __attribute__((ext_vector_type(2)));
+  __device__ static cx<double> get(const raw &q, int) { return mk(q.x, q.y); }
+  __device__ static void set(raw &q, int, cx<double> v) {
+    q.x = v.re;
+    q.y = v.im;
+  }
+};
+template <>
+struct Unit<float> {
+  static constexpr int EV = 2;
+  typedef float raw __attribute__((ext_vector_type(4)));
+  __device__ static cx<double> get(const raw &q, int e) {
+    return e ? mk(double(q.z), double(q.w)) : mk(double(q.x), double(q.y));
+  }
+  __device__ static void set(raw &q, int e, cx<double> v) {
+    if (e) {
+      q.z = float(v.re);
+      q.w = float(v.im);
+    } else {
+      q.x = float(v.re);
+      q.y = float(v.im);
+    }
+  }
+};
+
+// U units of a vector at the lane's places (64 apart, nun units in all).
+template <class R, int U>
+struct UnitSet {
+  using Un = Unit<R>;
+  typename Un::raw q[U];
+  __device__ void load(const cx<R> *v, size_t base, size_t nun) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const size_t i = base + size_t(u) * 64;
+      q[u] = typename Un::raw(R(0));
+      if (i < nun) q[u] = reinterpret_cast<const typename Un::raw *>(v)[i];
+    }
+  }
+  __device__ void load_nt(const cx<R> *v, size_t base, size_t nun) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const size_t i = base + size_t(u) * 64;
+      q[u] = typename Un::raw(R(0));
+      if (i < nun) q[u] = __builtin_nontemporal_load(reinterpret_cast<const typename Un::raw *>(v) + i);
+    }
+  }
+  __device__ void store(cx<R> *v, size_t base, size_t nun) const {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const size_t i = base + size_t(u) * 64;
+      if (i < nun) reinterpret_cast<typename Un::raw *>(v)[i] = q[u];
+    }
+  }
+  __device__ cx<double> get(int e) const { return Un::get(q[e / Un::EV], e % Un::EV); }
+  __device__ void set(int e, cx<double> v) { Un::set(q[e / Un::EV], e % Un::EV, v); }
+};
+
+// Dots of the S vectors (part[r][block][S J], entry k J + j for w_k against
+// V_j) and, with gpart, their Gram matrix (gpart[(r nblk + b) S^2 + q]), per
+// workgroup.  Dynamic LDS: kWaves * 2 S J doubles.
+template <class R, int S, int U>
+__global__ void __launch_bounds__(kBlock)
+    k_mdots_part(const cx<R> *__restrict__ V, size_t ldv, size_t V_rs, int J, const cx<R> *__restrict__ w,
+                 size_t w_vs, size_t w_rs, size_t n, double *__restrict__ part, double *__restrict__ gpart,
+                 const int *__restrict__ flag) {
+  constexpr int E = U * Unit<R>::EV;
+  constexpr int NP = pow2_at_least(2 * S), LB = ilog2(NP);
+  extern __shared__ double dshd[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = blockIdx.y;
+  if (flag && flag[r] == 0) return;
+  const size_t nun = n / Unit<R>::EV;
+  const size_t base = (size_t(blockIdx.x) * kWaves + wave) * (64 * U) + lane;
+  const int nv = 2 * S * J;
+  V += r * V_rs;
+  w += r * w_rs;
+  cx<double> a[S][E];
+#pragma unroll
+  for (int k = 0; k < S; ++k) {
+    UnitSet<R, U> q;
+    q.load(w + k * w_vs, base, nun);
+#pragma unroll
+    for (int e = 0; e < E; ++e) a[k][e] = q.get(e);
+  }
+  double *my = dshd + wave * nv;
+  const int idx = lane >> (6 - LB);  // the value this lane ends up with
+  const bool writer = (lane & ((64 >> LB) - 1)) == 0 && idx < 2 * S;
+  const int wk = idx >> 1, wri = idx & 1;
+  UnitSet<R, U> cur, nx1, nx2;
+  if (J > 0) cur.load_nt(V, base, nun);
+  if (J > 1) nx1.load_nt(V + ldv, base, nun);
+  for (int j = 0; j < J; ++j) {
+    if (j + 2 < J) nx2.load_nt(V + size_t(j + 2) * ldv, base, nun);
+    double v[NP];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) v[k] = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const cx<double> x = cur.get(e);
+#pragma unroll
+      for (int k = 0; k < S; ++k) {
+        const cx<double> p = cmulc(x, a[k][e]);
+        v[2 * k] += p.re;
+        v[2 * k + 1] += p.im;
+      }
+    }
+    cur = nx1;
+    nx1 = nx2;
+    wave_sum_multi(v, lane);
+    if (writer) my[2 * (wk * J + j) + wri] = v[0];
+  }
+  if (gpart) {
+    constexpr int NG = S * S, NQ = pow2_at_least(NG), LQ = ilog2(NQ);
+    __shared__ double gsh[kWaves][NQ];
+    double g[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) g[q] = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+#pragma unroll
+      for (int l = 0; l < S; ++l) {
+        g[l] += a[l][e].re * a[l][e].re + a[l][e].im * a[l][e].im;
+#pragma unroll
+        for (int m = l + 1; m < S; ++m) {
+          const cx<double> p = cmulc(a[l][e], a[m][e]);
+          g[gram_pair_idx(S, l, m)] += p.re;
+          g[gram_pair_idx(S, l, m) + 1] += p.im;
+        }
+      }
+    wave_sum_multi(g, lane);
+    if ((lane & ((64 >> LQ) - 1)) == 0) gsh[wave][lane >> (6 - LQ)] = g[0];
+    __syncthreads();
+    if (threadIdx.x < NG) {
+      double t = 0;
+#pragma unroll
+      for (int q = 0; q < kWaves; ++q) t += gsh[q][threadIdx.x];
+      gpart[(size_t(r) * gridDim.x + blockIdx.x) * NG + threadIdx.x] = t;
+    }
+  }
+  __syncthreads();
+  double *po = part + (size_t(r) * gridDim.x + blockIdx.x) * size_t(nv);
+  for (int t = threadIdx.x; t < nv; t += kBlock) {
+    double s = 0;
+#pragma unroll
+    for (int q = 0; q < kWaves; ++q) s += dshd[q * nv + t];
+    po[t] = s;
+  }
+}
+
+// y_k = w_k - V c_k for the S vectors (c_k at coef[r][k J]).  DIRECT (the
+// right-hand sides whose flag is clear): out slot m (out + r out_rs + m
+// out_vs) = sum_{l <= m} F[l][m] y_l, F = f[r][S][S]; w is not written.  Else
+// (flag set): w_k = y_k in place, with the per-workgroup Gram partials of the
+// stored y_k in part (or not).
+template <class R, int S, int U, bool DIRECT>
+__global__ void __launch_bounds__(kBlock)
+    k_maxpys(const cx<R> *__restrict__ V, size_t ldv, size_t V_rs, int J, const cx<double> *__restrict__ coef,
+             size_t coef_rs, cx<R> *w, size_t w_vs, size_t w_rs, size_t n, double *__restrict__ part,
+             const int *__restrict__ flag, const cx<double> *__restrict__ f, cx<R> *out, size_t out_vs,
+             size_t out_rs) {
+  constexpr int E = U * Unit<R>::EV, NG = S * S;
+  extern __shared__ cx<double> scd[];  // S J coefficients
+  const int r = blockIdx.y;
+  if ((flag[r] != 0) == DIRECT) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const size_t nun = n / Unit<R>::EV;
+  const size_t base = (size_t(blockIdx.x) * kWaves + wave) * (64 * U) + lane;
+  V += r * V_rs;
+  w += r * w_rs;
+  coef += r * coef_rs;
+  for (int t = threadIdx.x; t < S * J; t += kBlock) scd[t] = coef[t];
+  __syncthreads();
+  cx<double> a[S][E];
+#pragma unroll
+  for (int k = 0; k < S; ++k) {
+    UnitSet<R, U> q;
+    q.load(w + k * w_vs, base, nun);
+#pragma unroll
+    for (int e = 0; e < E; ++e) a[k][e] = q.get(e);
+  }
+  UnitSet<R, U> cur, nx1, nx2;
+  if (J > 0) cur.load_nt(V, base, nun);
+  if (J > 1) nx1.load_nt(V + ldv, base, nun);
+  for (int j = 0; j < J; ++j) {
+    if (j + 2 < J) nx2.load_nt(V + size_t(j + 2) * ldv, base, nun);
+#pragma unroll
+    for (int k = 0; k < S; ++k) {
+      const cx<double> c = scd[k * J + j];
+#pragma unroll
+      for (int e = 0; e < E; ++e) a[k][e] = a[k][e] - cur.get(e) * c;
+    }
+    cur = nx1;
+    nx1 = nx2;
+  }
+  if constexpr (DIRECT) {
+    const cx<double> *fr = f + size_t(r) * NG;
+#pragma unroll
+    for (int m = 0; m < S; ++m) {
+      UnitSet<R, U> q;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        cx<double> y = mk(0.0, 0.0);
+#pragma unroll
+        for (int l = 0; l <= m; ++l) y = y + a[l][e] * fr[l * S + m];
+        q.set(e, y);
+      }
+      q.store(out + r * out_rs + m * out_vs, base, nun);
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < S; ++k) {
+      UnitSet<R, U> q;
+#pragma unroll
+      for (int e = 0; e < E; ++e) q.set(e, a[k][e]);
+      q.store(w + k * w_vs, base, nun);
+#pragma unroll
+      for (int e = 0; e < E; ++e) a[k][e] = q.get(e);  // as stored
+    }
+    if (part) {
+      __shared__ double sh[NG][kWaves];
+      double g[NG];
+#pragma unroll
+      for (int q = 0; q < NG; ++q) g[q] = 0;
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+#pragma unroll
+        for (int l = 0; l < S; ++l) {
+          g[l] += a[l][e].re * a[l][e].re + a[l][e].im * a[l][e].im;
+#pragma unroll
+          for (int m = l + 1; m < S; ++m) {
+            const cx<double> p = cmulc(a[l][e], a[m][e]);
+            g[gram_pair_idx(S, l, m)] += p.re;
+            g[gram_pair_idx(S, l, m) + 1] += p.im;
+          }
+        }
+      block_sum<NG>(g, sh);
+      if (threadIdx.x == 0)
+#pragma unroll
+        for (int q = 0; q < NG; ++q) part[(size_t(r) * gridDim.x + blockIdx.x) * NG + q] = g[q];
+    }
+  }
+}
+
+// Slot m = sum_{l <= m} F[l][m] w_l for the right-hand sides whose flag is
+// set (the explicit path's store).
+template <class R, int S>
+__global__ void __launch_bounds__(kBlock)
+    k_sstore(const cx<R> *__restrict__ w, size_t w_vs, size_t w_rs, const cx<double> *__restrict__ f, cx<R> *out,
+             size_t out_vs, size_t out_rs, size_t n, const int *__restrict__ flag) {
+  const int r = blockIdx.y;
+  if (flag[r] == 0) return;
+  const size_t i = size_t(blockIdx.x) * kBlock + threadIdx.x;
+  if (i >= n) return;
+  f += size_t(r) * S * S;
+  cx<double> a[S];
+#pragma unroll
+  for (int k = 0; k < S; ++k) a[k] = ld64(w + r * w_rs + k * w_vs + i);
+#pragma unroll
+  for (int m = 0; m < S; ++m) {
+    cx<double> y = mk(0.0, 0.0);
+#pragma unroll
+    for (int l = 0; l <= m; ++l) y = y + a[l] * f[l * S + m];
+    stc(out + r * out_rs + m * out_vs + i, mk<R>(R(y.re), R(y.im)));
   }
 }
 
@@ -1633,6 +1912,119 @@ void recombine(lqcd_ctx *c, void *V, size_t ldv, int Jin, const cdouble *P, size
 INST(double)
 INST(float)
 #undef INST
+
+// ------------------------------------- s-step Arnoldi, plain basis (host)
+// Units per lane: two where that still gives every SIMD of the chip four
+// waves, one on smaller fields.  (The 16-byte units need even n; n = 12 Vh.)
+template <class R>
+bool two_units(size_t n, int nrhs) {
+  return n / Unit<R>::EV / 128 * size_t(nrhs) >= 4096;
+}
+
+template <class R>
+int sstep_blocks(size_t n, int nrhs) {
+  const size_t per = size_t(kBlock) * (two_units<R>(n, nrhs) ? 2 : 1);
+  return int((n / Unit<R>::EV + per - 1) / per);
+}
+
+template <class R, int S>
+void multi_dots_part(lqcd_ctx *c, const void *V, size_t ldv, size_t V_rs, int J, const void *w, size_t w_vs,
+                     size_t w_rs, size_t n, int nrhs, double *part, double *gpart, const int *flag) {
+  if (J <= 0 || nrhs <= 0) return;
+  LQCD_CHECK(J <= kMaxJ, LQCD_EINVAL, "basis of %d vectors exceeds %d", J, kMaxJ);
+  const dim3 grid(sstep_blocks<R>(n, nrhs), nrhs);
+  const size_t shm = size_t(kWaves) * 2 * S * J * sizeof(double);
+  Timed tm(c, LQCD_KC_DOT, flag ? 0.0 : double(J + S) * n * nrhs * sizeof(cx<R>));
+  const cx<R> *Vp = static_cast<const cx<R> *>(V), *wp = static_cast<const cx<R> *>(w);
+  if (two_units<R>(n, nrhs)) {
+    if (shm > 48 * 1024)
+      LQCD_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mdots_part<R, S, 2>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, int(shm)));
+    LQCD_TLAUNCH(tm, true, true, (k_mdots_part<R, S, 2>), grid, dim3(kBlock), shm, c->stream, Vp, ldv, V_rs, J, wp,
+                 w_vs, w_rs, n, part, gpart, flag);
+  } else {
+    if (shm > 48 * 1024)
+      LQCD_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mdots_part<R, S, 1>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, int(shm)));
+    LQCD_TLAUNCH(tm, true, true, (k_mdots_part<R, S, 1>), grid, dim3(kBlock), shm, c->stream, Vp, ldv, V_rs, J, wp,
+                 w_vs, w_rs, n, part, gpart, flag);
+  }
+  LQCD_HIP(hipGetLastError());
+}
+
+void sum_dots(lqcd_ctx *c, const double *part, int nblk, int J, int nrhs, cdouble *out, size_t out_rs,
+              const int *flag) {
+  hipLaunchKernelGGL(k_mdot_final, dim3(J, nrhs), dim3(kBlock), 0, c->stream, part, nblk, J,
+                     reinterpret_cast<cx<double> *>(out), out_rs, flag);
+  LQCD_HIP(hipGetLastError());
+}
+
+template <class R, int S, bool DIRECT>
+void multi_axpys_impl(lqcd_ctx *c, const void *V, size_t ldv, size_t V_rs, int J, const cdouble *coef,
+                      size_t coef_rs, void *w, size_t w_vs, size_t w_rs, size_t n, int nrhs, double *part,
+                      const int *flag, const cdouble *f, void *out, size_t out_vs, size_t out_rs) {
+  if (nrhs <= 0) return;
+  LQCD_CHECK(J <= kMaxJ, LQCD_EINVAL, "basis of %d vectors exceeds %d", J, kMaxJ);
+  const dim3 grid(sstep_blocks<R>(n, nrhs), nrhs);
+  const size_t shm = size_t(S) * J * sizeof(cx<double>);
+  // credited as if every right-hand side took the direct path
+  Timed tm(c, LQCD_KC_AXPY, DIRECT ? double(J + 2 * S) * n * nrhs * sizeof(cx<R>) : 0.0);
+  const cx<R> *Vp = static_cast<const cx<R> *>(V);
+  const cx<double> *cf = reinterpret_cast<const cx<double> *>(coef), *fp = reinterpret_cast<const cx<double> *>(f);
+  cx<R> *wp = static_cast<cx<R> *>(w), *op = static_cast<cx<R> *>(out);
+  if (two_units<R>(n, nrhs))
+    LQCD_TLAUNCH(tm, true, true, (k_maxpys<R, S, 2, DIRECT>), grid, dim3(kBlock), shm, c->stream, Vp, ldv, V_rs, J,
+                 cf, coef_rs, wp, w_vs, w_rs, n, part, flag, fp, op, out_vs, out_rs);
+  else
+    LQCD_TLAUNCH(tm, true, true, (k_maxpys<R, S, 1, DIRECT>), grid, dim3(kBlock), shm, c->stream, Vp, ldv, V_rs, J,
+                 cf, coef_rs, wp, w_vs, w_rs, n, part, flag, fp, op, out_vs, out_rs);
+  LQCD_HIP(hipGetLastError());
+}
+
+template <class R, int S>
+void multi_axpys(lqcd_ctx *c, const void *V, size_t ldv, size_t V_rs, int J, const cdouble *coef, size_t coef_rs,
+                 void *w, size_t w_vs, size_t w_rs, size_t n, int nrhs, double *part, const int *flag) {
+  multi_axpys_impl<R, S, false>(c, V, ldv, V_rs, J, coef, coef_rs, w, w_vs, w_rs, n, nrhs, part, flag, nullptr,
+                                nullptr, 0, 0);
+}
+
+template <class R, int S>
+void multi_axpys_store(lqcd_ctx *c, const void *V, size_t ldv, size_t V_rs, int J, const cdouble *coef,
+                       size_t coef_rs, const void *w, size_t w_vs, size_t w_rs, size_t n, int nrhs, const int *flag,
+                       const cdouble *f, void *out, size_t out_vs, size_t out_rs) {
+  multi_axpys_impl<R, S, true>(c, V, ldv, V_rs, J, coef, coef_rs, const_cast<void *>(w), w_vs, w_rs, n, nrhs,
+                               nullptr, flag, f, out, out_vs, out_rs);
+}
+
+template <class R, int S>
+void sstore(lqcd_ctx *c, const void *w, size_t w_vs, size_t w_rs, const cdouble *f, void *out, size_t out_vs,
+            size_t out_rs, size_t n, int nrhs, const int *flag) {
+  if (nrhs <= 0) return;
+  hipLaunchKernelGGL((k_sstore<R, S>), dim3(nblocks(n), nrhs), dim3(kBlock), 0, c->stream,
+                     static_cast<const cx<R> *>(w), w_vs, w_rs, reinterpret_cast<const cx<double> *>(f),
+                     static_cast<cx<R> *>(out), out_vs, out_rs, n, flag);
+  LQCD_HIP(hipGetLastError());
+}
+
+#define PINST(R, S)                                                                                          \
+  template void multi_dots_part<R, S>(lqcd_ctx *, const void *, size_t, size_t, int, const void *, size_t,   \
+                                      size_t, size_t, int, double *, double *, const int *);                 \
+  template void multi_axpys<R, S>(lqcd_ctx *, const void *, size_t, size_t, int, const cdouble *, size_t,    \
+                                  void *, size_t, size_t, size_t, int, double *, const int *);               \
+  template void multi_axpys_store<R, S>(lqcd_ctx *, const void *, size_t, size_t, int, const cdouble *,      \
+                                        size_t, const void *, size_t, size_t, size_t, int, const int *,      \
+                                        const cdouble *, void *, size_t, size_t);                            \
+  template void sstore<R, S>(lqcd_ctx *, const void *, size_t, size_t, const cdouble *, void *, size_t,      \
+                             size_t, size_t, int, const int *);
+PINST(double, 2)
+PINST(double, 3)
+PINST(double, 4)
+PINST(float, 2)
+PINST(float, 3)
+PINST(float, 4)
+#undef PINST
+template int sstep_blocks<double>(size_t, int);
+template int sstep_blocks<float>(size_t, int);
 
 // ------------------------------------------------ 16-bit stored bases (host)
 // Stored bytes of one 12 Vh-element vector: 48 per site plus the 4-byte scale.

@@ -201,6 +201,10 @@ void apply_dd_h_pair(lqcd_ctx *c, const void *in, void *out, void *tmp_odd, int 
                      size_t stmp);
 void apply_dd_pair(lqcd_ctx *c, const void *in, void *out, void *tmp_odd, int nrhs, size_t sin, size_t sout,
                    size_t stmp);
+// Mhat - 1 on plain fields of precision R.
+template <class R>
+void apply_dd(lqcd_ctx *c, const void *in, void *out, void *tmp_odd, int nrhs, size_t sin, size_t sout,
+              size_t stmp);
 // Mhat - 1 from a 16-bit stored input to a 16-bit stored output (the
 // per-site scaled form of half.h, kind KIND; strides in words).
 template <int KIND>

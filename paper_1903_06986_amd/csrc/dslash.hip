@@ -598,6 +598,28 @@ void apply_dd_pair(lqcd_ctx *c, const void *in, void *out, void *tmp_odd, int nr
       sout);
 }
 
+// Mhat - 1 on plain fields of precision R.
+template <class R>
+void apply_dd(lqcd_ctx *c, const void *in, void *out, void *tmp_odd, int nrhs, size_t sin, size_t sout,
+              size_t stmp) {
+  if (nrhs <= 0) return;
+  const double k = c->kappa;
+  if constexpr (std::is_same<R, float>::value) {
+    const SrcPlain<float> none{nullptr};
+    launch_hop_src<float, false, false, false, SrcPlain<float>, SrcPlain<float>, OutPair>(
+        c, 1, SrcPlain<float>{static_cast<const cx<float> *>(in)}, none, tmp_odd, cdouble(0, 0), 1.0, nrhs, sin, 0,
+        stmp);
+    launch_hop_src<float, false, false, false, SrcPair, SrcPlain<float>>(
+        c, 0, SrcPair{static_cast<const cx<float> *>(tmp_odd)}, none, out, cdouble(0, 0), -k * k, nrhs, stmp, 0,
+        sout);
+  } else {
+    hop_half<R>(c, 1, in, nullptr, tmp_odd, cdouble(0, 0), 1.0, false, false, nrhs, sin, 0, stmp);
+    hop_half<R>(c, 0, tmp_odd, nullptr, out, cdouble(0, 0), -k * k, false, false, nrhs, stmp, 0, sout);
+  }
+}
+template void apply_dd<double>(lqcd_ctx *, const void *, void *, void *, int, size_t, size_t, size_t);
+template void apply_dd<float>(lqcd_ctx *, const void *, void *, void *, int, size_t, size_t, size_t);
+
 template void hop_half<double>(lqcd_ctx *, int, const void *, const void *, void *, cdouble, double,
                                bool, bool, int, size_t, size_t, size_t);
 template void hop_half<float>(lqcd_ctx *, int, const void *, const void *, void *, cdouble, double,

@@ -117,6 +117,29 @@ void hmulti_axpys_store(lqcd_ctx *c, const void *V, size_t ldv, size_t V_rs, int
 template <int KIND, int S, bool W16>
 void hsstore(lqcd_ctx *c, const void *w, size_t w_vs, size_t w_rs, const cdouble *f, void *out, size_t out_vs,
              size_t out_rs, size_t n, int nrhs, const int *flag);
+// The same on a plain basis of precision R, S = 2 .. 4 (vectors and strides
+// in complex elements, every sum in FP64).  multi_dots_part leaves the dots in
+// per-workgroup partials part[(r nblk + b) S J + k J + j] (complex as re, im)
+// and the Gram matrix in gpart, nblk = sstep_blocks<R>(n, nrhs); sum_dots adds
+// them: out[r out_rs + q], q < J (of S J entries).  multi_axpys acts on the
+// right-hand sides whose flag is set, multi_axpys_store on the others.
+template <class R>
+int sstep_blocks(size_t n, int nrhs);
+template <class R, int S>
+void multi_dots_part(lqcd_ctx *c, const void *V, size_t ldv, size_t V_rs, int J, const void *w, size_t w_vs,
+                     size_t w_rs, size_t n, int nrhs, double *part, double *gpart, const int *flag);
+void sum_dots(lqcd_ctx *c, const double *part, int nblk, int J, int nrhs, cdouble *out, size_t out_rs,
+              const int *flag);
+template <class R, int S>
+void multi_axpys(lqcd_ctx *c, const void *V, size_t ldv, size_t V_rs, int J, const cdouble *coef, size_t coef_rs,
+                 void *w, size_t w_vs, size_t w_rs, size_t n, int nrhs, double *part, const int *flag);
+template <class R, int S>
+void multi_axpys_store(lqcd_ctx *c, const void *V, size_t ldv, size_t V_rs, int J, const cdouble *coef,
+                       size_t coef_rs, const void *w, size_t w_vs, size_t w_rs, size_t n, int nrhs, const int *flag,
+                       const cdouble *f, void *out, size_t out_vs, size_t out_rs);
+template <class R, int S>
+void sstore(lqcd_ctx *c, const void *w, size_t w_vs, size_t w_rs, const cdouble *f, void *out, size_t out_vs,
+            size_t out_rs, size_t n, int nrhs, const int *flag);
 // Index of the Gram entry w_l^H w_m (l <= m) in those partials.
 __host__ __device__ constexpr int gram_pair_idx(int S, int l, int m) {
   return l == m ? l : S + 2 * (l * (2 * S - l - 1) / 2 + (m - l - 1));

@@ -125,13 +125,13 @@ __device__ inline int chol_gram(const double *g, cx<double> (&R)[S][S], double p
 }
 
 // Sums the S^2 Gram partials of one right-hand side over nblk workgroups
-// (one 64-lane block; every lane ends with the totals).
+// (one wave; every lane ends with the totals).
 template <int S>
 __device__ inline void gram_total(const double *__restrict__ part, int r, int nblk, double (&g)[S * S]) {
   constexpr int NG = S * S;
 #pragma unroll
   for (int q = 0; q < NG; ++q) g[q] = 0;
-  for (int b = threadIdx.x; b < nblk; b += blockDim.x)
+  for (int b = threadIdx.x & 63; b < nblk; b += 64)
 #pragma unroll
     for (int q = 0; q < NG; ++q) g[q] += part[(size_t(r) * nblk + b) * NG + q];
 #pragma unroll
@@ -156,21 +156,19 @@ constexpr double kPivotMin = 1e-3;
 // passes on each vector (|y_k|^2 at least eta2 |z_k|^2) and each Cholesky
 // pivot keeps kPivotMin of its diagonal entry; otherwise the explicit path
 // (flag set, counted as a second pass): update in place, second block
-// pass, Gram matrix of the final vectors.
+// pass, Gram matrix of the final vectors.  One wave per right-hand side r.
 template <int S>
-__global__ void k_sstep_plan(const double *__restrict__ gpart, int nblk, const cx<double> *__restrict__ C, size_t ldc,
-                             int J, double *__restrict__ G, int *__restrict__ flag, int *__restrict__ reorth_count,
-                             double eta2) {
+__device__ inline void sstep_plan(int r, const double *gpart, int nblk, const cx<double> *C, size_t ldc, int J,
+                                  double *G, int *flag, int *reorth_count, double eta2) {
   constexpr int NG = S * S;
   constexpr int NPR = S * (S + 1) / 2;
-  const int r = blockIdx.x;
   double g[NG];
   gram_total<S>(gpart, r, nblk, g);
   // C^H C over the J basis vectors, pairs l <= m in the order of gram_pair_idx
   double cc[2 * NPR];
 #pragma unroll
   for (int q = 0; q < 2 * NPR; ++q) cc[q] = 0;
-  for (int i = threadIdx.x; i < J; i += blockDim.x) {
+  for (int i = threadIdx.x & 63; i < J; i += 64) {
     cx<double> cv[S];
 #pragma unroll
     for (int l = 0; l < S; ++l) cv[l] = C[r * ldc + size_t(l) * J + i];
@@ -188,7 +186,7 @@ __global__ void k_sstep_plan(const double *__restrict__ gpart, int nblk, const c
   for (int q = 0; q < 2 * NPR; ++q)
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) cc[q] += __shfl_xor(cc[q], off, 64);
-  if (threadIdx.x != 0) return;
+  if ((threadIdx.x & 63) != 0) return;
   double gp[NG];
   int need = 0;
   {
@@ -216,9 +214,15 @@ __global__ void k_sstep_plan(const double *__restrict__ gpart, int nblk, const c
   flag[r] = need;
   if (need) reorth_count[r] += 1;
 }
+template <int S>
+__global__ void k_sstep_plan(const double *__restrict__ gpart, int nblk, const cx<double> *__restrict__ C, size_t ldc,
+                             int J, double *__restrict__ G, int *__restrict__ flag, int *__restrict__ reorth_count,
+                             double eta2) {
+  sstep_plan<S>(blockIdx.x, gpart, nblk, C, ldc, J, G, flag, reorth_count, eta2);
+}
 
 // Columns j .. j + S - 1 of Hbar from the block z_k = B^k v_j, k = 1..S,
-// B = A - sigma (one 64-lane block per right-hand side).  With the
+// B = A - sigma (one workgroup per right-hand side r).  With the
 // projected block Y = Z - V C = Q R (R the Cholesky factor of its Gram
 // matrix, Q = [v_{j+1} .. v_{j+S}]), z_k has the coordinates
 // zeta_k = (c_k; R[0..k)[k]) in the basis [V, Q], and
@@ -237,17 +241,16 @@ __global__ void k_sstep_plan(const double *__restrict__ gpart, int nblk, const c
 // zero.  Hbar's earlier columns must be Hessenberg (columns 0 .. j - 1 of
 // an Arnoldi process started at column 0).
 template <int S, bool EXPLICIT>
-__global__ void k_sstep_finish(cx<double> *__restrict__ Hd, size_t Hrs, int ldh, int j,
-                               const cx<double> *__restrict__ C1, const cx<double> *__restrict__ C2, size_t ldc,
-                               const double *__restrict__ part, int nblk, const double *__restrict__ G,
-                               const int *__restrict__ flag, double sigma, cx<double> *__restrict__ f) {
+__device__ inline void sstep_finish(int r, cx<double> *Hd, size_t Hrs, int ldh, int j, const cx<double> *C1,
+                                    const cx<double> *C2, size_t ldc, const double *part, int nblk, const double *G,
+                                    const int *flag, double sigma, cx<double> *f) {
   constexpr int NG = S * S;
   constexpr int LDB = kSstepMaxJ + S + 1;
   __shared__ cx<double> sc[S][kSstepMaxJ];
   __shared__ cx<double> sb[S][LDB];
   __shared__ cx<double> sR[S][S];
   __shared__ int st;
-  const int r = blockIdx.x, J = j + 1;
+  const int J = j + 1;
   if ((flag[r] != 0) != EXPLICIT) return;
   for (int i = threadIdx.x; i < J; i += blockDim.x)
 #pragma unroll
@@ -322,6 +325,41 @@ __global__ void k_sstep_finish(cx<double> *__restrict__ Hd, size_t Hrs, int ldh,
     }
     __syncthreads();
   }
+}
+template <int S, bool EXPLICIT>
+__global__ void k_sstep_finish(cx<double> *__restrict__ Hd, size_t Hrs, int ldh, int j,
+                               const cx<double> *__restrict__ C1, const cx<double> *__restrict__ C2, size_t ldc,
+                               const double *__restrict__ part, int nblk, const double *__restrict__ G,
+                               const int *__restrict__ flag, double sigma, cx<double> *__restrict__ f) {
+  sstep_finish<S, EXPLICIT>(blockIdx.x, Hd, Hrs, ldh, j, C1, C2, ldc, part, nblk, G, flag, sigma, f);
+}
+
+// Between the dot pass and the update of a block, in one launch: the sums of
+// the dots over nblk workgroups into C1 (ldc apart), the plan, and for the
+// right-hand sides on the direct path the Hessenberg columns.  One workgroup
+// per right-hand side; chosen while the sums are short (up to kMidBlocks
+// workgroups), where three launches would cost more than the sums.
+constexpr int kMidBlocks = 96;
+template <int S>
+__global__ void __launch_bounds__(kBlock)
+    k_sstep_mid(const double *__restrict__ dpart, const double *__restrict__ gpart, int nblk, cx<double> *C1,
+                size_t ldc, double *G, int *flag, int *reorth_count, double eta2, cx<double> *Hd, size_t Hrs,
+                int ldh, int j, double sigma, cx<double> *f) {
+  const int r = blockIdx.x, J = j + 1;
+  for (int q = threadIdx.x; q < S * J; q += kBlock) {
+    double re = 0, im = 0;
+#pragma unroll 8
+    for (int b = 0; b < nblk; ++b) {
+      const double *p = dpart + ((size_t(r) * nblk + b) * (S * J) + q) * 2;
+      re += p[0];
+      im += p[1];
+    }
+    C1[r * ldc + q] = mk(re, im);
+  }
+  __syncthreads();
+  if (threadIdx.x < 64) sstep_plan<S>(r, gpart, nblk, C1, ldc, J, G, flag, reorth_count, eta2);
+  __syncthreads();
+  sstep_finish<S, false>(r, Hd, Hrs, ldh, j, C1, C1, ldc, nullptr, 0, G, flag, sigma, f);
 }
 
 __global__ void k_izero(int *__restrict__ p, int n) {
@@ -402,6 +440,13 @@ struct Op {
     const size_t hl = half_len(c->g);
     void *t = tmp->ensure(hl * size_t(nb) * sizeof(cx<float>));
     apply_dd_pair(c, in, out, t, nb, sin, sout, hl);
+  }
+  // Mhat - 1 on plain vectors of precision R
+  void apply_dd_plain(const void *in, size_t sin, void *out, size_t sout, int nb) const {
+    if (nb <= 0) return;
+    const size_t hl = half_len(c->g);
+    void *t = tmp->ensure(hl * size_t(nb) * sizeof(cx<R>));
+    ::lqcd::apply_dd<R>(c, in, out, t, nb, sin, sout, hl);
   }
   // the same from a 16-bit stored input to a 16-bit stored output (strides
   // in words)
@@ -644,6 +689,81 @@ void arnoldi_hs(lqcd_ctx *c, const Op<float> &A, void *W, size_t n, size_t ldv, 
     }
   }
   arnoldi_hs_impl<BK, false>(c, A, W, n, ldv, Wrs, j0, m, nb, s, eta2, wt, steps);
+}
+
+// The s-step form on a plain basis of precision R (FP64 or FP32; even/odd
+// operator): as sstep_block, the powers and the basis both held in R, every
+// sum in FP64.  S <= 4: the update holds S vectors' elements in FP64 registers.
+// The one-step form reads the basis twice per step (half of the time of an
+// FP64 solve) and takes ten launches per step beside the operator's two, this
+// one 14 per block.  Ten FP64 solves on 16^3 x 32: 55.9 -> 34.2 ms, 32 on
+// 12^4: 34.9 -> 22.1 ms; 16 with an FP32 basis inside the whole path on 8^4:
+// 15.7 -> 8.2 ms; same matrix-vector products.
+template <class R, int S>
+void sstep_block_plain(lqcd_ctx *c, const Op<R> &A, cx<R> *Wb, size_t n, size_t Wrs, int j, int m, int nb, Small &s,
+                       double eta2, cx<R> *wt) {
+  constexpr double kSigma = 1.0;
+  constexpr int NG = S * S;
+  const size_t ldc = size_t(S) * (m + 1);
+  const int J = j + 1, nblk = sstep_blocks<R>(n, nb);
+  LQCD_CHECK(J <= kSstepMaxJ, LQCD_EINVAL, "s-step Arnoldi: basis of %d vectors exceeds %d", J, kSstepMaxJ);
+  char *q = static_cast<char *>(c->sstep.ensure(2 * ldc * nb * sizeof(cdouble) + size_t(NG) * nb * sizeof(cdouble) +
+                                                size_t(NG) * nb * sizeof(double) +
+                                                2 * size_t(nb) * nblk * NG * sizeof(double)));
+  cdouble *C1 = reinterpret_cast<cdouble *>(q), *C2 = C1 + ldc * nb, *f = C2 + ldc * nb;
+  double *G = reinterpret_cast<double *>(f + size_t(NG) * nb), *part = G + size_t(NG) * nb;
+  double *gpart = part + size_t(nb) * nblk * NG;
+  double *dpart = static_cast<double *>(c->red.ensure(size_t(nb) * nblk * 2 * S * J * sizeof(double)));
+  const size_t wvs = size_t(nb) * n;  // vector k of the block, right-hand side r at wt + k wvs + r n
+  cx<R> *out = Wb + size_t(J) * n;
+  const cx<double> *C1d = reinterpret_cast<const cx<double> *>(C1), *C2d = reinterpret_cast<const cx<double> *>(C2);
+  cx<double> *Hd = reinterpret_cast<cx<double> *>(s.Hd), *fd = reinterpret_cast<cx<double> *>(f);
+  A.apply_dd_plain(Wb + size_t(j) * n, Wrs, wt, n, nb);
+  for (int k = 1; k < S; ++k) A.apply_dd_plain(wt + (k - 1) * wvs, n, wt + k * wvs, n, nb);
+  multi_dots_part<R, S>(c, Wb, n, Wrs, J, wt, wvs, n, n, nb, dpart, gpart, nullptr);
+  if (nblk <= kMidBlocks) {
+    hipLaunchKernelGGL(k_sstep_mid<S>, dim3(nb), dim3(kBlock), 0, c->stream, dpart, gpart, nblk,
+                       reinterpret_cast<cx<double> *>(C1), ldc, G, s.flag, s.reorth, eta2, Hd, s.Hrs, m + 1, j,
+                       kSigma, fd);
+  } else {
+    sum_dots(c, dpart, nblk, S * J, nb, C1, ldc, nullptr);
+    hipLaunchKernelGGL(k_sstep_plan<S>, dim3(nb), dim3(64), 0, c->stream, gpart, nblk, C1d, ldc, J, G, s.flag,
+                       s.reorth, eta2);
+    LQCD_HIP(hipGetLastError());
+    hipLaunchKernelGGL((k_sstep_finish<S, false>), dim3(nb), dim3(64), 0, c->stream, Hd, s.Hrs, m + 1, j, C1d, C2d,
+                       ldc, part, nblk, G, s.flag, kSigma, fd);
+  }
+  LQCD_HIP(hipGetLastError());
+  multi_axpys_store<R, S>(c, Wb, n, Wrs, J, C1, ldc, wt, wvs, n, n, nb, s.flag, f, out, n, Wrs);
+  // explicit path (flagged right-hand sides)
+  multi_axpys<R, S>(c, Wb, n, Wrs, J, C1, ldc, wt, wvs, n, n, nb, nullptr, s.flag);
+  multi_dots_part<R, S>(c, Wb, n, Wrs, J, wt, wvs, n, n, nb, dpart, nullptr, s.flag);
+  sum_dots(c, dpart, nblk, S * J, nb, C2, ldc, s.flag);
+  multi_axpys<R, S>(c, Wb, n, Wrs, J, C2, ldc, wt, wvs, n, n, nb, part, s.flag);
+  hipLaunchKernelGGL((k_sstep_finish<S, true>), dim3(nb), dim3(64), 0, c->stream, Hd, s.Hrs, m + 1, j, C1d, C2d, ldc,
+                     part, nblk, G, s.flag, kSigma, fd);
+  LQCD_HIP(hipGetLastError());
+  sstore<R, S>(c, wt, wvs, n, f, out, n, Wrs, n, nb, s.flag);
+}
+
+constexpr int kMaxPlainSteps = 4;
+
+template <class R>
+void arnoldi_s(lqcd_ctx *c, const Op<R> &A, void *W, size_t n, size_t Wrs, int m, int nb, Small &s, double eta2,
+               void *wt, int steps) {
+  cx<R> *Wb = static_cast<cx<R> *>(W), *w = static_cast<cx<R> *>(wt);
+  for (int j = 0; j < m;) {
+    const int b = std::min(steps, m - j);
+    if (b == 4)
+      sstep_block_plain<R, 4>(c, A, Wb, n, Wrs, j, m, nb, s, eta2, w);
+    else if (b == 3)
+      sstep_block_plain<R, 3>(c, A, Wb, n, Wrs, j, m, nb, s, eta2, w);
+    else if (b == 2)
+      sstep_block_plain<R, 2>(c, A, Wb, n, Wrs, j, m, nb, s, eta2, w);
+    else
+      arnoldi<R>(c, A, W, n, Wrs, j, m, nb, s, eta2);  // the one step left
+    j += b;
+  }
 }
 
 // MINRES-DR basis extension (one right-hand side, FP64; hermitian A):
@@ -959,7 +1079,8 @@ bool gmres_dr(lqcd_ctx *c, const Op<double> &A, const void *S, void *X, const lq
 // cycle_cap cycles of this call, or when a cycle leaves the residual above
 // `stall` times the previous one: it only has to shrink the residual.
 // BK >= 0 (R = float only): the GMRES(p) basis W is stored in 16 bits
-// (half.h kind BK) and wt is FP32 scratch of nb vectors.
+// (half.h kind BK).  wt is scratch of nb vectors of precision R per Arnoldi
+// step of a block (null, plain bases only: one step at a time).
 template <class R, int BK = -1>
 void proj_solve(lqcd_ctx *c, const Op<R> &A, const void *Vdef, const lqcd_defl *d, int p, void *S,
                 void *X, void *Rr, void *W, int nb, std::vector<double> ref, double tol,
@@ -1059,7 +1180,11 @@ void proj_solve(lqcd_ctx *c, const Op<R> &A, const void *Vdef, const lqcd_defl *
         arnoldi_h<BK>(c, A, W, n, ldh, Wrs, 0, p, na, s, eta2, wt);
     } else {
       axpby<R>(c, sc.data(), Rb, n, zs.data(), W, Wrs, n, na, true);
-      arnoldi<R>(c, A, W, n, Wrs, 0, p, na, s, c->cycle_reorth ? kReorthAlways : kReorthCycle);
+      const double eta2 = c->cycle_reorth ? kReorthAlways : kReorthCycle;
+      if (wt)
+        arnoldi_s<R>(c, A, W, n, Wrs, p, na, s, eta2, wt, std::min(c->arnoldi_steps, kMaxPlainSteps));
+      else
+        arnoldi<R>(c, A, W, n, Wrs, 0, p, na, s, eta2);
     }
     harvest_reorth(c, s, na, perm, reorth);
     Hh.resize(s.Hrs * na);
@@ -1269,6 +1394,9 @@ extern "C" lqcd_status gmresdr_solve(lqcd_ctx *c, lqcd_op op, const lqcd_solve_p
     LQCD_CHECK(p.proj_m >= 0 && p.proj_m <= 250, LQCD_EINVAL, "gmresdr_solve: proj_m outside 0..250");
     const int p_cyc = p.proj_m > 0 ? p.proj_m : p.m - p.k;
     const int blk = std::max(1, p.rhs_block);
+    // Arnoldi steps per basis pass on a plain basis: the power basis of Mhat is
+    // well conditioned about its centre 1; the indefinite M' keeps single steps
+    const int ps = op == LQCD_OP_SCHUR ? std::min(c->arnoldi_steps, kMaxPlainSteps) : 1;
     for (int r0 = start; r0 < nrhs; r0 += blk) {
       const int nb = std::min(blk, nrhs - r0);
       const cx<double> *bl = static_cast<const cx<double> *>(b) + size_t(r0) * fl;
@@ -1282,8 +1410,9 @@ extern "C" lqcd_status gmresdr_solve(lqcd_ctx *c, lqcd_op op, const lqcd_solve_p
       void *Rr = w.R.ensure(n * nb * sizeof(cx<double>));
       if (p.inner == LQCD_F64) {
         void *W = w.W.ensure(size_t(p_cyc + 1) * n * nb * sizeof(cx<double>));
+        void *WT = ps > 1 ? w.WT.ensure(n * nb * sizeof(cx<double>) * size_t(ps)) : nullptr;
         proj_solve<double>(c, A64, d->V.ptr, d, p_cyc, w.S.ptr, X, Rr, W, nb, ref, p.tol,
-                           p.max_cycles, mv, cy, res, ro);
+                           p.max_cycles, mv, cy, res, ro, 0, 0.0, WT);
       } else {
         // FP64 refinement around FP32 deflated inner solves
         {
@@ -1301,9 +1430,10 @@ extern "C" lqcd_status gmresdr_solve(lqcd_ctx *c, lqcd_op op, const lqcd_solve_p
         const bool h16 = p.inner == LQCD_F16 || p.inner == LQCD_BF16;
         void *W32 = h16 ? w.W32.ensure(size_t(p_cyc + 1) * hvec_words(n / 12) * nb * sizeof(uint32_t))
                         : w.W32.ensure(size_t(p_cyc + 1) * n * nb * sizeof(cx<float>));
-        // FP32 work vectors of the 16-bit Arnoldi steps (two per right-hand
-        // side in the two-step form)
-        void *WT = h16 ? w.WT.ensure(n * nb * sizeof(cx<float>) * size_t(c->arnoldi_steps)) : nullptr;
+        // FP32 work vectors of the Arnoldi steps (one per step of a block and
+        // right-hand side)
+        const size_t nw = h16 ? size_t(c->arnoldi_steps) : ps > 1 ? size_t(ps) : 0;
+        void *WT = nw ? w.WT.ensure(n * nb * sizeof(cx<float>) * nw) : nullptr;
         void *T = w.T.ensure(n * nb * sizeof(cx<double>));
         fill_zero(c, X, n * nb * sizeof(cx<double>));
         copy_dev(c, Rr, w.S.ptr, n * nb * sizeof(cx<double>));
@@ -1344,7 +1474,7 @@ extern "C" lqcd_status gmresdr_solve(lqcd_ctx *c, lqcd_op op, const lqcd_solve_p
                                  p.max_cycles, mv, cy, ires, ro, kInnerCycleCap, kInnerStall, WT);
           else
             proj_solve<float>(c, A32, d->V32.ptr, d, p_cyc, S32, X32, R32, W32, nb, iref, itol,
-                              p.max_cycles, mv, cy, ires, ro, kInnerCycleCap, kInnerStall);
+                              p.max_cycles, mv, cy, ires, ro, kInnerCycleCap, kInnerStall, WT);
           hipLaunchKernelGGL(k_acc_widen, dim3(std::min<size_t>(nblocks(n * nb), 8192)), dim3(kBlock),
                              0, c->stream, static_cast<const cx<float> *>(X32), static_cast<cx<double> *>(X),
                              n * nb);

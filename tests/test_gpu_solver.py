@@ -335,3 +335,55 @@ def test_recombination_forms_agree(method, op):
     assert rel_err(out[1][0], out[0][0]) < 1e-11
     assert np.abs(out[1][1] - out[0][1]).max() < 1e-9 * np.abs(out[0][1]).max()
     assert abs(out[1][2] - out[0][2]) <= 8
+
+
+@pytest.mark.parametrize("m", [19, 20, 21])
+@pytest.mark.parametrize("forced", [0, 1])
+@pytest.mark.parametrize("inner", ["f64", "f32"])
+def test_sstep_arnoldi_plain_basis(inner, forced, m):
+    """Several Arnoldi steps per pass over an FP64 or FP32 basis span the same
+    Krylov space as single ones: solutions reach LU and the true residual in
+    about as many matrix-vector products, with the second pass forced on every
+    block and with last blocks of 1 to 3 steps (p = 9, 10, 11)."""
+    require_gpu()
+    dims, kappa = (6, 4, 2, 8), 0.13
+    ctx, U = context(dims, 0.3, 1001, kappa)
+    eta = z4_noise(2003, dims, 0, 4)
+    xref, _ = _dense_solve(U, kappa, dims, eta)
+    st = {}
+    for steps in (1, 2, 3, 4, 6):  # 6: blocks of 4, the longest on these bases
+        ctx.tune(arnoldi_steps=steps, cycle_reorth=forced)
+        say("solve s-step", inner, forced, m, steps)
+        x, _, s = ctx.gmresdr_solve(to_gpu(eta), op="schur", m=m, k=10, tol=1e-12, tol_super=1e-13, inner=inner,
+                                    inner_tol=1e-4, rhs_block=3)
+        x = to_host(x)
+        for r in range(4):
+            assert rel_err(x[r], xref[r]) < (1e-10 if inner == "f64" else 1e-9), (steps, r)
+            assert s[r]["true_resid"] < 1e-11, (steps, r)
+        st[steps] = s
+    for steps in (2, 3, 4, 6):
+        for r in range(1, 4):
+            assert st[steps][r]["matvecs"] <= st[1][r]["matvecs"] + (m - 10 + 1), (steps, r)
+            assert (st[steps][r]["reorth"] > 0) == bool(forced), (steps, r)
+
+
+@pytest.mark.parametrize("inner", ["f64", "f32"])
+def test_sstep_arnoldi_plain_basis_two_units_per_lane(inner):
+    """A field large enough for two 16-byte units per lane and the separate
+    sums, plan and finish launches: same solution as single steps."""
+    require_gpu()
+    dims, kappa, nrhs = (16, 12, 12, 24), 0.124, 6
+    ctx, _ = context(dims, 0.25, 1004, kappa)
+    eta = to_gpu(z4_noise(2004, dims, 0, nrhs))
+    kw = dict(op="schur", m=30, k=10, tol=1e-12, inner=inner, inner_tol=1e-4, rhs_block=nrhs)
+    _, defl, _ = ctx.gmresdr_solve(eta[0:1], op="schur", m=30, k=10, tol=1e-10)
+    xs = {}
+    for steps in (1, 4):
+        ctx.tune(arnoldi_steps=steps)
+        say("solve s-step", inner, dims, steps)
+        xs[steps], _, st = ctx.gmresdr_solve(eta, defl=defl, **kw)
+        for s in st:
+            assert s["true_resid"] <= 1.05e-12, s
+    a, b = to_host(xs[1]), to_host(xs[4])
+    # both within 1e-12 / lambda_min(M) of the solution, lambda_min > 0.05 here
+    assert np.linalg.norm(a - b) < 4e-11 * np.linalg.norm(a)
