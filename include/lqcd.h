@@ -491,6 +491,10 @@ lqcd_status lqcd_timer_read(lqcd_ctx *ctx, int kclass, double *ms, double *bytes
  * basis keeps them in FP32).  LQCD_TUNE_RECOMBINE_REGS: 1 (default) runs
  * the restart recombination V_{k+1} = V_{m+1} P with its outputs in
  * registers (up to 48 of them, P in LDS); 0 uses the LDS-tiled form.
+ * LQCD_TUNE_HOP_LEGS: the leg-split stencil (the eight neighbour terms of a
+ * site on eight waves): -1 (default) unless one of the LQCD_TUNE_HOP_ launch
+ * shapes above was set on the context (they belong to the lane-grouped and the
+ * link-tiled forms), 0 never, 1 always.
  * Values are per context; EINVAL for other values. */
 typedef enum {
   LQCD_TUNE_HOP_NB64 = 0,
@@ -509,7 +513,8 @@ typedef enum {
   LQCD_TUNE_KEPT_PERIOD = 13,
   LQCD_TUNE_ARNOLDI_STEPS = 14,
   LQCD_TUNE_SSTEP_Z16 = 15,
-  LQCD_TUNE_RECOMBINE_REGS = 16
+  LQCD_TUNE_RECOMBINE_REGS = 16,
+  LQCD_TUNE_HOP_LEGS = 17
 } lqcd_tune_param;
 lqcd_status lqcd_tune_set(lqcd_ctx *ctx, lqcd_tune_param param, int value);
 

@@ -144,6 +144,8 @@ struct lqcd_ctx {
   int hop_tsites[2] = {32, 32};  // tiled stencil: sites per tile, FP64 (16, 32), FP32 (16, 32, 64)
   int hop_rgroup = 0;            // tiled stencil: right-hand sides per group (0: all in one)
   int hop_rnest = -1;            // tiled stencil: groups swept in turn within each block (0: off, -1: auto)
+  int hop_legs = -1;             // leg-split stencil: 0 never, 1 always, -1 unless hop_shaped
+  bool hop_shaped = false;       // a launch shape of the other stencil forms was set
   int gemm_mfma = 1;             // V C with one shared basis on the matrix cores (0: FMA kernel)
   int cycle_reorth = 0;          // 1: second Gram-Schmidt pass on every GMRES-Proj step
   int kept_period = 16;          // MINRES-DR: steps between tests against the kept vectors
@@ -245,6 +247,9 @@ template <class R>
 void pack_eo(lqcd_ctx *c, const void *lex, void *eo, int nrhs, size_t eo_stride);
 template <class R>
 void unpack_eo(lqcd_ctx *c, const void *eo, void *lex, int nrhs, size_t eo_stride);
+// unpack_eo of even halves (eo_stride apart); the odd sites of lex are zero.
+template <class R>
+void unpack_even(lqcd_ctx *c, const void *eo, void *lex, int nrhs, size_t eo_stride);
 // Links from host memory (lexicographic complex128 [V][4][3][3]) into U64 and
 // U32 (allocated here); returns when links_host has been read.
 void pack_links(lqcd_ctx *c, const double *links_host);

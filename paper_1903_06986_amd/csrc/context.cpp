@@ -147,6 +147,7 @@ extern "C" lqcd_status lqcd_timer_read(lqcd_ctx *c, int k, double *ms, double *b
 extern "C" lqcd_status lqcd_tune_set(lqcd_ctx *c, lqcd_tune_param param, int value) {
   return guarded([&] {
     LQCD_CHECK(c, LQCD_EINVAL, "lqcd_tune_set: null context");
+    const bool shape = param <= LQCD_TUNE_HOP_TSITES64 || param == LQCD_TUNE_HOP_RNEST;
     switch (param) {
       case LQCD_TUNE_HOP_NB64:
       case LQCD_TUNE_HOP_NB32:
@@ -191,6 +192,10 @@ extern "C" lqcd_status lqcd_tune_set(lqcd_ctx *c, lqcd_tune_param param, int val
         LQCD_CHECK(value >= 1 && value <= 6, LQCD_EINVAL, "lqcd_tune_set: Arnoldi steps per basis pass in 1..6");
         c->arnoldi_steps = value;
         break;
+      case LQCD_TUNE_HOP_LEGS:
+        LQCD_CHECK(value >= -1 && value <= 1, LQCD_EINVAL, "lqcd_tune_set: leg-split stencil switch must be -1, 0 or 1");
+        c->hop_legs = value;
+        break;
       case LQCD_TUNE_RECOMBINE_REGS:
         LQCD_CHECK(value == 0 || value == 1, LQCD_EINVAL, "lqcd_tune_set: recombination form must be 0 or 1");
         c->recombine_regs = value;
@@ -214,6 +219,7 @@ extern "C" lqcd_status lqcd_tune_set(lqcd_ctx *c, lqcd_tune_param param, int val
       default:
         LQCD_CHECK(false, LQCD_EINVAL, "lqcd_tune_set: unknown parameter %d", int(param));
     }
+    if (shape) c->hop_shaped = true;
   });
 }
 

@@ -53,7 +53,8 @@ __global__ void k_pack(Geom g, const cx<double> *__restrict__ lex, cx<R> *__rest
   }
 }
 
-template <class R>
+// EVEN: the odd sites of lex are set to zero (eo holds even halves only).
+template <class R, bool EVEN>
 __global__ void k_unpack(Geom g, const cx<R> *__restrict__ eo, cx<double> *__restrict__ lex,
                          size_t eo_stride) {
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
@@ -67,7 +68,8 @@ __global__ void k_unpack(Geom g, const cx<R> *__restrict__ eo, cx<double> *__res
   cx<double> *dst = lex + (rhs * g.V + s) * 12;
 #pragma unroll
   for (int c = 0; c < 12; ++c) {
-    cx<R> v = ldc(src + c * Vh);
+    cx<R> v = mk<R>(0, 0);
+    if (!EVEN || p == 0) v = ldc(src + c * Vh);
     stc(dst + c, mk<double>(double(v.re), double(v.im)));
   }
 }
@@ -158,7 +160,15 @@ void pack_eo(lqcd_ctx *c, const void *lex, void *eo, int nrhs, size_t eo_stride)
 template <class R>
 void unpack_eo(lqcd_ctx *c, const void *eo, void *lex, int nrhs, size_t eo_stride) {
   if (nrhs <= 0) return;
-  hipLaunchKernelGGL(k_unpack<R>, dim3(nblocks(c->g.V), nrhs), dim3(kBlock), 0, c->stream, c->g,
+  hipLaunchKernelGGL((k_unpack<R, false>), dim3(nblocks(c->g.V), nrhs), dim3(kBlock), 0, c->stream, c->g,
+                     static_cast<const cx<R> *>(eo), static_cast<cx<double> *>(lex), eo_stride);
+  LQCD_HIP(hipGetLastError());
+}
+
+template <class R>
+void unpack_even(lqcd_ctx *c, const void *eo, void *lex, int nrhs, size_t eo_stride) {
+  if (nrhs <= 0) return;
+  hipLaunchKernelGGL((k_unpack<R, true>), dim3(nblocks(c->g.V), nrhs), dim3(kBlock), 0, c->stream, c->g,
                      static_cast<const cx<R> *>(eo), static_cast<cx<double> *>(lex), eo_stride);
   LQCD_HIP(hipGetLastError());
 }
@@ -186,6 +196,8 @@ template void pack_eo<double>(lqcd_ctx *, const void *, void *, int, size_t);
 template void pack_eo<float>(lqcd_ctx *, const void *, void *, int, size_t);
 template void unpack_eo<double>(lqcd_ctx *, const void *, void *, int, size_t);
 template void unpack_eo<float>(lqcd_ctx *, const void *, void *, int, size_t);
+template void unpack_even<double>(lqcd_ctx *, const void *, void *, int, size_t);
+template void unpack_even<float>(lqcd_ctx *, const void *, void *, int, size_t);
 template void convert<double, float>(lqcd_ctx *, const void *, void *, size_t);
 template void convert<float, double>(lqcd_ctx *, const void *, void *, size_t);
 template void convert<double, double>(lqcd_ctx *, const void *, void *, size_t);

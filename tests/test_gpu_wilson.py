@@ -161,3 +161,36 @@ def test_link_tiled_stencil(dims, prec, nrhs):
             assert rel_err(y, _oracle_op(op, U, kappa, x, dims)) < tol, (op, tb, ts, rg, rn)
     ctx.tune(hop_tile64=1, hop_tile32=1, hop_tblock64=-1, hop_tblock32=-1, hop_tsites32=32, hop_rgroup=0,
              hop_tsites64=32, hop_rnest=-1)
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (6, 4, 2, 8), (10, 6, 4, 2), (8, 8, 4, 6), (8, 6, 6, 20),
+                                  (12, 12, 10, 12)])
+@pytest.mark.parametrize("nrhs", [1, 3, 4, 17])
+def test_leg_split_stencil_equals_the_other_forms(dims, nrhs):
+    """The leg-split form (eight waves per 64 sites; 1 to 135 tiles here, the
+    last one ragged on three of the lattices, a partial last block of timeslices
+    on the fifth, several right-hand sides per workgroup on the last) adds the
+    same terms in the same order as the lane-grouped form (up to 3
+    right-hand sides) and the tiled form (from 4 on): FP32 and 16-bit results
+    agree bit for bit, FP64 ones to the rounding of two sums (the lane-grouped
+    form has other FMAs).  Both layouts, all operators."""
+    require_gpu()
+    import torch
+    ctx, _ = context(dims, 0.3, 41, 0.13)
+    rng = np.random.default_rng(3)
+    x = to_gpu(rng.normal(size=(nrhs,) + ctx.shape) + 1j * rng.normal(size=(nrhs,) + ctx.shape))
+    for prec in ("f64", "f32", "f16", "bf16"):
+        ops = ("schur",) if prec in ("f16", "bf16") else ("M", "Mdag", "MG5", "hop", "schur")
+        for op in ops:
+            for layout in ("lex", "eo") if prec in ("f64", "f32") and op != "schur" else ("lex",):
+                say("leg-split", dims, nrhs, prec, op, layout)
+                f = x if layout == "lex" else ctx.pack_eo(x, prec=prec)
+                y = {}
+                for legs in (0, 1, -1):
+                    ctx.tune(hop_legs=legs)
+                    y[legs] = to_host(ctx.wilson_apply(op, f, prec=prec, layout=layout))
+                assert np.array_equal(y[1], y[-1])  # lattices of this size take it by themselves
+                if prec == "f64":
+                    assert rel_err(y[1], y[0]) < 1e-14, (op, layout)
+                else:
+                    assert np.array_equal(y[1], y[0]), (prec, op, layout)
