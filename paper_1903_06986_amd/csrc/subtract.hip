@@ -777,6 +777,15 @@ void es_pairs(lqcd_ctx *c, lqcd_defl *d, int Q) {
   std::vector<cdouble> lh;
   la::Mat Sr;
   LQCD_CHECK(la::eig(T, lh, Sr), LQCD_ENOCONV, "eigenvalue subtraction: Ritz eigenproblem did not converge");
+  // Mhat's eigenvalues come in conjugate pairs (g5-hermiticity): a converged
+  // pair's two values, equal to rounding, are made exactly conjugate, so that
+  // the order of the eigenvalues does not hang on their last digits
+  for (int i = 0; i < k; ++i)
+    for (int j = i + 1; j < k; ++j)
+      if (std::abs(lh[i] - std::conj(lh[j])) <= 1e-13 * std::abs(lh[i])) {
+        lh[i] = 0.5 * (lh[i] + std::conj(lh[j]));
+        lh[j] = std::conj(lh[i]);
+      }
   std::vector<cdouble> lam(k);
   for (int i = 0; i < k; ++i) lam[i] = 1.0 - std::sqrt(1.0 - lh[i]);
   std::vector<int> ord(k);
