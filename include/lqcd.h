@@ -251,6 +251,14 @@ lqcd_status deflate_project_multi(lqcd_ctx *ctx, lqcd_defl *defl, int Q, int nva
                                   int ntheta, const void *eta, void *const *xt_list, int nrhs,
                                   double *const *corr_list);
 
+/* deflate_project_multi with xt_list[v] written instead of added to where
+ * fresh[v] is nonzero (host int [nvar], or NULL for none): the same result as
+ * on a zero field, which need not be filled first. */
+lqcd_status deflate_project_multi_set(lqcd_ctx *ctx, lqcd_defl *defl, int Q, int nvar, const int *modes,
+                                      const double *const *coeffs_list, const int *ncoeffs,
+                                      const int *thetas_host, int ntheta, const void *eta, void *const *xt_list,
+                                      const int *fresh, int nrhs, double *const *corr_list);
+
 /* Perturbative subtraction (Sec. 5.1, Eqs. (28)-(35)): xt[n] =
  * sum_{j=0}^{order} (kappa P)^j eta[n] (device LEX), and the exact trace
  * correction Tr_t(Theta sum_j (kappa P)^j) per timeslice (host complex128

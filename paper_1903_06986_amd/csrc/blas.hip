@@ -1433,18 +1433,13 @@ __global__ void k_inv_sqrt(const double *__restrict__ nrm2, double *__restrict__
 
 
 // ---------------------------------------------------- V^H X on MFMA
-// C = V^H X for J <= 64 basis vectors and nb <= 8 columns, as one real
-// GEMM on the matrix cores: with K running over (element, re/im),
-//   A[j][2e + q] = (Re, Im) V_j[e],
-//   B[2e + q][c]      = (Re, Im) X_c[e]        -> Re C[j][c],
-//   B[2e + q][nb + c] = (Im, -Re) X_c[e]       -> Im C[j][c].
-// A workgroup (4 waves, wave w owns rows 16w .. 16w + 15) walks a K range
-// in chunks of 64 elements staged in LDS (rows padded by 2 words against
-// bank conflicts), accumulates one 16 x 16 tile per wave with
-// v_mfma_*_16x16x4 (16 x 4 times 4 x 16 per instruction: lane l supplies
-// A[l % 16][l / 16] and B[l / 16][l % 16] and holds four rows of column
-// l % 16, Mfma::row), and writes its partial tile; a second kernel adds the
-// workgroups' partials in a fixed order.  V and X are each read once.
+// Both products run on the matrix cores with operands loaded from memory into
+// the registers that the instruction reads, without LDS: v_mfma_*_16x16x4
+// takes A[l % 16][l / 16] and B[l / 16][l % 16] from lane l and leaves four
+// rows of column l % 16 (Mfma::row) there.  The contraction index may run over
+// the elements in any order that A and B share, so a lane always loads units
+// of 16 bytes (one FP64 or two FP32 complex numbers), and the real and
+// imaginary parts of a product take four instructions on the same registers.
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef double d4v __attribute__((ext_vector_type(4)));
 
@@ -1469,220 +1464,236 @@ struct Mfma<double> {
   __device__ static int row(int q, int v) { return q + 4 * v; }
 };
 
-constexpr int kTE = 64;           // elements per LDS chunk
-constexpr int kTP = 2 * kTE + 2;  // reals per staged row (padded)
-
+// A 16-byte unit in R.
 template <class R>
+struct RUnit {
+  static constexpr int EV = Unit<R>::EV;
+  typename Unit<R>::raw q;
+  __device__ R re(int e) const { return q[2 * e]; }
+  __device__ R im(int e) const { return q[2 * e + 1]; }
+  __device__ void zero() { q = typename Unit<R>::raw(R(0)); }
+  __device__ void load(const cx<R> *p) { q = *reinterpret_cast<const typename Unit<R>::raw *>(p); }
+  __device__ void load_nt(const cx<R> *p) {
+    q = __builtin_nontemporal_load(reinterpret_cast<const typename Unit<R>::raw *>(p));
+  }
+  __device__ void store(cx<R> *p) const { *reinterpret_cast<typename Unit<R>::raw *>(p) = q; }
+};
+
+// C = V^H X for J <= 16 RT basis vectors and nb <= 16 columns.  Lane (row or
+// column l % 16, k = l / 16) loads unit k of a group of four: four lanes take
+// 64 contiguous bytes of each of 16 vectors, kTnGroups groups go out together
+// (256 bytes a vector), and those of the next step are in flight while one is
+// multiplied.  Every wave sums its own steps (grid stride); a workgroup's four
+// waves add in LDS, in FP64, and a second kernel adds the workgroups.  V and X
+// are read once: 30 modes of 16^3 x 32 against 16 right-hand sides 2 x 306 (V
+// through LDS, 8 columns a launch) -> 350 us, 3.3 TB/s.  (V through plain loads:
+// streaming ones fetch the 128-byte lines once per 64-byte half, 404 us.)
+constexpr int kTnGroups = 4;
+template <class R, int RT>
 __global__ void __launch_bounds__(kBlock)
-    k_gemm_tn_mfma(const cx<R> *__restrict__ V, size_t ldv, int J, const cx<R> *__restrict__ X,
-                   size_t ldx, int nb, size_t n, size_t chunks_per_block, R *__restrict__ part) {
-  __shared__ R sV[64 * kTP];
-  __shared__ R sX[8 * kTP];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    k_gemm_tn_mfma(const cx<R> *__restrict__ V, size_t ldv, int J, const cx<R> *__restrict__ X, size_t ldx, int nb,
+                   size_t n, double *__restrict__ part) {
+  constexpr int EV = RUnit<R>::EV, STEP = 4 * EV * kTnGroups;  // elements per step
   using A = Mfma<R>;
-  typename A::acc_t acc = {0, 0, 0, 0};
-  const size_t c0 = size_t(blockIdx.x) * chunks_per_block;
-  const size_t nchunk = (n + kTE - 1) / kTE;
-  const size_t c1 = c0 + chunks_per_block < nchunk ? c0 + chunks_per_block : nchunk;
-  const int row = 16 * wave + (lane & 15);   // A row (basis vector) of this lane
-  const int kq = lane >> 4;                   // 0..3: element 2 * step + kq / 2, part kq % 2
-  const int col = lane & 15;                  // B column
-  // The next chunk's operands are loaded into registers while the current
-  // one is multiplied from LDS (J + nb <= 72 rows of kTE elements: at most
-  // kLpt loads per thread).
-  constexpr int kLpt = (72 * kTE + kBlock - 1) / kBlock;
-  const int nld = (J + nb) * kTE;
-  cx<R> pre[kLpt];
-  auto fetch = [&](size_t e0) {
+  __shared__ double sh[kWaves][RT * 16 * 16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l16 = lane & 15, k = lane >> 4;
+  typename A::acc_t ar[RT], ai[RT];
 #pragma unroll
-    for (int u = 0; u < kLpt; ++u) {
-      const int t = threadIdx.x + u * kBlock;
-      const int r = t / kTE, e = t % kTE;
-      const size_t idx = e0 + e;
-      pre[u] = mk<R>(0, 0);
-      if (t < nld && idx < n) pre[u] = r < J ? ldc(V + size_t(r) * ldv + idx) : ldc(X + size_t(r - J) * ldx + idx);
+  for (int t = 0; t < RT; ++t) ar[t] = ai[t] = typename A::acc_t{0, 0, 0, 0};
+  const size_t nstep = (n + STEP - 1) / STEP, stride = size_t(gridDim.x) * kWaves;
+  RUnit<R> v[RT][kTnGroups], x[kTnGroups];
+  auto fetch = [&](size_t st) {
+#pragma unroll
+    for (int g = 0; g < kTnGroups; ++g) {
+      const size_t e = st * STEP + size_t(4 * g + k) * EV;
+      const bool in = e < n;  // n is a multiple of EV
+#pragma unroll
+      for (int t = 0; t < RT; ++t) {
+        v[t][g].zero();
+        if (in && 16 * t + l16 < J) v[t][g].load(V + size_t(16 * t + l16) * ldv + e);
+      }
+      x[g].zero();
+      if (in && l16 < nb) x[g].load(X + size_t(l16) * ldx + e);
     }
   };
-  if (c0 < c1) fetch(c0 * kTE);
-  for (size_t ch = c0; ch < c1; ++ch) {
-    __syncthreads();  // the previous chunk's operands are consumed
-    // stage V rows 0..J-1 and X columns 0..nb-1 (zero beyond n)
+  size_t st = size_t(blockIdx.x) * kWaves + wave;
+  if (st < nstep) fetch(st);
+  for (; st < nstep; st += stride) {
+    RUnit<R> cv[RT][kTnGroups], cxx[kTnGroups];
 #pragma unroll
-    for (int u = 0; u < kLpt; ++u) {
-      const int t = threadIdx.x + u * kBlock;
-      if (t < nld) {
-        const int r = t / kTE, e = t % kTE;
-        R *dst = r < J ? sV + r * kTP : sX + (r - J) * kTP;
-        dst[2 * e] = pre[u].re;
-        dst[2 * e + 1] = pre[u].im;
-      }
+    for (int g = 0; g < kTnGroups; ++g) {
+#pragma unroll
+      for (int t = 0; t < RT; ++t) cv[t][g] = v[t][g];
+      cxx[g] = x[g];
     }
-    __syncthreads();
-    if (ch + 1 < c1) fetch((ch + 1) * kTE);
-    if (16 * wave < J) {
-#pragma unroll 8
-      for (int st = 0; st < kTE / 2; ++st) {
-        const int e = 2 * st + (kq >> 1), q = kq & 1;
-        const R a = row < J ? sV[row * kTP + 2 * e + q] : R(0);
-        R b = 0;
-        if (col < nb) {
-          b = sX[col * kTP + 2 * e + q];
-        } else if (col - nb < nb) {
-          const R xr = sX[(col - nb) * kTP + 2 * e], xi = sX[(col - nb) * kTP + 2 * e + 1];
-          b = q == 0 ? xi : -xr;
+    if (st + stride < nstep) fetch(st + stride);
+#pragma unroll
+    for (int g = 0; g < kTnGroups; ++g)
+#pragma unroll
+      for (int e = 0; e < EV; ++e)
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+          const R vr = cv[t][g].re(e), vi = cv[t][g].im(e), xr = cxx[g].re(e), xi = cxx[g].im(e);
+          ar[t] = A::op(vr, xr, ar[t]);
+          ai[t] = A::op(vr, xi, ai[t]);
+          ar[t] = A::op(vi, xi, ar[t]);
+          ai[t] = A::op(-vi, xr, ai[t]);
         }
-        acc = A::op(a, b, acc);
-      }
-    }
   }
-  // partial tile: part[block][row][col], rows 4 (lane / 16) + v of the wave's tile
-  if (16 * wave < J) {
-    R *po = part + size_t(blockIdx.x) * 64 * 16;
+  // part[block][(re, im)][row][column]
+  for (int c = 0; c < 2; ++c) {
+    if (c) __syncthreads();
 #pragma unroll
-    for (int v = 0; v < 4; ++v) po[(16 * wave + A::row(kq, v)) * 16 + col] = acc[v];
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        sh[wave][(16 * t + A::row(k, u)) * 16 + l16] = double(c ? ai[t][u] : ar[t][u]);
+    __syncthreads();
+    for (int i = threadIdx.x; i < RT * 256; i += kBlock) {
+      double s = 0;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) s += sh[w][i];
+      part[(size_t(blockIdx.x) * 2 + c) * (RT * 256) + i] = s;
+    }
   }
 }
 
-// C[j + ldc * c] = sum over blocks of the partial tiles (complex).
-template <class R>
+// C[j + ldc * c] = sum over blocks of the partial tiles (tile = 256 RT reals).
 __global__ void __launch_bounds__(kBlock)
-    k_gemm_tn_final(const R *__restrict__ part, int nblk, int J, int nb, cx<double> *__restrict__ C,
+    k_gemm_tn_final(const double *__restrict__ part, int nblk, int tile, int J, cx<double> *__restrict__ C,
                     size_t ldc) {
-  // one workgroup per output (j, column): the lanes stride over the ~1024
-  // partial tiles and the block sums them (a single lane per output would
-  // walk them as one chain of dependent loads)
+  // one workgroup per output (j, column): the lanes stride over the partial
+  // tiles and the block sums them (a single lane per output would walk them as
+  // one chain of dependent loads)
   __shared__ double sh[2][kWaves];
   const int t = blockIdx.x;
   const int j = t % J, c = t / J;
   double v[2] = {0, 0};
   for (int b = threadIdx.x; b < nblk; b += kBlock) {
-    v[0] += double(part[(size_t(b) * 64 + j) * 16 + c]);
-    v[1] += double(part[(size_t(b) * 64 + j) * 16 + nb + c]);
+    v[0] += part[size_t(b) * 2 * tile + j * 16 + c];
+    v[1] += part[(size_t(b) * 2 + 1) * tile + j * 16 + c];
   }
   block_sum<2>(v, sh);
   if (threadIdx.x == 0) C[j + ldc * size_t(c)] = mk(v[0], v[1]);
 }
 
 // ---------------------------------------------------- V C on MFMA
-// Y_b += alpha sum_j V_j C[j][b] for J <= 64 vectors and up to 16 columns
-// (one V shared by all columns), as one real GEMM on the matrix cores per
-// group of 8 columns: D[(b, s)][e] = sum_{(j, p)} A[(b, s)][(j, p)] B[(j, p)][e]
-// with B[(j, p)][e] = (Re, Im) V_j[e] and the coefficients in A:
-//   s = 0 (Re Y):  A[(b, 0)][(j, 0)] =  Re c,  A[(b, 0)][(j, 1)] = -Im c,
-//   s = 1 (Im Y):  A[(b, 1)][(j, 0)] =  Im c,  A[(b, 1)][(j, 1)] =  Re c,
-// c = alpha C[j][b].  A workgroup stages 64 elements of all J vectors in LDS
-// (the next chunk's loads in flight in registers, as in k_gemm_tn_mfma);
-// wave w multiplies its 16 elements (the D columns) by the G groups' A
-// operands, which stay in LDS for the whole launch.  The D rows are ordered
-// so that each lane's four accumulator registers hold the real and
-// imaginary parts of two outputs of one element (Mfma::row): the update of
-// Y is then a complex load and store per output, 16 consecutive elements
-// per 16 lanes.  V is read once for up to 16 columns.
-template <class R>
-struct OutRow;
-template <>
-struct OutRow<float> {  // rows 4q + v: (b, s) = (r / 2, r % 2)
-  __device__ static int b(int r) { return r >> 1; }
-  __device__ static int s(int r) { return r & 1; }
-};
-template <>
-struct OutRow<double> {  // rows q + 4v: (b, s) = (r % 8, r / 8)
-  __device__ static int b(int r) { return r & 7; }
-  __device__ static int s(int r) { return r >> 3; }
+// Y_b += alpha sum_j V_j C[j][b] for J <= 64 vectors and G groups of up to 16
+// columns that share one V, each with its own Y and coefficients (optionally
+// times weights w[j]).  A holds the coefficients (row = column of Y, k =
+// vector 4 s + k of step s; in LDS for the launch, 16 bytes a lane and step), B
+// the vectors: lane (element l % 16, k) loads 16 bytes of vector 4 s + k, 256
+// contiguous bytes per vector.  D's four rows per lane are four columns of the
+// lane's element, read and written in 256-byte runs.  A wave takes 16 units of
+// elements at a time (grid stride) with the next ones' V in flight.  V is
+// read once for all G groups.
+constexpr int kNNGroups = 4, kNNSteps = 16;  // J <= 4 * kNNSteps
+struct NNSet {
+  const cx<double> *C[kNNGroups], *w[kNNGroups];
+  size_t ldc[kNNGroups];
+  void *Y[kNNGroups];
+  size_t ldy[kNNGroups];
+  int nb[kNNGroups];
+  int fresh[kNNGroups];  // Y is written, not added to
 };
 
-constexpr int kNNSteps = 32;  // K steps of 4 (two vectors each): J <= 64
-
-template <class R, int G>
+template <class R, int S>
 __global__ void __launch_bounds__(kBlock)
-    k_gemm_nn_mfma(const cx<R> *__restrict__ V, size_t ldv, int J, const cx<double> *__restrict__ C,
-                   size_t ldcc, cx<R> *__restrict__ Y, size_t ldy, int nb, size_t n, double alpha) {
-  // dynamic LDS: the staged vectors [J][kTP] reals, then the A operands
-  // [G][nst][64] (sized by the launch: 64 KiB for FP64, J = 41, G = 2)
-  extern __shared__ unsigned char smem[];
+    k_gemm_nn_mfma(const cx<R> *__restrict__ V, size_t ldv, int J, NNSet set, int G, size_t n, double alpha) {
+  constexpr int EV = RUnit<R>::EV;
   using A = Mfma<R>;
+  extern __shared__ unsigned char smem[];
+  cx<R> *sA = reinterpret_cast<cx<R> *>(smem);  // [G][S][64]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int nst = (J + 1) / 2;
-  R *sV = reinterpret_cast<R *>(smem);
-  R *sA = sV + size_t(J) * kTP;
-  // the A operands: lane l supplies A[l % 16][l / 16] of step st
-  for (int t = threadIdx.x; t < G * nst * 64; t += kBlock) {
-    const int l = t & 63, st = (t >> 6) % nst, g = t / (64 * nst);
-    const int r = l & 15, k = l >> 4;
-    const int j = 2 * st + (k >> 1), p = k & 1;
-    const int b = 8 * g + OutRow<R>::b(r), sr = OutRow<R>::s(r);
-    R v = 0;
-    if (j < J && b < nb) {
-      const cx<double> cc = C[j + ldcc * size_t(b)];
-      const double cr = alpha * cc.re, ci = alpha * cc.im;
-      v = R(sr == 0 ? (p == 0 ? cr : -ci) : (p == 0 ? ci : cr));
+  const int l16 = lane & 15, k = lane >> 4;
+  for (int t = threadIdx.x; t < G * S * 64; t += kBlock) {
+    const int l = t & 63, s = (t >> 6) % S, g = t / (64 * S);
+    const int b = l & 15, j = 4 * s + (l >> 4);
+    cx<double> c = mk(0.0, 0.0);
+    if (j < J && b < set.nb[g]) {
+      c = set.C[g][j + set.ldc[g] * size_t(b)];
+      if (set.w[g]) c = c * set.w[g][j];
+      c = alpha * c;
     }
-    sA[(g * nst + st) * 64 + l] = v;
+    sA[t] = mk<R>(R(c.re), R(c.im));
   }
-  const size_t nchunk = (n + kTE - 1) / kTE;
-  constexpr int kLpt = (64 * kTE + kBlock - 1) / kBlock;
-  const int nld = J * kTE;
-  cx<R> pre[kLpt];
-  auto fetch = [&](size_t e0) {
+  __syncthreads();
+  const size_t ntile = (n / EV + 15) / 16, stride = size_t(gridDim.x) * kWaves;
+  for (size_t tile = size_t(blockIdx.x) * kWaves + wave; tile < ntile; tile += stride) {
+    const size_t e0 = (tile * 16 + l16) * EV;
+    const bool in = e0 < n;
+    RUnit<R> v[S];
 #pragma unroll
-    for (int u = 0; u < kLpt; ++u) {
-      const int t = threadIdx.x + u * kBlock;
-      const size_t idx = e0 + (t % kTE);
-      pre[u] = (t < nld && idx < n) ? ldc(V + size_t(t / kTE) * ldv + idx) : mk<R>(0, 0);
+    for (int s = 0; s < S; ++s) {
+      v[s].zero();
+      if (in && 4 * s + k < J) v[s].load_nt(V + size_t(4 * s + k) * ldv + e0);
     }
-  };
-  size_t ch = blockIdx.x;
-  if (ch < nchunk) fetch(ch * kTE);
-  const int e = 16 * wave + (lane & 15);  // this lane's element (D column) in the chunk
-  const int kq = lane >> 4;
-  for (; ch < nchunk; ch += gridDim.x) {
-    __syncthreads();  // the previous chunk's operands are consumed (and sA is written)
+#pragma unroll 1
+    for (int g = 0; g < G; ++g) {
+      cx<R> *Yg = static_cast<cx<R> *>(set.Y[g]) + e0;
+      const int nbg = set.nb[g];
+      RUnit<R> y[4];
 #pragma unroll
-    for (int u = 0; u < kLpt; ++u) {
-      const int t = threadIdx.x + u * kBlock;
-      if (t < nld) {
-        R *dst = sV + (t / kTE) * kTP + 2 * (t % kTE);
-        dst[0] = pre[u].re;
-        dst[1] = pre[u].im;
+      for (int u = 0; u < 4; ++u) {
+        const int b = A::row(k, u);
+        y[u].zero();
+        if (in && b < nbg && !set.fresh[g]) y[u].load(Yg + size_t(b) * set.ldy[g]);
       }
-    }
-    __syncthreads();
-    if (ch + gridDim.x < nchunk) fetch((ch + gridDim.x) * kTE);
-    typename A::acc_t acc[G];
+      typename A::acc_t ar[EV], ai[EV];
 #pragma unroll
-    for (int g = 0; g < G; ++g) acc[g] = typename A::acc_t{0, 0, 0, 0};
-    for (int st = 0; st < nst; ++st) {
-      const int j = 2 * st + (kq >> 1);
-      const R bv = j < J ? sV[j * kTP + 2 * e + (kq & 1)] : R(0);
+      for (int e = 0; e < EV; ++e) ar[e] = ai[e] = typename A::acc_t{0, 0, 0, 0};
 #pragma unroll
-      for (int g = 0; g < G; ++g) acc[g] = A::op(sA[(g * nst + st) * 64 + lane], bv, acc[g]);
-    }
-    const size_t idx = ch * kTE + e;
-    if (idx < n) {
+      for (int s = 0; s < S; ++s) {
+        const cx<R> c = ldc(sA + (g * S + s) * 64 + lane);
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        // registers v = 0..3 hold rows row(kq, v): two outputs (b, Re / Im)
-        int bo[2] = {-1, -1};
-        R re[2] = {0, 0}, im[2] = {0, 0};
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int r = A::row(kq, v), b = OutRow<R>::b(r), sr = OutRow<R>::s(r);
-          const int slot = (bo[0] < 0 || bo[0] == b) ? 0 : 1;
-          bo[slot] = b;
-          (sr == 0 ? re[slot] : im[slot]) = acc[g][v];
+        for (int e = 0; e < EV; ++e) {
+          const R vr = v[s].re(e), vi = v[s].im(e);
+          ar[e] = A::op(c.re, vr, ar[e]);
+          ai[e] = A::op(c.re, vi, ai[e]);
+          ar[e] = A::op(-c.im, vi, ar[e]);
+          ai[e] = A::op(c.im, vr, ai[e]);
         }
+      }
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const int b = 8 * g + bo[q];
-          if (bo[q] >= 0 && b < nb) {
-            cx<R> *yp = Y + size_t(b) * ldy + idx;
-            const cx<R> y = ldc(yp);
-            stc(yp, mk<R>(y.re + re[q], y.im + im[q]));
-          }
+      for (int u = 0; u < 4; ++u) {
+        const int b = A::row(k, u);
+#pragma unroll
+        for (int e = 0; e < EV; ++e) {
+          y[u].q[2 * e] += ar[e][u];
+          y[u].q[2 * e + 1] += ai[e][u];
         }
+        if (in && b < nbg) y[u].store(Yg + size_t(b) * set.ldy[g]);
       }
     }
   }
+}
+
+// G groups in one launch; bytes: V once, every Y twice (written ones once).
+template <class R>
+void gemm_nn_set(lqcd_ctx *c, const void *V, size_t ldv, int J, const NNSet &set, int G, size_t n, double alpha) {
+  int moved = 0;
+  for (int g = 0; g < G; ++g) moved += (set.fresh[g] ? 1 : 2) * set.nb[g];
+  Timed tm(c, LQCD_KC_GEMM, double(J + moved) * n * sizeof(cx<R>));
+  const size_t ntile = (n / RUnit<R>::EV + 15) / 16;
+  const dim3 grid(unsigned(std::min<size_t>((ntile + kWaves - 1) / kWaves, 2048)));
+  const cx<R> *v = static_cast<const cx<R> *>(V);
+#define LQCD_NN(S)                                                                                              \
+  LQCD_TLAUNCH(tm, true, true, (k_gemm_nn_mfma<R, S>), grid, dim3(kBlock), size_t(G) * S * 64 * sizeof(cx<R>), \
+               c->stream, v, ldv, J, set, G, n, alpha)
+  if (J <= 16) LQCD_NN(4);
+  else if (J <= 32) LQCD_NN(8);
+  else if (J <= 48) LQCD_NN(12);
+  else LQCD_NN(16);
+#undef LQCD_NN
+  LQCD_HIP(hipGetLastError());
+}
+
+// out[j + J b] = C[j + ldc b] w[j]
+__global__ void k_weigh_rows(const cx<double> *__restrict__ C, size_t ldc, const cx<double> *__restrict__ w, int J,
+                             int nb, cx<double> *__restrict__ out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < J * nb) out[i] = C[i % J + ldc * size_t(i / J)] * w[i % J];
 }
 
 inline unsigned grid_elems(size_t n) { return unsigned(std::min<size_t>(nblocks(n), 8192)); }
@@ -1782,30 +1793,20 @@ void gemm_nn(lqcd_ctx *c, const void *V, size_t ldv, size_t V_rs, int J, const c
              size_t ldc, size_t C_rs, void *Y, size_t ldy, size_t Y_rs, int nb, size_t n, int nrhs,
              double alpha) {
   if (nb <= 0 || nrhs <= 0) return;
-  if (nrhs == 1 && nb >= 2 && J >= 1 && J <= 2 * kNNSteps && n >= size_t(kTE) && c->gemm_mfma) {
-    // one basis for all columns: the matrix cores, 16 columns per launch
-    // (two groups of 8), V read once per launch
-    const size_t nchunk = (n + kTE - 1) / kTE;
-    const unsigned grid = unsigned(std::min<size_t>(nchunk, 2048));
-    for (int b0 = 0; b0 < nb; b0 += 16) {
-      const int w = std::min(16, nb - b0);
-      const int G = w > 8 ? 2 : 1;
-      const size_t shm = (size_t(J) * kTP + size_t(G) * ((J + 1) / 2) * 64) * sizeof(R);
-      Timed tm(c, LQCD_KC_GEMM, double(J + 2 * w) * n * sizeof(cx<R>));
-      const cx<double> *Cb = reinterpret_cast<const cx<double> *>(C) + ldc * size_t(b0);
-      cx<R> *Yb = static_cast<cx<R> *>(Y) + ldy * size_t(b0);
-      if (shm > 64 * 1024) {  // more than the default dynamic LDS limit (J > 44 in FP64)
-        const void *f = G == 2 ? reinterpret_cast<const void *>(&k_gemm_nn_mfma<R, 2>)
-                               : reinterpret_cast<const void *>(&k_gemm_nn_mfma<R, 1>);
-        LQCD_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(shm)));
+  if (nrhs == 1 && nb >= 2 && J >= 1 && J <= 4 * kNNSteps && n >= 64 && n % RUnit<R>::EV == 0 &&
+      ldv % RUnit<R>::EV == 0 && ldy % RUnit<R>::EV == 0 && c->gemm_mfma) {
+    // one basis for all columns: the matrix cores, V read once per 64 columns
+    for (int b0 = 0; b0 < nb; b0 += 16 * kNNGroups) {
+      NNSet set{};
+      int G = 0;
+      for (int b = b0; b < std::min(nb, b0 + 16 * kNNGroups); b += 16, ++G) {
+        set.C[G] = reinterpret_cast<const cx<double> *>(C) + ldc * size_t(b);
+        set.ldc[G] = ldc;
+        set.Y[G] = static_cast<cx<R> *>(Y) + ldy * size_t(b);
+        set.ldy[G] = ldy;
+        set.nb[G] = std::min(16, nb - b);
       }
-      if (G == 2)
-        LQCD_TLAUNCH(tm, true, true, (k_gemm_nn_mfma<R, 2>), dim3(grid), dim3(kBlock), shm, c->stream,
-                     static_cast<const cx<R> *>(V), ldv, J, Cb, ldc, Yb, ldy, w, n, alpha);
-      else
-        LQCD_TLAUNCH(tm, true, true, (k_gemm_nn_mfma<R, 1>), dim3(grid), dim3(kBlock), shm, c->stream,
-                     static_cast<const cx<R> *>(V), ldv, J, Cb, ldc, Yb, ldy, w, n, alpha);
-      LQCD_HIP(hipGetLastError());
+      gemm_nn_set<R>(c, V, ldv, J, set, G, n, alpha);
     }
     return;
   }
@@ -1821,34 +1822,77 @@ template <class R>
 void gemm_tn(lqcd_ctx *c, const void *V, size_t ldv, int J, const void *X, size_t ldx, int nb,
              size_t n, cdouble *C, size_t ldc) {
   if (J <= 0 || nb <= 0) return;
-  if (J <= 64 && nb > 8 && n >= size_t(kTE)) {
-    // more columns than one matrix-core tile holds: tiles of 8 columns, so V
-    // is read once per 8 right-hand sides
-    for (int b0 = 0; b0 < nb; b0 += 8)
-      gemm_tn<R>(c, V, ldv, J, static_cast<const cx<R> *>(X) + size_t(b0) * ldx, ldx, std::min(8, nb - b0), n,
-                 C + size_t(b0) * ldc, ldc);
-    return;
-  }
-  if (J > 64 || nb > 8 || n < size_t(kTE)) {
+  constexpr int EV = RUnit<R>::EV;
+  if (J > 64 || n < 64 || n % EV != 0 || ldv % EV != 0 || ldx % EV != 0) {
     // outside the matrix-core tile: one multi-dot per column of X
     multi_dot_impl<R>(c, V, ldv, 0, J, X, ldx, n, nb, C, ldc, LQCD_KC_GEMM,
                       double(J + nb) * n * sizeof(cx<R>));
     return;
   }
-  // split K so that about 1024 workgroups share the reduction
-  const size_t nchunk = (n + kTE - 1) / kTE;
-  const size_t cpb = std::max<size_t>(1, (nchunk + 1023) / 1024);
-  const int nblk = int((nchunk + cpb - 1) / cpb);
-  R *part = static_cast<R *>(c->red.ensure(size_t(nblk) * 64 * 16 * sizeof(R)));
-  {
-    Timed tm(c, LQCD_KC_GEMM, double(J + nb) * n * sizeof(cx<R>));
-    LQCD_TLAUNCH(tm, true, true, (k_gemm_tn_mfma<R>), dim3(nblk), dim3(kBlock), 0, c->stream,
-                 static_cast<const cx<R> *>(V), ldv, J, static_cast<const cx<R> *>(X), ldx, nb, n, cpb, part);
+  // 16 columns per launch, the contraction split over up to 512 workgroups
+  const int RT = (J + 15) / 16;
+  const size_t nstep = (n + 4 * EV * kTnGroups - 1) / (4 * EV * kTnGroups);
+  const int nblk = int(std::min<size_t>((nstep + kWaves - 1) / kWaves, 512));
+  double *part = static_cast<double *>(c->red.ensure(size_t(nblk) * 2 * RT * 256 * sizeof(double)));
+  const cx<R> *Vp = static_cast<const cx<R> *>(V);
+  for (int b0 = 0; b0 < nb; b0 += 16) {
+    const int w = std::min(16, nb - b0);
+    const cx<R> *Xb = static_cast<const cx<R> *>(X) + size_t(b0) * ldx;
+    {
+      Timed tm(c, LQCD_KC_GEMM, double(J + w) * n * sizeof(cx<R>));
+      switch (RT) {
+        case 1:
+          LQCD_TLAUNCH(tm, true, true, (k_gemm_tn_mfma<R, 1>), dim3(nblk), dim3(kBlock), 0, c->stream, Vp, ldv, J, Xb,
+                       ldx, w, n, part);
+          break;
+        case 2:
+          LQCD_TLAUNCH(tm, true, true, (k_gemm_tn_mfma<R, 2>), dim3(nblk), dim3(kBlock), 0, c->stream, Vp, ldv, J, Xb,
+                       ldx, w, n, part);
+          break;
+        case 3:
+          LQCD_TLAUNCH(tm, true, true, (k_gemm_tn_mfma<R, 3>), dim3(nblk), dim3(kBlock), 0, c->stream, Vp, ldv, J, Xb,
+                       ldx, w, n, part);
+          break;
+        default:
+          LQCD_TLAUNCH(tm, true, true, (k_gemm_tn_mfma<R, 4>), dim3(nblk), dim3(kBlock), 0, c->stream, Vp, ldv, J, Xb,
+                       ldx, w, n, part);
+      }
+    }
+    LQCD_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_gemm_tn_final, dim3(unsigned(J * w)), dim3(kBlock), 0, c->stream, part, nblk, RT * 256, J,
+                       reinterpret_cast<cx<double> *>(C) + ldc * size_t(b0), ldc);
+    LQCD_HIP(hipGetLastError());
   }
-  LQCD_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_gemm_tn_final<R>, dim3(unsigned(J * nb)), dim3(kBlock), 0, c->stream, part, nblk, J, nb,
-                     reinterpret_cast<cx<double> *>(C), ldc);
-  LQCD_HIP(hipGetLastError());
+}
+
+void gemm_nn_multi(lqcd_ctx *c, const void *V, size_t ldv, int J, const cdouble *C, size_t ldc, int nvar,
+                   const cdouble *w, size_t ldw, void *const *Y, size_t ldy, const int *fresh, int nb, size_t n) {
+  LQCD_CHECK(nvar >= 1 && nvar <= kNNGroups && nb >= 1 && nb <= 16, LQCD_EINVAL, "gemm_nn_multi: %d x %d columns",
+             nvar, nb);
+  const cx<double> *Cp = reinterpret_cast<const cx<double> *>(C), *wp = reinterpret_cast<const cx<double> *>(w);
+  if (J > 4 * kNNSteps || n < 64 || !c->gemm_mfma) {  // outside the matrix-core form
+    cdouble *Cw = static_cast<cdouble *>(c->red.ensure(size_t(J) * nb * sizeof(cdouble)));
+    for (int v = 0; v < nvar; ++v) {
+      hipLaunchKernelGGL(k_weigh_rows, dim3(nblocks(size_t(J) * nb)), dim3(kBlock), 0, c->stream, Cp, ldc,
+                         wp + v * ldw, J, nb, reinterpret_cast<cx<double> *>(Cw));
+      LQCD_HIP(hipGetLastError());
+      if (fresh && fresh[v])
+        for (int b = 0; b < nb; ++b) fill_zero(c, static_cast<cx<double> *>(Y[v]) + b * ldy, n * sizeof(cx<double>));
+      gemm_nn<double>(c, V, ldv, 0, J, Cw, J, 0, Y[v], ldy, 0, nb, n, 1, 1.0);
+    }
+    return;
+  }
+  NNSet set{};
+  for (int v = 0; v < nvar; ++v) {
+    set.C[v] = Cp;
+    set.w[v] = wp + v * ldw;
+    set.ldc[v] = ldc;
+    set.Y[v] = Y[v];
+    set.ldy[v] = ldy;
+    set.nb[v] = nb;
+    set.fresh[v] = fresh ? fresh[v] : 0;
+  }
+  gemm_nn_set<double>(c, V, ldv, J, set, nvar, n, 1.0);
 }
 
 template <class R>

@@ -64,6 +64,12 @@ template <class R>
 void gemm_tn(lqcd_ctx *c, const void *V, size_t ldv, int J, const void *X, size_t ldx, int nb,
              size_t n, cdouble *C, size_t ldc);
 
+// Y_v[b] += sum_j V[j] w[v ldw + j] C[j + ldc b], v < nvar <= 4, b < nb <= 16
+// (FP64; V read once for all; device coefficients and weights; where fresh[v] is
+// set, Y_v is written instead of added to).
+void gemm_nn_multi(lqcd_ctx *c, const void *V, size_t ldv, int J, const cdouble *C, size_t ldc, int nvar,
+                   const cdouble *w, size_t ldw, void *const *Y, size_t ldy, const int *fresh, int nb, size_t n);
+
 // In place: V[j] <- sum_l V[l] P[l + ldp * j], j < Jout, over Jin input
 // vectors (Jout <= Jin); P device complex.
 template <class R>

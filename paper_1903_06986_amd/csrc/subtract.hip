@@ -459,12 +459,6 @@ __global__ void k_g5_eo(cx<double> *__restrict__ f, size_t Vh, size_t stride, in
   *p = -*p;
 }
 
-// C[r][q] *= w[q] for nb columns of Q rows (w on the device).
-__global__ void k_scale_rows(cx<double> *__restrict__ C, const cx<double> *__restrict__ w, int Q, int nb) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < Q * nb) C[i] = C[i] * w[i % Q];
-}
-
 void h2d(lqcd_ctx *c, void *dst, const void *src, size_t bytes) {
   LQCD_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->stream));
   LQCD_HIP(hipStreamSynchronize(c->stream));
@@ -989,9 +983,10 @@ std::vector<cdouble> hf_weights(lqcd_ctx *c, lqcd_defl *d, int Q, lqcd_defl_mode
   return w;
 }
 
-// xt[v] += g5 E (w[v] .* (E^H eta)) for nvar weight sets, with E^H eta formed
-// once per block of right-hand sides.
-void hf_update(lqcd_ctx *c, lqcd_defl *d, int Q, const void *eta, int nvar, void *const *xt,
+// xt[v] += g5 E (w[v] .* (E^H eta)) for nvar weight sets (xt[v] = ... where
+// fresh[v] is set; fresh may be null), with E^H eta formed once per block of
+// right-hand sides.
+void hf_update(lqcd_ctx *c, lqcd_defl *d, int Q, const void *eta, int nvar, void *const *xt, const int *fresh,
                const std::vector<cdouble> *w, int nrhs) {
   const size_t fl = full_len(c->g);
   const cx<double> *E = d->E.as<cx<double>>();
@@ -1021,18 +1016,11 @@ void hf_update(lqcd_ctx *c, lqcd_defl *d, int Q, const void *eta, int nvar, void
   const int blk = kSubBlock;
   for (int r0 = 0; r0 < nrhs; r0 += blk) {
     const int nb = std::min(blk, nrhs - r0);
-    // [E^H eta | w[0] .* E^H eta | w[1] .* ...]: the overlaps, then one scaled copy per weight set
-    cdouble *Cd = static_cast<cdouble *>(c->ws[5].ensure(size_t(Q) * nb * (nvar + 1) * sizeof(cdouble)));
+    cdouble *Cd = static_cast<cdouble *>(c->ws[5].ensure(size_t(Q) * nb * sizeof(cdouble)));
     gemm_tn<double>(c, El, fl, Q, static_cast<const cdouble *>(eta) + r0 * fl, fl, nb, fl, Cd, Q);
-    for (int v = 0; v < nvar; ++v) {
-      cdouble *Cv = Cd + size_t(Q) * nb * (v + 1);
-      LQCD_HIP(hipMemcpyAsync(Cv, Cd, size_t(Q) * nb * sizeof(cdouble), hipMemcpyDeviceToDevice, c->stream));
-      hipLaunchKernelGGL(k_scale_rows, dim3(nblocks(size_t(Q) * nb)), dim3(kBlock), 0, c->stream,
-                         reinterpret_cast<cx<double> *>(Cv), reinterpret_cast<const cx<double> *>(wd) + size_t(v) * Q,
-                         Q, nb);
-      LQCD_HIP(hipGetLastError());
-      gemm_nn<double>(c, Gl, fl, 0, Q, Cv, Q, 0, static_cast<cdouble *>(xt[v]) + r0 * fl, fl, 0, nb, fl, 1, 1.0);
-    }
+    void *y[kMaxHfVariants];
+    for (int v = 0; v < nvar; ++v) y[v] = static_cast<cdouble *>(xt[v]) + r0 * fl;
+    gemm_nn_multi(c, Gl, fl, Q, Cd, Q, nvar, wd, Q, y, fl, fresh, nb, fl);
   }
 }
 
@@ -1174,6 +1162,14 @@ extern "C" lqcd_status deflate_project_multi(lqcd_ctx *c, lqcd_defl *d, int Q, i
                                              const double *const *coeffs_list, const int *ncoeffs,
                                              const int *thetas, int nth, const void *eta, void *const *xt_list,
                                              int nrhs, double *const *corr_list) {
+  return deflate_project_multi_set(c, d, Q, nvar, modes, coeffs_list, ncoeffs, thetas, nth, eta, xt_list, nullptr,
+                                   nrhs, corr_list);
+}
+
+extern "C" lqcd_status deflate_project_multi_set(lqcd_ctx *c, lqcd_defl *d, int Q, int nvar, const int *modes,
+                                                 const double *const *coeffs_list, const int *ncoeffs,
+                                                 const int *thetas, int nth, const void *eta, void *const *xt_list,
+                                                 const int *fresh, int nrhs, double *const *corr_list) {
   return guarded([&] {
     LQCD_CHECK(c && d && modes, LQCD_EINVAL, "deflate_project_multi: null argument");
     LQCD_CHECK(nvar >= 1 && nvar <= kMaxHfVariants, LQCD_EINVAL, "deflate_project_multi: %d variants (1..%d)",
@@ -1199,7 +1195,7 @@ extern "C" lqcd_status deflate_project_multi(lqcd_ctx *c, lqcd_defl *d, int Q, i
       w[v] = hf_weights(c, d, Q, lqcd_defl_mode(modes[v]), poly ? coeffs_list[v] : nullptr, poly ? ncoeffs[v] : 0,
                         thetas, nth, corr_list ? corr_list[v] : nullptr, nullptr);
     }
-    hf_update(c, d, Q, eta, nvar, xt_list, w.data(), nrhs);
+    hf_update(c, d, Q, eta, nvar, xt_list, fresh, w.data(), nrhs);
   });
 }
 
@@ -1230,6 +1226,6 @@ extern "C" lqcd_status deflate_project(lqcd_ctx *c, lqcd_defl *d, int Q, lqcd_de
     defl_eigpairs(c, d, Q);
     const std::vector<cdouble> w =
         hf_weights(c, d, Q, mode, coeffs_host, ncoeff, thetas, nth, corr, xi_inv_host);
-    hf_update(c, d, Q, eta, 1, &xt, &w, nrhs);
+    hf_update(c, d, Q, eta, 1, &xt, nullptr, &w, nrhs);
   });
 }

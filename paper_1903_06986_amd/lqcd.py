@@ -68,6 +68,7 @@ _SIGS = {
     "lqcd_defl_ritz": [_P, _P, ctypes.POINTER(ctypes.c_int)],
     "deflate_project": [_P, _P, _I, _I, _P, _I, _P, _I, _P, _P, _I, _P, _P],
     "deflate_project_multi": [_P, _P, _I, _I, _P, _P, _P, _P, _I, _P, _P, _I, _P],
+    "deflate_project_multi_set": [_P, _P, _I, _I, _P, _P, _P, _P, _I, _P, _P, _P, _I, _P],
     "pert_subtract": [_P, _I, _P, _I, _P, _P, _I, _P],
     "poly_subtract": [_P, _I, _P, _P, _P, _P, _I, _P, _P, _I, _P],
     "poly_subtract_multi": [_P, _I, _I, _P, _P, _P, _I],
@@ -381,7 +382,7 @@ class Context:
         modes = np.array([m for m, _, _, _ in variants], dtype=np.int32)
         cps, ncs = [], []
         for mode, coeffs, xt, corr in variants:
-            xts.append(torch.zeros_like(eta) if xt is None else xt)
+            xts.append(torch.empty_like(eta) if xt is None else xt)
             cr = np.zeros((nth, self.dims[3]), dtype=np.complex128) if corr is None else \
                 np.ascontiguousarray(corr, dtype=np.complex128).copy()
             corrs.append(cr)
@@ -394,11 +395,13 @@ class Context:
                 cps.append(cf.ctypes.data_as(_P))
                 ncs.append(len(cf))
         nc = np.array(ncs, dtype=np.int32)
-        _check(lib().deflate_project_multi(self.handle, defl.handle, Q, nv, modes.ctypes.data_as(_P),
-                                           (_P * nv)(*cps), nc.ctypes.data_as(_P), thp, nth,
-                                           _field(eta, n, 12 * self.V, "eta"),
-                                           (_P * nv)(*[_field(x, n, 12 * self.V, "xt") for x in xts]), n,
-                                           (_P * nv)(*[c.ctypes.data_as(_P) for c in corrs])))
+        fresh = np.array([xt is None for _, _, xt, _ in variants], dtype=np.int32)
+        _check(lib().deflate_project_multi_set(self.handle, defl.handle, Q, nv, modes.ctypes.data_as(_P),
+                                               (_P * nv)(*cps), nc.ctypes.data_as(_P), thp, nth,
+                                               _field(eta, n, 12 * self.V, "eta"),
+                                               (_P * nv)(*[_field(x, n, 12 * self.V, "xt") for x in xts]),
+                                               fresh.ctypes.data_as(_P), n,
+                                               (_P * nv)(*[c.ctypes.data_as(_P) for c in corrs])))
         del keep
         return list(zip(xts, corrs))
 

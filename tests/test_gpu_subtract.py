@@ -190,6 +190,44 @@ def test_deflate_project_multi_equals_single_calls():
         ctx.deflate_project_multi(hdefl, Q, eta, [(lqcd.DEFL_HFES, None, None, None)] * 5, THETAS)
 
 
+@pytest.mark.parametrize("Q", [1, 15, 16, 17, 33])
+def test_projection_on_the_matrix_cores_equals_the_other_form(Q):
+    """V^H X and V C of the projection on the matrix cores (rows and columns
+    in tiles of 16) against the FMA form, for one mode up to three tiles of
+    them and 1, 15 and 18 right-hand sides, in one variant and in three, on
+    given fields and on fresh ones (written, not added to).  Sums of 1536
+    terms in another order: 1e-12 of the largest element."""
+    require_gpu()
+    import torch
+    from paper_1903_06986_amd import lqcd
+    dims, kappa = (4, 4, 2, 4), 0.125
+    ctx, U = context(dims, 0.3, 31, kappa)
+    eta = to_gpu(z4_noise(5, dims, 0, 18))
+    say("projection tiles", Q)
+    _, hdefl, _ = ctx.gmresdr_solve(eta[0:1], op="MG5", m=90, k=50, tol=1e-12, tol_super=1e-13,
+                                    eig_tol=1e-8, n_eig=35, max_cycles=300)
+    rng = np.random.default_rng(4)
+    cp = S.pert_coeffs(6)
+    base = torch.from_numpy(rng.standard_normal((18,) + ctx.shape) + 0j).cuda()
+    for n in (1, 15, 18):
+        out = {}
+        for mfma in (1, 0):
+            ctx.tune(gemm_mfma=mfma)
+            try:
+                out[mfma] = ctx.deflate_project_multi(
+                    hdefl, Q, eta[:n].contiguous(),
+                    [(lqcd.DEFL_HFES, None, None, None), (lqcd.DEFL_EIGPOLY, cp, base[:n].clone(), None),
+                     (lqcd.DEFL_EIGPOLY, cp, None, None)], THETAS)
+            finally:
+                ctx.tune(gemm_mfma=1)
+        for v in range(3):
+            a, b = to_host(out[1][v][0]), to_host(out[0][v][0])
+            assert np.abs(a - b).max() <= 1e-12 * np.abs(b).max(), (n, v)
+            np.testing.assert_array_equal(out[1][v][1], out[0][v][1])
+        one = ctx.deflate_project(hdefl, Q, eta[:n].contiguous(), thetas=THETAS)
+        np.testing.assert_array_equal(to_host(one[0]), to_host(out[1][0][0]))
+
+
 @pytest.mark.parametrize("dims", [(10, 14, 14, 16), (10, 2, 4, 6)])
 def test_trace_corrections_double_with_a_periodic_copy(dims):
     """Links repeated once along x: no loop of length <= 8 winds round an
