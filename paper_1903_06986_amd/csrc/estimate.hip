@@ -27,8 +27,7 @@ __device__ inline double wave_sum(double v) {
 // together: variant v forms x - xt_v (xt_v null: x itself) with the same
 // operations, in the same order, as a pass with that variant alone, so its
 // sums equal that pass's bit for bit.  Both kernels read eta and x once for
-// a group of variants (the point-split kernel also its neighbours' eta and
-// the links).
+// a group of variants.
 constexpr int kMaxVar = 6;
 // Partial-sum slots per (variant, right-hand side, timeslice, chunk): the
 // nine operator codes, with code 8 (point-split in t) in two slots, 8 and
@@ -103,48 +102,51 @@ __global__ void __launch_bounds__(kBlock)
   }
 }
 
-// Point-split operators (codes 5..8): t_n[mu][t] = sum_{x in t} eta_n(x)^+
-// (Theta(mu) (x_n - xt_n))(x), Theta(mu) = kappa [(1 + g_mu) U_mu(x - mu)^+
-// S_- - (1 - g_mu) U_mu(x) S_+] with S_-+ the shifts to x -+ mu.
+// All nine operators at once, where a point-split one (codes 5..8) is asked
+// for: t_n[mu][t] = sum_{x in t} eta_n(x)^+ (Theta(mu) (x_n - xt_n))(x),
+// Theta(mu) = kappa [(1 + g_mu) U_mu(x - mu)^+ S_- - (1 - g_mu) U_mu(x) S_+]
+// with S_-+ the shifts to x -+ mu.
 //
-// (1 -+ g_mu) has rank 2 and squares to twice itself, and its lower half
+// Every term is linear in d = x - xt at one site y, so at each y operator o is
+// a 12-vector g_o(y) of eta and the links that is the same for all variants,
+//   t[o][v] = sum_y g_o(y)^+ d_v(y):
+// a matrix product of ten rows (the five local operators, x, y, z, and t in
+// two rows: its forward terms belong to the timeslice below y's, its backward
+// terms to the one above) with two columns per variant (real and imaginary
+// part) over the 12 V components, summed on the matrix cores
+// (v_mfma_f64_16x16x4, 4 components an instruction).  A column's sum depends
+// on that column only, so a variant gives the same bits alone and in a group.
+//
+// g: (1 -+ g_mu) has rank 2 and squares to twice itself, and its lower half
 // spinor is a unitary R times the upper one, so for any colour matrix W
-//   a^+ (1 -+ g_mu) W b = sum_{s=0,1} at_s^+ W h_s = sum_s (W^+ at_s)^+ h_s,
+//   a^+ (1 -+ g_mu) W b = sum_{s=0,1} (W^+ at_s)^+ h_s,
 // where at and h are the upper halves of (1 -+ g_mu) a and (1 -+ g_mu) b:
 // at_s = a_s + alpha_s a_{p(s)} with a spin partner p(s) in {2, 3} and a
-// phase alpha_s in {+-1, +-i}.
+// phase alpha_s in {+-1, +-i}.  The forward term of row x = y - mu is -kappa
+// (U_mu(y - mu)^+ at)^+ h with at from eta(y - mu), the backward term of row x
+// = y + mu is kappa (U_mu(y) at)^+ h with at from eta(y + mu), both with h
+// from d(y).
 //
-// The sums are taken over the site y that d = x - xt is read at: the
-// forward term of row x = y - mu is -kappa (U_mu(y - mu)^+ at)^+ h with at
-// from eta(y - mu), the backward term of row x = y + mu is kappa (U_mu(y)
-// at)^+ h with at from eta(y + mu), both with h from d(y).  So eta is read at
-// the neighbours and d only at y: the colour vectors c = W^+ at of a site
-// (one per direction and half spin) do not depend on d, and every variant
-// adds a dot product of three per direction and half spin.  A term belongs
-// to the timeslice of its row site, which for mu = t is the one below (the
-// forward terms) or above (the backward terms) y's.
+// A workgroup takes 64 consecutive sites of one timeslice at a time.  Wave mu
+// makes the rows of direction mu for them (lane = site), staging eta at the
+// backward and then the forward neighbours through LDS (coalesced 16-byte
+// loads; the rows take the same place afterwards, so no other wave waits for
+// it), while eta at the sites, of which the local rows are permutations with
+// phases, is staged by all.  Then each wave sums the products of 16 of the
+// sites: the rows come from LDS, d straight from memory into registers (lane =
+// half a complex number: 64 contiguous bytes of each variant an instruction).
 //
-// A workgroup takes 64 consecutive sites of one timeslice at a time.  The
-// fields are site-major (192 bytes per site), so it stages them in LDS with
-// coalesced 16-byte loads (consecutive lanes read consecutive pieces of
-// consecutive sites): for each direction eta at the sites' forward and
-// backward neighbours (whose site runs are contiguous but for the wrap of
-// the periodic boundary), then for each variant d at the sites.  LDS holds
-// them component-major, [12][64 sites] with a row stride of 65, so that a
-// wave reading one component of 64 sites, and a wave writing 12 components
-// of consecutive sites, touch distinct banks in every group of 8 lanes.
-// Wave q of the workgroup takes one of the four half spins for all 64 sites
-// (lane = site): q < 2 the forward one s = q, q >= 2 the backward one s = q
-// - 2; the branch is uniform per wave and the link loads are coalesced.
-constexpr int kPsSites = 64;                // sites per chunk
-constexpr int kPsRow = kPsSites + 1;        // LDS stride of one component
-constexpr int kPsArr = 12 * kPsRow;         // one staged field
-
-// Link U_mu at the site of full lexicographic index s and parity par, in
-// the even/odd layout [parity][mu][9][Vh].
-__device__ inline const cx<double> *ps_link_at(const cx<double> *U, size_t Vh, size_t s, int par, int mu) {
-  return U + ((size_t(par) * 4 + mu) * 9) * Vh + (s >> 1);
-}
+// Bound by HBM (eta, x and each xt once): 24^3 x 32, 16 right-hand sides, six
+// variants 7.9 ms (a local kernel for three variants a launch, and one that
+// staged x - xt of every variant in LDS) -> 3.7 ms, 2.9 TB/s.
+// Two workgroups a CU (LDS, registers) hide the latency of the two phases of
+// each other only in part.
+constexpr int kPsSites = 64;             // sites per chunk
+constexpr int kPsStride = 13;            // LDS stride of a site: distinct banks across sites
+constexpr int kPsRegion = kPsSites * kPsStride + 4;  // one staged field; consecutive ones 16 banks apart
+constexpr int kPsRows = kNumTheta + kNumPS + 1;      // rows of the product
+static_assert(kPsRows == kOpSlots && 2 * kMaxVar <= 16, "rows are slots, columns fit a tile");
+static_assert(kNumPS == kWaves, "one direction per wave");
 
 // Half spin HS of direction MU, forward (FWD: projector 1 - g_mu) or
 // backward (1 + g_mu).
@@ -159,201 +161,259 @@ struct PsHalf {
   __device__ static cx<double> proj(cx<double> p, cx<double> q) {
     return AR != 0.0 ? mk(p.re + AR * q.re, p.im + AR * q.im) : mk(p.re - AI * q.im, p.im + AI * q.re);
   }
-  // c = W^+ at for the staged eta column ea (components kPsRow apart) and
-  // the link u (entries Vh apart): W = U_mu(y - mu) (FWD), U_mu(y)^+ (else)
-  __device__ static void eta_side(const cx<double> *u, size_t Vh, const cx<double> *ea, cx<double> c[3]) {
-    cx<double> at[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) at[k] = proj(ea[(HS * 3 + k) * kPsRow], ea[(PS * 3 + k) * kPsRow]);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) c[k] = mk(0.0, 0.0);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      cx<double> e[3];  // row a of U (one row in flight: fewer registers live)
-#pragma unroll
-      for (int b = 0; b < 3; ++b) e[b] = ldc(u + (3 * a + b) * Vh);
-#pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        if (FWD) c[b] = c[b] + cmulc(e[b], at[a]);  // (U^+ at)_b = sum_a conj(U_ab) at_a
-        else c[a] = c[a] + e[b] * at[b];            // (U at)_a = sum_b U_ab at_b
-      }
-      asm volatile("" : "+v"(c[0].re), "+v"(c[0].im), "+v"(c[1].re), "+v"(c[1].im), "+v"(c[2].re),
-                   "+v"(c[2].im)::"memory");
-    }
+  // conj(alpha) q
+  __device__ static cx<double> phase(cx<double> q) {
+    return AR != 0.0 ? mk(AR * q.re, AR * q.im) : mk(AI * q.im, -AI * q.re);
   }
-  // c^+ h for the staged d column db
-  __device__ static cx<double> term(const cx<double> c[3], const cx<double> *db) {
-    cx<double> acc = mk(0.0, 0.0);
+  // at of a staged spinor
+  __device__ static void at(const cx<double> *e, cx<double> a[3]) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) acc = acc + cmulc(c[k], proj(db[(HS * 3 + k) * kPsRow], db[(PS * 3 + k) * kPsRow]));
-    return acc;
+    for (int k = 0; k < 3; ++k) a[k] = proj(e[HS * 3 + k], e[PS * 3 + k]);
   }
 };
 
-// Stage 64 sites' worth of f - g (g null: f) into LDS: piece p = 12 site +
-// k is complex k of the spinor at full site index idx[site] (-1: a site
-// past the end, zero; it loads site 0 and drops it, so that the loads of
-// all pieces go out together).
-__device__ inline void ps_stage(cx<double> *sh, const cx<double> *f, const cx<double> *g, const int *idx) {
-  cx<double> v[3];
-  bool ok[3];
-  int at[3];
-#pragma unroll
-  for (int u = 0; u < 3; ++u) {
-    const int p = threadIdx.x + u * kBlock;
-    const int site = p / 12, k = p - 12 * site;
-    const int s = idx[site];
-    ok[u] = s >= 0;
-    const size_t o = size_t(ok[u] ? s : 0) * 12 + k;
-    v[u] = ldc(f + o);
-    if (g) v[u] = v[u] - ldc(g + o);
-    at[u] = k * kPsRow + site;
-  }
-#pragma unroll
-  for (int u = 0; u < 3; ++u) sh[at[u]] = ok[u] ? v[u] : mk(0.0, 0.0);
+// LDS operations of one wave are carried out in order; this keeps the
+// compiler from moving them across the point where lanes exchange data.
+__device__ inline void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
-// Wave q's colour vector of direction MU at its lane's site: eta at y + mu
-// in fS, at y - mu in bS.
-template <int MU>
-__device__ inline void ps_eta_side(const cx<double> *U, size_t Vh, const int (*nb)[kPsSites],
-                                   const cx<double> *fS, const cx<double> *bS, size_t s, int par, int q,
-                                   cx<double> c[3]) {
-  const int site = threadIdx.x & 63;
-  if (q < 2) {
-    const cx<double> *u = ps_link_at(U, Vh, size_t(nb[2 * MU + 1][site]), par ^ 1, MU);  // U_mu(y - mu)
-    if (q == 0) PsHalf<MU, true, 0>::eta_side(u, Vh, bS + site, c);
-    else PsHalf<MU, true, 1>::eta_side(u, Vh, bS + site, c);
-  } else {
-    const cx<double> *u = ps_link_at(U, Vh, s, par, MU);  // U_mu(y)
-    if (q == 2) PsHalf<MU, false, 0>::eta_side(u, Vh, fS + site, c);
-    else PsHalf<MU, false, 1>::eta_side(u, Vh, fS + site, c);
+// c = U^+ a (DAG) or U a.
+template <bool DAG>
+__device__ inline void ps_colour(const cx<double> u[9], const cx<double> a[3], cx<double> c[3]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    double re = 0.0, im = 0.0;
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      const cx<double> w = u[DAG ? 3 * b + k : 3 * k + b];
+      const double wi = DAG ? -w.im : w.im;
+      re = fma(w.re, a[b].re, re);
+      im = fma(w.re, a[b].im, im);
+      re = fma(-wi, a[b].im, re);
+      im = fma(wi, a[b].re, im);
+    }
+    c[k] = mk(re, im);
   }
 }
 
+// The rows of direction MU at the wave's 64 sites (lane = site, full index
+// s of parity par; on: inside the timeslice, else the rows are zero) into
+// reg.  sf, sb: index of the site's forward and backward neighbour.
 template <int MU>
-__device__ inline cx<double> ps_term(const cx<double> c[3], const cx<double> *dS, int q, double kappa) {
-  const int site = threadIdx.x & 63;
-  if (q == 0) return -kappa * PsHalf<MU, true, 0>::term(c, dS + site);
-  if (q == 1) return -kappa * PsHalf<MU, true, 1>::term(c, dS + site);
-  if (q == 2) return kappa * PsHalf<MU, false, 0>::term(c, dS + site);
-  return kappa * PsHalf<MU, false, 1>::term(c, dS + site);
+__device__ inline void ps_rows(const cx<double> *__restrict__ U, size_t Vh, const cx<double> *__restrict__ eta,
+                               double kappa, int s, int sf, int sb, int par, bool on, cx<double> *reg) {
+  const int lane = threadIdx.x & 63;
+  cx<double> vb[12], vf[12], ub[9], uf[9];
+#pragma unroll
+  for (int u = 0; u < 12; ++u) {  // piece j = lane + 64 u: complex j % 12 of site j / 12
+    const int j = lane + 64 * (u % 3), site = j / 12 + 16 * (u / 3), k = j % 12;
+    vb[u] = ldc(eta + size_t(__shfl(sb, site)) * 12 + k);
+    vf[u] = ldc(eta + size_t(__shfl(sf, site)) * 12 + k);
+  }
+  const cx<double> *Ub = U + ((size_t(par ^ 1) * 4 + MU) * 9) * Vh + (sb >> 1);  // U_mu(y - mu)
+  const cx<double> *Uf = U + ((size_t(par) * 4 + MU) * 9) * Vh + (s >> 1);       // U_mu(y)
+#pragma unroll
+  for (int e = 0; e < 9; ++e) ub[e] = ldc(Ub + e * Vh);
+  cx<double> *own = reg + lane * kPsStride;
+  cx<double> a0[3], a1[3], cf[2][3], cb[2][3];
+  auto put = [&](const cx<double> *v) {
+    wave_order();
+#pragma unroll
+    for (int u = 0; u < 12; ++u) {
+      const int j = lane + 64 * (u % 3), site = j / 12 + 16 * (u / 3), k = j % 12;
+      reg[site * kPsStride + k] = v[u];
+    }
+    wave_order();
+  };
+  put(vb);
+#pragma unroll
+  for (int e = 0; e < 9; ++e) uf[e] = ldc(Uf + e * Vh);
+  PsHalf<MU, true, 0>::at(own, a0);
+  PsHalf<MU, true, 1>::at(own, a1);
+  ps_colour<true>(ub, a0, cf[0]);
+  ps_colour<true>(ub, a1, cf[1]);
+  put(vf);
+  PsHalf<MU, false, 0>::at(own, a0);
+  PsHalf<MU, false, 1>::at(own, a1);
+  ps_colour<false>(uf, a0, cb[0]);
+  ps_colour<false>(uf, a1, cb[1]);
+  wave_order();
+  const double kp = on ? kappa : 0.0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (MU == kNumPS - 1) {  // t: the upper halves of both rows (the lower ones differ by a sign)
+        own[3 * h + k] = on ? -kp * cf[h][k] : mk(0.0, 0.0);
+        own[6 + 3 * h + k] = on ? kp * cb[h][k] : mk(0.0, 0.0);
+      } else {
+        const cx<double> lo = -kp * (cf[h][k] + cb[h][k]);
+        own[3 * h + k] = on ? kp * (cb[h][k] - cf[h][k]) : mk(0.0, 0.0);
+        if (h == 0) own[PsHalf<MU, true, 0>::PS * 3 + k] = on ? PsHalf<MU, true, 0>::phase(lo) : mk(0.0, 0.0);
+        else own[PsHalf<MU, true, 1>::PS * 3 + k] = on ? PsHalf<MU, true, 1>::phase(lo) : mk(0.0, 0.0);
+      }
+    }
+}
+
+// Where component k of a row's vector is found at a site (place in LDS, site
+// 0) and the quarter turns to apply to it.
+__device__ inline void row_piece(int row, int k, int *off, int *turns) {
+  const int s = k / 3, c = k % 3;
+  *off = k;
+  *turns = 0;
+#pragma unroll
+  for (int th = 0; th < kNumTheta; ++th)  // (Theta d)_sp = val d_col: g_col = conj(val) eta_sp
+#pragma unroll
+    for (int sp = 0; sp < 4; ++sp)
+      if (row == th && kGamma[th].col[sp] == s) {
+        *off = 3 * sp + c;
+        *turns = kGamma[th].re[sp] == 1.0 ? 0 : kGamma[th].im[sp] == -1.0 ? 1 : kGamma[th].re[sp] == -1.0 ? 2 : 3;
+      }
+  if (row >= kNumTheta && row < kPsRows - 2) *off = (row - kNumTheta + 1) * kPsRegion + k;
+  if (row == kPsRows - 2 || row == kPsRows - 1) {
+    *off = kNumPS * kPsRegion + (row == kPsRows - 1 ? 6 : 0) + 3 * (s & 1) + c;
+    *turns = row == kPsRows - 2 && s >= 2 ? 2 : 0;
+  }
+}
+
+// The value of the lane next to this one (lane ^ 1).
+__device__ inline double swap_pair(double v) {
+  const long long b = __builtin_bit_cast(long long, v);
+  const int lo = __builtin_amdgcn_update_dpp(0, int(b), 0xB1, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, int(b >> 32), 0xB1, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
+}
+// v, or -v where mask is the sign bit.
+__device__ inline double flip(double v, unsigned mask) {
+  return __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, v) ^
+                                        (static_cast<unsigned long long>(mask) << 32));
 }
 
 // Workgroup order: the right-hand side varies fastest within one XCD's
 // contiguous range of logical workgroups (hardware workgroup h runs on XCD
 // h % 8), so the nrhs workgroups of one chunk of sites run back to back on
 // one XCD and read its links from that XCD's L2 (links are as many bytes as
-// one right-hand side's three fields).  Variant v of the launch is variant
-// v0 + v of the call.
-template <int NV>
-__global__ void __launch_bounds__(kBlock)
-    k_estimate_ps(Geom g, const cx<double> *__restrict__ U, double kappa,
-                  const cx<double> *__restrict__ eta, const cx<double> *__restrict__ x, XtSet xts, int v0,
-                  int nch, int nrhs, int xq, double *__restrict__ out) {
-  __shared__ double sh[NV * 2 * kNumPS][kWaves];
-  __shared__ cx<double> fS[kPsArr], bS[kPsArr], dS[kPsArr];
-  __shared__ int nb[2 * kNumPS + 1][kPsSites];  // neighbour site indices [2 mu + backward]; the sites
+// one right-hand side's three fields).
+__global__ void __launch_bounds__(kBlock, 2)
+    k_estimate_all(Geom g, const cx<double> *__restrict__ U, double kappa, const cx<double> *__restrict__ eta,
+                   const cx<double> *__restrict__ x, XtSet xts, int nv, int nch, int nrhs, int xq,
+                   double *__restrict__ out) {
+  typedef double d4 __attribute__((ext_vector_type(4)));
+  __shared__ cx<double> reg[(1 + kNumPS) * kPsRegion];
   const int L = int(blockIdx.x % 8) * xq + int(blockIdx.x / 8);
   if (L >= g.L[3] * nch * nrhs) return;  // whole workgroup: padding of the grid
   const int r = L % nrhs, tch = L / nrhs;
   const int t = tch / nch, ch = tch % nch;
   const int Lx = g.L[0], Ly = g.L[1], Lz = g.L[2], Lt = g.L[3];
   const int Vs = Lx * Ly * Lz;
-  const size_t Vh = size_t(g.Vh);
-  const size_t base = size_t(r) * size_t(g.V) * 12;
+  const size_t Vh = size_t(g.Vh), base = size_t(r) * size_t(g.V) * 12;
   eta += base;
-  x += base;
+  const int lane = threadIdx.x & 63, q = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  // product: lane = row and column l % 16, components l / 16 of groups of four;
+  // gr, gi: places (in doubles) of the real and imaginary part of the row's
+  // components and the signs they take
+  const int l16 = lane & 15, kq = lane >> 4;
+  int gr[3], gi[3];
+  unsigned sr[3], si[3];
 #pragma unroll
-  for (int v = 0; v < NV; ++v)
-    if (xts.p[v]) xts.p[v] += base;
-  const int q = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
-  double acc[NV][2 * kNumPS] = {};
+  for (int j = 0; j < 3; ++j) {
+    int off, turns;
+    row_piece(l16, 4 * j + kq, &off, &turns);
+    off += q * (kPsSites / kWaves) * kPsStride;
+    gr[j] = 2 * off + (turns & 1);
+    gi[j] = 2 * off + 1 - (turns & 1);
+    sr[j] = turns == 1 || turns == 2 ? 0x80000000u : 0u;
+    si[j] = turns >= 2 ? 0x80000000u : 0u;
+  }
+  const double *xp = reinterpret_cast<const double *>(x + base) + 2 * kq + (l16 & 1), *tp = nullptr;
+#pragma unroll
+  for (int v = 0; v < kMaxVar; ++v)
+    if (v < nv && v == l16 >> 1) tp = reinterpret_cast<const double *>(xts.p[v]);
+  const double minus = tp ? -1.0 : 0.0;
+  tp = tp ? tp + 2 * base + 2 * kq + (l16 & 1) : xp;
+  const unsigned odd = (l16 & 1) ? 0x80000000u : 0u;
+  d4 tot = {0, 0, 0, 0};
   for (int i0 = ch * kPsSites; i0 < Vs; i0 += nch * kPsSites) {
-    const int site = threadIdx.x & 63;
-    const int i = i0 + site;
+    const int i = i0 + lane;
     const bool on = i < Vs;
     const int c4[4] = {i % Lx, (i / Lx) % Ly, i / (Lx * Ly), t};
-    const size_t s = size_t(t) * Vs + i;
     const int par = (c4[0] + c4[1] + c4[2] + t) & 1;
-    __syncthreads();  // the previous chunk's reads of nb and dS are done
-    {
-      // wave q: the forward and backward neighbours of the sites along mu = q
-      const int st = q == 0 ? 1 : q == 1 ? Lx : q == 2 ? Lx * Ly : Vs;
-      const int Lm = g.L[q], cm = c4[q];
-      nb[2 * q][site] = on ? int(cm + 1 == Lm ? s - size_t(st) * (Lm - 1) : s + st) : -1;
-      nb[2 * q + 1][site] = on ? int(cm == 0 ? s + size_t(st) * (Lm - 1) : s - st) : -1;
-      if (q == 0) nb[2 * kNumPS][site] = on ? int(s) : -1;
-    }
-    // the colour vectors of the four directions
-    cx<double> c[kNumPS][3];
+    const int s = on ? t * Vs + i : 0;
+    const int st = q == 0 ? 1 : q == 1 ? Lx : q == 2 ? Lx * Ly : Vs;
+    const int Lm = g.L[q], cm = c4[q];
+    const int sf = on ? (cm + 1 == Lm ? s - st * (Lm - 1) : s + st) : 0;
+    const int sb = on ? (cm == 0 ? s + st * (Lm - 1) : s - st) : 0;
+    __syncthreads();  // the previous chunk's products are done
+    {  // eta at the sites: piece j = thread + 256 u (past the end: site 0, dropped)
+      cx<double> v[3];
 #pragma unroll
-    for (int mu = 0; mu < kNumPS; ++mu) {
-      __syncthreads();  // nb written; the previous direction's reads of fS, bS done
-      ps_stage(fS, eta, nullptr, nb[2 * mu]);
-      asm volatile("" ::: "memory");  // the backward loads after the forward ones (fewer registers live)
-      ps_stage(bS, eta, nullptr, nb[2 * mu + 1]);
-      __syncthreads();
-      if (on) {
-        if (mu == 0) ps_eta_side<0>(U, Vh, nb, fS, bS, s, par, q, c[0]);
-        else if (mu == 1) ps_eta_side<1>(U, Vh, nb, fS, bS, s, par, q, c[1]);
-        else if (mu == 2) ps_eta_side<2>(U, Vh, nb, fS, bS, s, par, q, c[2]);
-        else ps_eta_side<3>(U, Vh, nb, fS, bS, s, par, q, c[3]);
+      for (int u = 0; u < 3; ++u) {
+        const int j = threadIdx.x + u * kBlock;
+        v[u] = ldc(eta + (size_t(t) * Vs + i0) * 12 + (i0 + j / 12 < Vs ? j : 0));
+      }
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        const int j = threadIdx.x + u * kBlock;
+        reg[j / 12 * kPsStride + j % 12] = i0 + j / 12 < Vs ? v[u] : mk(0.0, 0.0);
       }
     }
+    cx<double> *mine = reg + (1 + q) * kPsRegion;
+    if (q == 0) ps_rows<0>(U, Vh, eta, kappa, s, sf, sb, par, on, mine);
+    else if (q == 1) ps_rows<1>(U, Vh, eta, kappa, s, sf, sb, par, on, mine);
+    else if (q == 2) ps_rows<2>(U, Vh, eta, kappa, s, sf, sb, par, on, mine);
+    else ps_rows<3>(U, Vh, eta, kappa, s, sf, sb, par, on, mine);
+    // products of the wave's 16 sites, two at a time, the next ones' d in
+    // flight (sites past the end, whose rows are zero, read the last one)
+    constexpr int NS = kPsSites / kWaves, BS = 2;
+    double xv[2][3 * BS], tv[2][3 * BS];
+    const int w0 = i0 + q * NS;
+    auto fetch = [&](int b, double *px, double *pt) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      if (v > 0) __syncthreads();  // the previous variant's reads of dS are done
-      ps_stage(dS, x, xts.p[v], nb[2 * kNumPS]);
-      __syncthreads();
-      if (on) {
-        const cx<double> t0 = ps_term<0>(c[0], dS, q, kappa), t1 = ps_term<1>(c[1], dS, q, kappa);
-        const cx<double> t2 = ps_term<2>(c[2], dS, q, kappa), t3 = ps_term<3>(c[3], dS, q, kappa);
-        acc[v][0] += t0.re;
-        acc[v][1] += t0.im;
-        acc[v][2] += t1.re;
-        acc[v][3] += t1.im;
-        acc[v][4] += t2.re;
-        acc[v][5] += t2.im;
-        acc[v][6] += t3.re;
-        acc[v][7] += t3.im;
+      for (int u = 0; u < BS; ++u) {
+        const size_t o = (size_t(t) * Vs + std::min(w0 + BS * b + u, Vs - 1)) * 24;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          px[3 * u + j] = xp[o + 8 * j];
+          pt[3 * u + j] = tp[o + 8 * j];
+        }
+      }
+    };
+    fetch(0, xv[0], tv[0]);
+    __syncthreads();
+    const double *rd = reinterpret_cast<const double *>(reg);
+    d4 acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};  // of this chunk: short chains of sums round less
+#pragma unroll
+    for (int b = 0; b < NS / BS; ++b) {
+      if (b + 1 < NS / BS) fetch(b + 1, xv[(b + 1) & 1], tv[(b + 1) & 1]);
+#pragma unroll
+      for (int u = 0; u < BS; ++u) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          const int site = 2 * (BS * b + u) * kPsStride;
+          const double d = fma(minus, tv[b & 1][3 * u + j], xv[b & 1][3 * u + j]);
+          acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(flip(rd[gr[j] + site], sr[j]), d, acc0, 0, 0, 0);
+          acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(flip(rd[gi[j] + site], si[j]), flip(swap_pair(d), odd), acc1, 0,
+                                                      0, 0);
+        }
       }
     }
+    tot += acc0 + acc1;
   }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int v = 0; v < NV; ++v)
-#pragma unroll
-    for (int k = 0; k < 2 * kNumPS; ++k) acc[v][k] = wave_sum(acc[v][k]);
-  if (lane == 0)
-#pragma unroll
-    for (int v = 0; v < NV; ++v)
-#pragma unroll
-      for (int k = 0; k < 2 * kNumPS; ++k) sh[v * 2 * kNumPS + k][wave] = acc[v][k];
+  // the four waves' sums, in order
   __syncthreads();
-  // directions x, y, z: all four waves' sums at this timeslice; t: the
-  // forward waves' (0, 1) at t - 1 in slot 8, the backward waves' (2, 3) at
-  // t + 1 in slot 9
-  if (threadIdx.x < NV * (2 * kNumPS + 2)) {
-    const int v = threadIdx.x / (2 * kNumPS + 2), k = threadIdx.x % (2 * kNumPS + 2);
-    const int m = k / 2, part = k % 2;  // m = 4: the backward t terms
-    const double *row = sh[v * 2 * kNumPS + 2 * (m < kNumPS ? m : kNumPS - 1) + part];
-    double sum;
-    int slot, trow;
-    if (m < kNumPS - 1) {
-      sum = ((row[0] + row[1]) + row[2]) + row[3];
-      slot = kNumTheta + m;
-      trow = t;
-    } else if (m == kNumPS - 1) {
-      sum = row[0] + row[1];
-      slot = kNumOps - 1;
-      trow = t == 0 ? Lt - 1 : t - 1;
-    } else {
-      sum = row[2] + row[3];
-      slot = kNumOps;
-      trow = t + 1 == Lt ? 0 : t + 1;
-    }
-    out[((((size_t(v0 + v) * nrhs + r) * kOpSlots + slot) * Lt + trow) * nch + ch) * 2 + part] = sum;
+  double *sh = reinterpret_cast<double *>(reg);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) sh[q * 256 + (kq + 4 * u) * 16 + l16] = tot[u];
+  __syncthreads();
+  const int row = threadIdx.x >> 4, col = threadIdx.x & 15, v = col >> 1;
+  if (row < kPsRows && v < nv) {
+    const int trow = row == kPsRows - 2 ? (t == 0 ? Lt - 1 : t - 1) : row == kPsRows - 1 ? (t + 1 == Lt ? 0 : t + 1) : t;
+    double sum = sh[threadIdx.x];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) sum += sh[w * 256 + threadIdx.x];
+    out[((((size_t(v) * nrhs + r) * kOpSlots + row) * Lt + trow) * nch + ch) * 2 + (col & 1)] = sum;
   }
 }
 
@@ -393,14 +453,10 @@ int estimate_chunks(const Geom &g, int nrhs, size_t cap_doubles) {
   return nch;
 }
 
-// Variants per launch.  The local kernel's per-lane sums grow by 10 doubles
-// per variant, and at 24^3 x 32 with 16 right-hand sides groups of three are
-// fastest (2.2 ms for six variants, 2.6 in pairs, 2.4 all at once).  The
-// point-split kernel's eta side (neighbour stagings and links, 2.5 ms) is
-// shared by the variants of a launch, each adding 0.6 ms: all six in one
-// launch (6.0 ms) beat three (8.9) or two (11.9) despite the occupancy its
-// registers leave.
-constexpr int kLocalGroup = 3, kPsGroup = 6;
+// Variants per launch of the local kernel: its per-lane sums grow by 10
+// doubles per variant, and at 24^3 x 32 with 16 right-hand sides groups of
+// three are fastest (2.0 ms for six variants, 2.6 in pairs, 2.4 all at once).
+constexpr int kLocalGroup = 3;
 
 template <int NV>
 void launch_local(lqcd_ctx *c, const void *eta, const void *x, const XtSet &xts, int v0, int nrhs, double *d,
@@ -413,28 +469,15 @@ void launch_local(lqcd_ctx *c, const void *eta, const void *x, const XtSet &xts,
   LQCD_HIP(hipGetLastError());
 }
 
-template <int NV>
-void launch_ps(lqcd_ctx *c, const void *eta, const void *x, const XtSet &xts, int v0, int nrhs, double *d,
-               int nch) {
+void launch_all(lqcd_ctx *c, const void *eta, const void *x, const XtSet &xts, int nv, int nrhs, double *d,
+                int nch) {
   const Geom &g = c->g;
-  const int Lt = g.L[3];
-  const int xq = (Lt * nch * nrhs + 7) / 8;  // logical workgroups per XCD (grid padded to 8 xq)
-  hipLaunchKernelGGL(k_estimate_ps<NV>, dim3(8 * xq), dim3(kBlock), 0, c->stream, g,
+  const int xq = (g.L[3] * nch * nrhs + 7) / 8;  // logical workgroups per XCD (grid padded to 8 xq)
+  hipLaunchKernelGGL(k_estimate_all, dim3(8 * xq), dim3(kBlock), 0, c->stream, g,
                      static_cast<const cx<double> *>(c->U64.ptr), c->kappa, static_cast<const cx<double> *>(eta),
-                     static_cast<const cx<double> *>(x), xts, v0, nch, nrhs, xq, d);
+                     static_cast<const cx<double> *>(x), xts, nv, nch, nrhs, xq, d);
   LQCD_HIP(hipGetLastError());
 }
-
-// Launch KERNEL<n> over the variants [v0, v0 + n) for n <= 6.
-#define LQCD_EST_DISPATCH(KERNEL, n, ...)                  \
-  switch (n) {                                             \
-    case 1: KERNEL<1>(__VA_ARGS__); break;                 \
-    case 2: KERNEL<2>(__VA_ARGS__); break;                 \
-    case 3: KERNEL<3>(__VA_ARGS__); break;                 \
-    case 4: KERNEL<4>(__VA_ARGS__); break;                 \
-    case 5: KERNEL<5>(__VA_ARGS__); break;                 \
-    default: KERNEL<6>(__VA_ARGS__); break;                \
-  }
 
 // The estimator of nvar variants (subtracted vectors xt[v], corrections
 // corr[v]) with its partial sums in d (at least nvar * nrhs * kOpSlots * Lt
@@ -444,24 +487,24 @@ void launch_ps(lqcd_ctx *c, const void *eta, const void *x, const XtSet &xts, in
 void estimate_with(lqcd_ctx *c, const int *thetas, int nth, const void *eta, const void *x,
                    const void *const *xt, int nvar, int nrhs, const double *const *corr, double *est,
                    double *stderr_, double *samples, double *d, int nch) {
-  bool any_local = false, any_ps = false;
-  for (int a = 0; a < nth; ++a) (thetas[a] < kNumTheta ? any_local : any_ps) = true;
+  bool any_ps = false;
+  for (int a = 0; a < nth; ++a) any_ps = any_ps || thetas[a] >= kNumTheta;
   auto group = [&](int v0, int n) {
     XtSet xts{};
     for (int v = 0; v < n; ++v) xts.p[v] = static_cast<const cx<double> *>(xt[v0 + v]);
     return xts;
   };
-  if (any_local)
+  // local operators alone need neither links nor neighbours: their own kernel
+  if (any_ps) launch_all(c, eta, x, group(0, nvar), nvar, nrhs, d, nch);
+  else
     for (int v0 = 0; v0 < nvar; v0 += kLocalGroup) {
-      const int n = std::min(kLocalGroup, nvar - v0);
-      LQCD_EST_DISPATCH(launch_local, n, c, eta, x, group(v0, n), v0, nrhs, d, nch)
+      const XtSet xts = group(v0, std::min(kLocalGroup, nvar - v0));
+      switch (nvar - v0) {
+        case 1: launch_local<1>(c, eta, x, xts, v0, nrhs, d, nch); break;
+        case 2: launch_local<2>(c, eta, x, xts, v0, nrhs, d, nch); break;
+        default: launch_local<kLocalGroup>(c, eta, x, xts, v0, nrhs, d, nch); break;
+      }
     }
-  if (any_ps)
-    for (int v0 = 0; v0 < nvar; v0 += kPsGroup) {
-      const int n = std::min(kPsGroup, nvar - v0);
-      LQCD_EST_DISPATCH(launch_ps, n, c, eta, x, group(v0, n), v0, nrhs, d, nch)
-    }
-#undef LQCD_EST_DISPATCH
   const int Lt = c->g.L[3];
   std::vector<double> hc(size_t(nvar) * nrhs * kOpSlots * Lt * nch * 2);
   LQCD_HIP(hipMemcpyAsync(hc.data(), d, hc.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream));
