@@ -387,3 +387,34 @@ def test_sstep_arnoldi_plain_basis_two_units_per_lane(inner):
     a, b = to_host(xs[1]), to_host(xs[4])
     # both within 1e-12 / lambda_min(M) of the solution, lambda_min > 0.05 here
     assert np.linalg.norm(a - b) < 4e-11 * np.linalg.norm(a)
+
+
+@pytest.mark.parametrize("zeros", [(), (1,), (2, 4), (1, 2, 3), (5,), (1, 2, 3, 4, 5)])
+@pytest.mark.parametrize("inner", ["f64", "f32", "f16"])
+def test_finished_right_hand_sides_change_places(zeros, inner):
+    """A block whose right-hand sides finish at different times: zero sources,
+    finished before the first cycle, at the front, middle and end of a block of
+    five, and one eigenvector-like source among noise.  Every solution belongs
+    to its own source (LU, 1e-9, the bar of the solver's other tests) and the
+    sources stay as they were."""
+    require_gpu()
+    dims, kappa = (4, 4, 2, 4), 0.13
+    ctx, U = context(dims, 0.3, 1001, kappa)
+    eta = z4_noise(2003, dims, 0, 6).astype(np.complex128)
+    eta[3] *= 1e-3
+    for z in zeros:
+        eta[z] = 0
+    M = W.dense_M(U, kappa, dims)
+    xref = np.linalg.solve(M, eta.reshape(6, -1).T).T.reshape(eta.shape)
+    say("solve swaps", zeros, inner)
+    eg = to_gpu(eta)
+    x, _, st = ctx.gmresdr_solve(eg, op="schur", m=20, k=10, tol=1e-11, tol_super=1e-13, inner=inner,
+                                 inner_tol=1e-3, rhs_block=5)
+    x = to_host(x)
+    np.testing.assert_array_equal(to_host(eg), eta)
+    for r in range(6):
+        if r in zeros:
+            np.testing.assert_array_equal(x[r], 0)
+        else:
+            assert rel_err(x[r], xref[r]) < 1e-9, r
+            assert st[r]["true_resid"] < 1e-11, r
