@@ -608,6 +608,190 @@ __global__ void __launch_bounds__(8 * kLegSites) __attribute__((amdgpu_waves_per
   }
 }
 
+// ------------------------------------------- full operators, lexicographic
+// A full-lattice operator on site-major FP64 fields (192 bytes a site) in
+// place of pack, hop and unpack.  Eight waves take the terms of 64 sites of
+// both parities, consecutive along x and y (lane = site, the link in registers
+// over the right-hand sides, as in k_hop_legs), but every access to a field
+// covers consecutive 16-byte pieces of consecutive sites: a wave loads both
+// spin partners of its neighbours in pieces, adds them and exchanges the half
+// spinors through LDS, where the products take their place; six waves then sum
+// the terms of the outputs, lane = piece, and store 1 KB runs.  The
+// lower half of a term is its upper one with signs and re / im exchanged, so
+// a lane reads the real and imaginary part it needs apart and adds them with
+// a sign.  Per right-hand side the arithmetic and its order are k_hop_legs's.
+// Bound by HBM and the latency of its phases: MG5 on 24^3 x 32, 16 right-hand
+// sides, FP64 2252 us (pack, hop, unpack) -> 1352 us, 2.4 TB/s of links and
+// fields; FP32 1676 -> 1014 us.  FP64 holds the next right-hand side's pieces in
+// registers and has one workgroup per CU; at two per CU without them it spills
+// (1839 us), with them more (3254 us).  FP32 fits two per CU without (1014 us;
+// with the pieces ahead 1374).
+constexpr int kLexStride = 7;                        // of a site's six products: distinct banks across sites
+constexpr int kLexRegion = kLegSites * kLexStride;   // one term
+// v, or -v where mask is the sign bit (one register where a factor takes two).
+__device__ inline double flip(double v, unsigned mask) {
+  return __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, v) ^
+                                        (static_cast<unsigned long long>(mask) << 32));
+}
+__device__ inline float flip(float v, unsigned mask) {
+  return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, v) ^ mask);
+}
+template <class R, bool G5IN, bool G5OUT, bool SELF>
+__global__ void __launch_bounds__(8 * kLegSites) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 2 : 4, 8)))
+    k_hop_lex(Geom g, const cx<R> *__restrict__ U, const cx<double> *__restrict__ in, cx<double> *__restrict__ out,
+              R alpha, R beta, size_t stride, int nrhs, int rg, int xq, int tb, int nt) {
+  __shared__ cx<R> sh[8 * kLexRegion];
+  const int L = int(blockIdx.x % 8) * xq + int(blockIdx.x / 8);  // XCD-aware order, as k_hop
+  const int ngr = (nrhs + rg - 1) / rg;
+  const int tile = L / ngr;
+  if (tile * kLegSites >= g.V) return;  // whole workgroup: padding of the grid
+  const int r0 = L % ngr * rg, r1 = min(nrhs, r0 + rg);
+  const int il = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const size_t Vh = size_t(g.Vh);
+  const int q = tile * kLegSites + il;
+  int lex, nb, par;
+  int c[4];
+  {
+    // place q of the sweep: blocks of tb timeslices, z, t within the block, y, x
+    const int ppl = g.L[0] * g.L[1];
+    int rem = q < g.V ? q : 0;
+    const int per = tb * g.L[2] * ppl, b = rem / per;
+    rem -= b * per;
+    const int nt_ = min(tb, g.L[3] - b * tb);
+    c[2] = rem / (nt_ * ppl);
+    rem -= c[2] * (nt_ * ppl);
+    const int tt = rem / ppl;
+    rem -= tt * ppl;
+    c[3] = b * tb + tt;
+    c[1] = rem / g.L[0];
+    c[0] = rem % g.L[0];
+    lex = c[0] + g.L[0] * (c[1] + g.L[1] * (c[2] + g.L[2] * c[3]));
+    par = (c[0] + c[1] + c[2] + c[3]) & 1;
+  }
+  const int mu = wave >> 1;
+  const bool fwd = !(wave & 1);
+  cx<R> e[9];  // this wave's link
+  {
+    const int Lm = g.L[mu], st = mu == 0 ? 1 : mu == 1 ? g.L[0] : mu == 2 ? g.L[0] * g.L[1] : g.L[0] * g.L[1] * g.L[2];
+    const int cm = mu == 0 ? c[0] : mu == 1 ? c[1] : mu == 2 ? c[2] : c[3];
+    nb = fwd ? (cm + 1 == Lm ? lex - st * (Lm - 1) : lex + st) : (cm == 0 ? lex + st * (Lm - 1) : lex - st);
+    const cx<R> *u = U + ((size_t(fwd ? par : 1 - par) * 4 + mu) * 9) * Vh + ((fwd ? lex : nb) >> 1);
+    if (nt) {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) e[k] = ldc_nt(u + k * Vh);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) e[k] = ldc(u + k * Vh);
+    }
+  }
+  constexpr unsigned kNeg = 0x80000000u;
+  // the wave's pieces of the neighbours: (half spin, colour) j % 6 of site j /
+  // 6, j = il + 64 m; the partner spin lies dp pieces on and enters with sign sg
+  // (times i along x and z)
+  uint32_t at[6];
+  int dp[3];
+  unsigned sg[3];
+#pragma unroll
+  for (int m = 0; m < 6; ++m) {
+    const int j = il + 64 * (m % 3), k = j % 6, h = k / 3;
+    at[m] = uint32_t(__shfl(nb, j / 6 + 32 * (m / 3))) * 12 + k;
+    if (m < 3) {
+      dp[m] = 3 * ((mu < 2 ? 3 - h : 2 + h) - h);
+      const bool neg = (mu == 0 ? false : mu == 3 ? true : h == 1) != !fwd;
+      sg[m] = neg != G5IN ? kNeg : 0u;
+    }
+  }
+  // the lane's outputs: component ko of sites so and so + 32
+  const int po = wave * 64 + il, so = po / 12, ko = po % 12, sp = ko / 3;
+  const uint32_t o0 = uint32_t(__shfl(lex, so & 63)) * 12 + ko, o1 = uint32_t(__shfl(lex, (so + 32) & 63)) * 12 + ko;
+  const bool on0 = wave < 6 && tile * kLegSites + so < g.V, on1 = wave < 6 && tile * kLegSites + so + 32 < g.V;
+  const int low = sp >= 2;
+  const R *sr = reinterpret_cast<const R *>(sh);
+  // x, y: product spin 3 - sp below; z, t: sp - 2; re and im exchanged along x, z
+  const int ba = 2 * (so * kLexStride + (low ? 3 - sp : sp) * 3 + ko % 3);
+  const int bb = 2 * (so * kLexStride + (low ? sp - 2 : sp) * 3 + ko % 3);
+  const unsigned f1 = low ? kNeg : 0u;      // x, t
+  const unsigned f2 = sp == 2 ? kNeg : 0u;  // y forward, z backward real
+  const unsigned f3 = sp == 3 ? kNeg : 0u;  // y backward, z forward real
+  auto term = [&](int leg, int h, unsigned fr, unsigned fi, bool x, int b, R &re, R &im) {
+    const R *p = sr + 2 * (leg * kLexRegion + h * 32 * kLexStride) + b;
+    const int w = x ? low : 0;
+    re = re + flip(p[w], fr);
+    im = im + flip(p[1 - w], fi);
+  };
+  auto store = [&](int h, uint32_t o, const cx<double> *ir, cx<double> *orr) {
+    R re = 0, im = 0;
+    // lower spins: x -i / +i; y: see f2, f3; z -+i; t -+1
+    term(0, h, 0u, f1, true, ba, re, im);
+    term(1, h, f1, 0u, true, ba, re, im);
+    term(2, h, f2, f2, false, ba, re, im);
+    term(3, h, f3, f3, false, ba, re, im);
+    term(4, h, f3, f2, true, bb, re, im);
+    term(5, h, f2, f3, true, bb, re, im);
+    term(6, h, f1, f1, false, bb, re, im);
+    term(7, h, 0u, 0u, false, bb, re, im);
+    re = beta * re;
+    im = beta * im;
+    if (SELF) {
+      const cx<double> w = ldc(ir + o);
+      re = re + alpha * flip(R(w.re), G5IN ? f1 : 0u);
+      im = im + alpha * flip(R(w.im), G5IN ? f1 : 0u);
+    }
+    if (G5OUT && low) {
+      re = -re;
+      im = -im;
+    }
+    if (nt) stc_nt(orr + o, mk(double(re), double(im)));
+    else stc(orr + o, mk(double(re), double(im)));
+  };
+  cx<R> *reg = sh + wave * kLexRegion;
+  cx<double> v[6], p[6];
+  auto fetch = [&](int r) {
+    const cx<double> *ir = in + size_t(r) * stride;
+#pragma unroll
+    for (int m = 0; m < 6; ++m) {
+      v[m] = ldc(ir + at[m]);
+      p[m] = ldc(ir + (at[m] + dp[m % 3]));
+    }
+  };
+  constexpr bool kAhead = sizeof(R) == 8;
+  if (kAhead) fetch(r0);
+  for (int r = r0; r < r1; ++r) {
+    const cx<double> *ir = in + size_t(r) * stride;
+    if (!kAhead) fetch(r);
+    if (r > r0) __syncthreads();  // the previous right-hand side's sums are done
+#pragma unroll
+    for (int m = 0; m < 6; ++m) {
+      const int j = il + 64 * (m % 3);
+      const R vr = R(v[m].re), vi = R(v[m].im), pr = flip(R(p[m].re), sg[m % 3]), pi = flip(R(p[m].im), sg[m % 3]);
+      reg[(j / 6 + 32 * (m / 3)) * kLexStride + j % 6] =
+          (mu & 1) ? mk<R>(vr + pr, vi + pi) : mk<R>(vr - pi, vi + pr);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // lanes of one wave exchange data
+    __builtin_amdgcn_wave_barrier();
+    cx<R> h[6], w[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) h[k] = reg[il * kLexStride + k];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        if (fwd) w[3 * s + k] = cfma(e[3 * k + 2], h[3 * s + 2], cfma(e[3 * k + 1], h[3 * s + 1], cmul_f(e[3 * k], h[3 * s])));
+        else w[3 * s + k] = cfmac(e[6 + k], h[3 * s + 2], cfmac(e[3 + k], h[3 * s + 1], cmulc_f(e[k], h[3 * s])));
+      }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int k = 0; k < 6; ++k) reg[il * kLexStride + k] = w[k];
+    if (kAhead && r + 1 < r1) fetch(r + 1);
+    __syncthreads();
+    cx<double> *orr = out + size_t(r) * stride;
+    if (on0) store(0, o0, ir, orr);
+    if (on1) store(1, o1, ir, orr);
+  }
+}
+
 template <class R, bool A, bool B, bool C, int T, class SI, class SS, class OT>
 void launch_hop_tile(lqcd_ctx *c, Timed &tm, int p, const cx<R> *U, SI in, SS self, void *out,
                      cdouble alpha, double beta, int nrhs, size_t si, size_t ss, size_t so) {
@@ -826,17 +1010,43 @@ void full_legs(lqcd_ctx *c, lqcd_op op, SI in, OT out, int nrhs, size_t sin, siz
   }
 }
 
-// wilson_apply on lexicographic fields in the leg-split form: the layout is
-// read and written in place.
+// A full-lattice operator on lexicographic fields, k_hop_lex.
 template <class R>
-void wilson_lex_legs(lqcd_ctx *c, lqcd_op op, const void *in, void *out, int nrhs) {
+void full_lex(lqcd_ctx *c, lqcd_op op, const void *in, void *out, int nrhs) {
+  const Geom &g = c->g;
+  const size_t fl = full_len(g);
+  const cx<R> *U = static_cast<const cx<R> *>(std::is_same<R, double>::value ? c->U64.ptr : c->U32.ptr);
+  const double bytes = double(g.V) * (72.0 * sizeof(cx<R>) + nrhs * 24.0 * sizeof(cx<double>));
+  Timed tm(c, std::is_same<R, double>::value ? LQCD_KC_HOP64 : LQCD_KC_HOP32, bytes);
+  const int ntile = (g.V + kLegSites - 1) / kLegSites;  // right-hand sides per workgroup: as launch_hop_legs
+  const int ngr = std::min(nrhs, std::max(1, 768 / ntile)), rg = (nrhs + ngr - 1) / ngr;
+  const int tb = (g.L[3] + 7) / 8;
+  const int xq = (ntile * ((nrhs + rg - 1) / rg) + 7) / 8;
+  const int nt = double(nrhs) * fl * 16 > 96e6;  // past the caches, as launch_hop_legs
+  const cx<double> *ip = static_cast<const cx<double> *>(in);
+  cx<double> *op_ = static_cast<cx<double> *>(out);
+  const R one = 1, k = R(-c->kappa);
+#define LQCD_LEX(A, B, C, al, be)                                                                                  \
+  LQCD_TLAUNCH(tm, true, true, (k_hop_lex<R, A, B, C>), dim3(8 * xq), dim3(8 * kLegSites), 0, c->stream, g, U, ip, \
+               op_, al, be, fl, nrhs, rg, xq, tb, nt)
+  switch (op) {
+    case LQCD_OP_HOP: LQCD_LEX(false, false, false, R(0), one); break;
+    case LQCD_OP_M: LQCD_LEX(false, false, true, one, k); break;
+    case LQCD_OP_MG5: LQCD_LEX(true, false, true, one, k); break;
+    case LQCD_OP_MDAG: LQCD_LEX(true, true, true, one, k); break;
+    default: LQCD_CHECK(false, LQCD_EINVAL, "full_lex: operator %d is not a full-lattice operator", int(op));
+  }
+#undef LQCD_LEX
+  LQCD_HIP(hipGetLastError());
+}
+
+// The even/odd operator on lexicographic fields in the leg-split form: the
+// layout is read and written in place.
+template <class R>
+void schur_lex_legs(lqcd_ctx *c, const void *in, void *out, int nrhs) {
   const size_t hl = half_len(c->g), fl = full_len(c->g);
   const LegLex<R> src{static_cast<const cx<double> *>(in)};
   const LegOutLex<R> dst{static_cast<cx<double> *>(out)};
-  if (op != LQCD_OP_SCHUR) {
-    full_legs<R>(c, op, src, dst, nrhs, fl, fl, 0);
-    return;
-  }
   const double k = c->kappa;
   // the odd temporary as apply_schur keeps it
   using SrcT = typename std::conditional<std::is_same<R, float>::value, SrcPair, SrcPlain<R>>::type;
@@ -1087,11 +1297,19 @@ void wilson_apply_t(lqcd_ctx *c, lqcd_op op, lqcd_layout layout, const void *in,
     const cdouble *src = static_cast<const cdouble *>(in) + r0 * fl;
     cdouble *dst = static_cast<cdouble *>(out) + r0 * fl;
     LegsForApply legs(c, f64, nb);
-    // in place (16-byte accesses 192 bytes apart) up to half a gigabyte, above
-    // through the library's layout: M in FP64 on 8^4, 16 right-hand sides 29 -> 23
-    // us, 16^3 x 32 648 -> 642, but 24^3 x 32 2288 -> 2388
-    if (use_legs(c) && fl * nb * sizeof(cdouble) <= kLexInPlace) {
-      wilson_lex_legs<R>(c, op, src, dst, nb);
+    // Full operators in place at every size whose components 32 bits can count.
+    // MG5 with pack and unpack, or on small fields in place through 16-byte
+    // accesses 192 bytes apart -> k_hop_lex: FP64 8^4, 16 right-hand sides 22 ->
+    // 17 us, 16^3 x 32, 1: 44 -> 41, 16: 602 -> 390, 24^3 x 32, 16: 2252 -> 1352;
+    // FP32 16^3 x 32, 16: 578 -> 272, 24^3 x 32, 16: 1676 -> 1014.
+    if (use_legs(c) && op != LQCD_OP_SCHUR && c->g.V <= (1 << 28)) {
+      full_lex<R>(c, op, src, dst, nb);
+      continue;
+    }
+    // the even/odd operator in place (16-byte accesses 192 bytes apart) up to
+    // half a gigabyte, above through the library's layout
+    if (use_legs(c) && op == LQCD_OP_SCHUR && fl * nb * sizeof(cdouble) <= kLexInPlace) {
+      schur_lex_legs<R>(c, src, dst, nb);
       continue;
     }
     void *a = c->ws[5].ensure(2 * hl * blk * sizeof(cx<R>));
