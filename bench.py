@@ -90,7 +90,7 @@ def dslash_rates(kt):
         return None
     ms, by, nl = kt["hop32"]
     alg = by / (ms * 1e-3) / 1e9
-    out = {"kernel": "k_hop_tile, FP32 arithmetic (16-bit and FP32 inputs)", "algorithmic_GBps": round(alg, 1),
+    out = {"kernel": "k_hop_legs, FP32 arithmetic (16-bit and FP32 inputs)", "algorithmic_GBps": round(alg, 1),
            "frac": round(alg / HBM_PEAK_GBS, 4), "hbm_GBps": None, "hbm_frac": None, "hbm_over_algorithmic": None}
     p = os.path.join(ROOT, "profiles", "traffic_hop32.json")
     if not os.path.exists(p):
