@@ -59,7 +59,11 @@ __device__ inline cx<double> ld64nt(const cx<R> *p) {
 // Wave-level chunks: each wave owns WEPT * 64 consecutive elements, keeps
 // its slice of w in registers and, for every basis vector, reduces its
 // partial dot product across the wave with shuffles only.  No block-level
-// barrier stalls the loads of the next basis vectors.
+// barrier stalls the loads of the next basis vectors.  Where the chunks alone
+// leave CUs idle (8^4 has 24 workgroups) the basis is split too, blockIdx.z =
+// group of dot_group vectors: each vector's sum is the same, its chain of loads
+// shorter.  MINRES-DR's steps on 8^4 (2 and 46 FP64 vectors in turn) 14.8 -> 6.2
+// us a pass.
 template <class R>
 struct MdotShape {
   static constexpr int EPT = sizeof(R) == 8 ? 8 : 16;  // elements per lane
@@ -69,7 +73,7 @@ struct MdotShape {
 template <class R>
 __global__ void __launch_bounds__(kBlock)
     k_mdot_part(const cx<R> *__restrict__ V, size_t ldv, size_t V_rs, int J,
-                const cx<R> *__restrict__ w, size_t w_rs, size_t n, double *__restrict__ part,
+                const cx<R> *__restrict__ w, size_t w_rs, size_t n, int gs, double *__restrict__ part,
                 const int *__restrict__ flag) {
   constexpr int E = MdotShape<R>::EPT, WC = MdotShape<R>::WCH;
   const int lane = threadIdx.x & 63;
@@ -87,8 +91,9 @@ __global__ void __launch_bounds__(kBlock)
     wv[e] = idx < n ? ld64(w + idx) : mk<double>(0, 0);
   }
   double *po = part + (size_t(r) * nwch + chunk) * size_t(J) * 2;
-  int j = 0;
-  for (; j + 2 <= J; j += 2) {
+  int j = int(blockIdx.z) * gs;
+  const int j1 = min(J, j + gs);
+  for (; j + 2 <= j1; j += 2) {
     double a0 = 0, b0 = 0, a1 = 0, b1 = 0;
     const cx<R> *v0 = V + size_t(j) * ldv, *v1 = v0 + ldv;
 #pragma unroll
@@ -114,7 +119,7 @@ __global__ void __launch_bounds__(kBlock)
       po[2 * j + 3] = b1;
     }
   }
-  if (j < J) {
+  if (j < j1) {
     double a0 = 0, b0 = 0;
     const cx<R> *v0 = V + size_t(j) * ldv;
 #pragma unroll
@@ -1710,9 +1715,10 @@ void multi_dot_impl(lqcd_ctx *c, const void *V, size_t ldv, size_t V_rs, int J, 
   const int nblk = ngrid * kWaves;  // wave chunks = partial sums per rhs and j
   double *part = static_cast<double *>(c->red.ensure(size_t(nrhs) * nblk * J * 2 * sizeof(double)));
   Timed tm(c, cls, bytes);
-  LQCD_TLAUNCH(tm, true, true, (k_mdot_part<R>), dim3(ngrid, nrhs), dim3(kBlock), 0, c->stream,
+  const int gs = dot_group(J, size_t(ngrid) * nrhs);
+  LQCD_TLAUNCH(tm, true, true, (k_mdot_part<R>), dim3(ngrid, nrhs, (J + gs - 1) / gs), dim3(kBlock), 0, c->stream,
                      static_cast<const cx<R> *>(V), ldv, V_rs, J, static_cast<const cx<R> *>(w),
-                     w_rs, n, part, flag);
+                     w_rs, n, gs, part, flag);
   LQCD_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_mdot_final, dim3(J, nrhs), dim3(kBlock), 0, c->stream, part, nblk, J,
                      reinterpret_cast<cx<double> *>(out), out_rs, flag);

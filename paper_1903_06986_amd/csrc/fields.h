@@ -7,6 +7,8 @@
 // writes its partial sums and a second kernel adds them in a fixed order.
 #pragma once
 
+#include <algorithm>
+
 #include "common.h"
 
 namespace lqcd {
@@ -63,6 +65,15 @@ void gemm_nn(lqcd_ctx *c, const void *V, size_t ldv, size_t V_rs, int J, const c
 template <class R>
 void gemm_tn(lqcd_ctx *c, const void *V, size_t ldv, int J, const void *X, size_t ldx, int nb,
              size_t n, cdouble *C, size_t ldc);
+
+// Vectors per workgroup (even) of a dot pass over J basis vectors whose chunks
+// of elements give `blocks` workgroups: all where these fill the 256 CUs four
+// times, else fewer, at least two.
+inline int dot_group(int J, size_t blocks) {
+  const size_t pairs = size_t(J + 1) / 2;
+  const size_t groups = std::min(pairs, std::max<size_t>(1, 1024 / std::max<size_t>(blocks, 1)));
+  return int(2 * ((pairs + groups - 1) / groups));
+}
 
 // Y_v[b] += sum_j V[j] w[v ldw + j] C[j + ldc b], v < nvar <= 4, b < nb <= 16
 // (FP64; V read once for all; device coefficients and weights; where fresh[v] is

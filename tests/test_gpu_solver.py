@@ -418,3 +418,26 @@ def test_finished_right_hand_sides_change_places(zeros, inner):
         else:
             assert rel_err(x[r], xref[r]) < 1e-9, r
             assert st[r]["true_resid"] < 1e-11, r
+
+
+@pytest.mark.parametrize("m,k", [(5, 2), (8, 3), (13, 6), (34, 17)])
+@pytest.mark.parametrize("dims", [(2, 2, 2, 4), (6, 4, 4, 4)])
+def test_dots_split_over_the_basis(dims, m, k):
+    """Single Arnoldi steps on small lattices, whose dot passes split the basis
+    into groups of two or more vectors (1 to 35 of them here: one vector, odd
+    and even counts, ragged last groups): solutions against LU (1e-9) and the
+    true residual, FP64 and FP32 bases, one and three right-hand sides at once."""
+    require_gpu()
+    kappa = 0.12
+    ctx, U = context(dims, 0.3, 1001, kappa)
+    eta = z4_noise(2003, dims, 0, 4).astype(np.complex128)
+    xref, _ = _dense_solve(U, kappa, dims, eta)
+    ctx.tune(arnoldi_steps=1)
+    for inner in ("f64", "f32"):
+        say("dot groups", dims, m, k, inner)
+        x, _, st = ctx.gmresdr_solve(to_gpu(eta), op="schur", m=m, k=k, tol=1e-11, tol_super=1e-12, inner=inner,
+                                     inner_tol=1e-3, rhs_block=3, max_cycles=400)
+        x = to_host(x)
+        for r in range(4):
+            assert rel_err(x[r], xref[r]) < 1e-9, (inner, r)
+            assert st[r]["true_resid"] < 1e-11, (inner, r)
