@@ -50,13 +50,16 @@ constexpr int kSubBlock = 16;
 
 // ---------------------------------------------------------- walk tables
 // The trace tr W_w(x) of a closed walk does not depend on where on its loop
-// the walk starts, a leading step that the last one undoes drops out of it,
-// and the walk run backwards has its complex conjugate.  So the device forms
-// one trace per loop (a cyclically reduced walk, up to rotation and
-// reversal) and site, summed over the sites of each timeslice, and every
-// walk's timeslice sums are a loop's sums shifted by the timeslices between
-// the two starting points: about 16 times fewer link products than one per
-// walk (length 8: 2.3k loops for 36k walks).
+// the walk starts, and the walk run backwards has its complex conjugate.  So
+// the device forms one trace per loop (a walk up to rotation and reversal)
+// and site, summed over the sites of each timeslice, and every walk's
+// timeslice sums are a loop's sums shifted by the timeslices between the two
+// starting points: about 16 times fewer link products than one per walk
+// (length 8: 2.3k loops for 36k walks).  Both hold for any 3x3 matrices; that
+// a step undone later drops out would need U U^+ = 1, which links rounded to
+// FP32 or smeared without a projection do not have, so a walk whose last step
+// undoes its first (length 6: 288 of them, with nonzero g_mu spin traces)
+// keeps all its links, as a loop of its own.
 constexpr int kMaxWalkLen = 8;  // local: length <= 6 (orders <= 7); point-split: <= 8
 
 // Directions are 2 * mu + (0: +mu, 1: -mu); a walk is coded in 3 bits per
@@ -105,17 +108,20 @@ struct Walk {
   cdouble coef[kNumOps];
 };
 
-// The loop of the walk dirs[0..n): the smallest code among the rotations of
-// the walk and of its reverse.  A walk starting at x has the loop's trace at
-// a site dt timeslices from x, conjugated if conj.  n >= 1, no step undone
-// by the next, cyclically.
+// The loop of the walk dirs[0..n), n >= 1: the smallest code among the
+// rotations of the walk and of its reverse.  A walk starting at x has the
+// loop's trace at a site dt timeslices from x, conjugated if conj.  Of the
+// rotations of a walk whose last step undoes its first only the walk itself
+// undoes no step at once, and so of its reverse, which starts with the same
+// step: these two alone are compared.
 Code loop_of(const int *dirs, int n, int &dt, bool &conj) {
   Code best = ~Code(0);
   int r[kMaxWalkLen];
+  const int nrot = dirs[0] == (dirs[n - 1] ^ 1) ? 1 : n;
   for (int o = 0; o < 2; ++o) {
     for (int i = 0; i < n; ++i) r[i] = o ? dirs[n - 1 - i] ^ 1 : dirs[i];
     int tk = 0;
-    for (int k = 0; k < n; ++k) {
+    for (int k = 0; k < nrot; ++k) {
       Code c = 0;
       for (int i = 0; i < n; ++i) c = (c << 3) | Code(r[(k + i) % n]);
       if (c < best) {
@@ -155,20 +161,28 @@ void each_walk(int len, const int L[4], int low, int depth, int disp[4], const S
   }
 }
 
-// The loops of length len in ascending order of their codes (depth-first).
-std::vector<Code> enumerate_loops(int len, const int L[4]) {
+// The loops of length len in ascending order of their codes (depth-first):
+// those whose walks' last step does not undo the first and, if undone is set,
+// those whose walks' does.
+std::vector<Code> enumerate_loops(int len, const int L[4], bool undone) {
   std::vector<Code> loops;
   int disp[4] = {0, 0, 0, 0}, dirs[kMaxWalkLen];
-  // a loop's code starts with a forward step in its lowest direction
+  auto take = [&](const int *w, bool un) {
+    if ((w[0] == (w[len - 1] ^ 1)) != un) return;
+    Code c = 0;
+    for (int i = 0; i < len; ++i) c = (c << 3) | Code(w[i]);
+    int dt;
+    bool conj;
+    if (loop_of(w, len, dt, conj) == c) loops.push_back(c);
+  };
+  // without an undone step a loop's code starts with a forward step in its
+  // lowest direction
   for (int low = 0; low < 8; low += 2)
-    each_walk(len, L, low, 0, disp, kSpinOne, dirs, [&](const int *w, const SpinInt &) {
-      if (w[0] == (w[len - 1] ^ 1)) return;
-      Code c = 0;
-      for (int i = 0; i < len; ++i) c = (c << 3) | Code(w[i]);
-      int dt;
-      bool conj;
-      if (loop_of(w, len, dt, conj) == c) loops.push_back(c);
-    });
+    each_walk(len, L, low, 0, disp, kSpinOne, dirs, [&](const int *w, const SpinInt &) { take(w, false); });
+  if (undone) {
+    each_walk(len, L, -1, 0, disp, kSpinOne, dirs, [&](const int *w, const SpinInt &) { take(w, true); });
+    std::sort(loops.begin(), loops.end());
+  }
   return loops;
 }
 
@@ -535,27 +549,18 @@ void ensure_walk_traces(lqcd_ctx *c, bool need_len8) {
   if (!c->have_walk_traces) {
     // odd walks cannot close on even extents; a walk of length len gives the
     // local rows of order len and the point-split rows of order len - 1
-    std::vector<Code> loops[kMaxWalkLen + 1];
-    std::vector<cdouble> tr[kMaxWalkLen + 1];
     for (int len = 2; len <= kMaxWalkLen - 2; len += 2) {
-      loops[len] = enumerate_loops(len, g.L);
-      if (!loops[len].empty()) tr[len] = loop_traces(c, loops[len], len);
+      const std::vector<Code> loops = enumerate_loops(len, g.L, true);
+      if (loops.empty()) continue;
+      const std::vector<cdouble> tr = loop_traces(c, loops, len);
       int disp[4] = {0, 0, 0, 0}, dirs[kMaxWalkLen];
       each_walk(len, g.L, -1, 0, disp, kSpinOne, dirs, [&](const int *d, const SpinInt &S) {
         Walk w{};
         for (int th = 0; th < kNumTheta; ++th) w.coef[th] = spin_trace(th, S);
         point_split(w, d[0], w.coef[0]);
-        // steps at the start that the end undoes
-        int a = 0, dt0 = 0, dt = 0;
-        while (d[a] == (d[len - 1 - a] ^ 1)) {
-          if ((d[a] >> 1) == 3) dt0 += (d[a] & 1) ? -1 : 1;
-          ++a;
-        }
-        const int n = len - 2 * a;
-        const Code code = loop_of(d + a, n, dt, w.conj);
-        w.loop = int(std::lower_bound(loops[n].begin(), loops[n].end(), code) - loops[n].begin());
-        w.dt = dt0 + dt;
-        add(len, w, &tr[n][size_t(w.loop) * Lt]);
+        const Code code = loop_of(d, len, w.dt, w.conj);
+        w.loop = int(std::lower_bound(loops.begin(), loops.end(), code) - loops.begin());
+        add(len, w, &tr[size_t(w.loop) * Lt]);
       });
     }
   }
@@ -564,7 +569,7 @@ void ensure_walk_traces(lqcd_ctx *c, bool need_len8) {
     // of a loop, the conjugate for its reverse and zero for a walk with a
     // first step that its last one undoes
     const int len = kMaxWalkLen;
-    const std::vector<Code> loops = enumerate_loops(len, g.L);
+    const std::vector<Code> loops = enumerate_loops(len, g.L, false);
     const std::vector<cdouble> tr = loops.empty() ? std::vector<cdouble>() : loop_traces(c, loops, len);
     for (size_t l = 0; l < loops.size(); ++l) {
       Code seen[2 * kMaxWalkLen];

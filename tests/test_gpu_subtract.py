@@ -248,3 +248,36 @@ def test_trace_corrections_double_with_a_periodic_copy(dims):
     for op in ops:
         scale = max(np.abs(a[op]).max(), 1e-4 * np.abs(a).max())  # some rows cancel to nothing
         assert np.abs(b[op] - 2 * a[op]).max() <= 1e-12 * 2 * scale, op
+
+
+@pytest.mark.parametrize("dims", [(4, 4, 2, 4), (2, 2, 2, 4), (2, 4, 2, 6)])
+@pytest.mark.parametrize("links", ["perturbed", "float32"])
+def test_trace_corrections_of_links_that_are_not_unitary(dims, links):
+    """The corrections are the traces of the operator as its links are, also
+    where U U^+ is not 1: links off by 5 %, and rounded to FP32 (a walk whose
+    last step undoes its first keeps both links).  Dense traces, orders 6 and 7
+    of PS and a polynomial, all nine operators, at 1e-10 as for unitary links;
+    without those links' U U^+ the vector currents are off by 5 % and 1e-8."""
+    require_gpu()
+    from oracle import pointsplit as PSO
+    from paper_1903_06986_amd import Context
+    from synth import random_su3_links
+    kappa = 0.12
+    U = random_su3_links(dims, 0.3, 77)
+    rng = np.random.default_rng(4)
+    if links == "perturbed":
+        U = U + 0.05 * (rng.standard_normal(U.shape) + 1j * rng.standard_normal(U.shape))
+    else:
+        U = U.astype(np.complex64).astype(np.complex128)
+    ctx = Context(dims, U, kappa)
+    Pd = W.dense_P(U, dims)
+    for order in (6, 7):
+        c = rng.standard_normal(order + 1) + 1j * rng.standard_normal(order + 1)
+        for coeffs in (S.pert_coeffs(order), c):
+            say("trace corrections of non-unitary links", dims, links, order)
+            _, corr, _, _ = ctx.poly_subtract(order, ctx.empty(0), coeffs=coeffs, thetas=range(9))
+            A = S.poly_dense(Pd, kappa, coeffs)
+            ref = np.concatenate([S.trace_correction_dense(A, dims, THETAS),
+                                  np.stack([PSO.trace_ps_dense(U, kappa, dims, mu, A) for mu in range(4)])])
+            for op in range(9):
+                assert np.abs(corr[op] - ref[op]).max() < 1e-10 * np.abs(ref[1:]).max(), (order, op)
