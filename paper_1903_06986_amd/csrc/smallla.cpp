@@ -364,6 +364,25 @@ void eigh(const Mat &A0, std::vector<double> &w, Mat &Vr) {
   Vr = V2;
 }
 
+std::vector<int> pair_conjugates(std::vector<cd> &w) {
+  const int n = int(w.size());
+  auto real = [&](int i) { return std::abs(w[i].imag()) <= 1e-12 * std::abs(w[i]); };
+  for (int i = 0; i < n; ++i)
+    for (int j = i + 1; j < n; ++j)
+      if (!real(i) && !real(j) && std::abs(w[i] - std::conj(w[j])) <= 1e-13 * std::abs(w[i])) {
+        w[i] = 0.5 * (w[i] + std::conj(w[j]));
+        w[j] = std::conj(w[i]);
+      }
+  std::vector<int> partner(n);
+  for (int j = 0; j < n; ++j) {
+    partner[j] = j;
+    if (real(j)) continue;
+    for (int i = 0; i < n; ++i)
+      if (std::abs(w[i] - std::conj(w[j])) < std::abs(w[partner[j]] - std::conj(w[j]))) partner[j] = i;
+  }
+  return partner;
+}
+
 bool cholesky_inv(const Mat &A, Mat &Li) {
   const int n = A.rows;
   Mat L(n, n);

@@ -58,6 +58,14 @@ bool eig(const Mat &A, std::vector<cd> &w, Mat &Vr);
 // ascending, orthonormal eigenvectors in the columns of Vr.
 void eigh(const Mat &A, std::vector<double> &w, Mat &Vr);
 
+// The conjugate partner of every entry of a spectrum that is closed under
+// conjugation up to rounding: the entry nearest to its conjugate, itself where
+// none is nearer.  A converged pair (imaginary parts above 1e-12 of the
+// modulus, equal to 1e-13 after conjugation) is made exactly conjugate, so that
+// the order of a sorted list does not hang on last digits; real entries stay as
+// they are and are their own partners, also where two of them are equal.
+std::vector<int> pair_conjugates(std::vector<cd> &w);
+
 // Li = L^{-1} for the Cholesky factor L L^H = A of a hermitian positive
 // definite A (lower triangular); false if A is not positive definite.
 bool cholesky_inv(const Mat &A, Mat &Li);

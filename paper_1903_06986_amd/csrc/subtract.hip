@@ -776,15 +776,8 @@ void es_pairs(lqcd_ctx *c, lqcd_defl *d, int Q) {
   std::vector<cdouble> lh;
   la::Mat Sr;
   LQCD_CHECK(la::eig(T, lh, Sr), LQCD_ENOCONV, "eigenvalue subtraction: Ritz eigenproblem did not converge");
-  // Mhat's eigenvalues come in conjugate pairs (g5-hermiticity): a converged
-  // pair's two values, equal to rounding, are made exactly conjugate, so that
-  // the order of the eigenvalues does not hang on their last digits
-  for (int i = 0; i < k; ++i)
-    for (int j = i + 1; j < k; ++j)
-      if (std::abs(lh[i] - std::conj(lh[j])) <= 1e-13 * std::abs(lh[i])) {
-        lh[i] = 0.5 * (lh[i] + std::conj(lh[j]));
-        lh[j] = std::conj(lh[i]);
-      }
+  // Mhat's eigenvalues are real or come in conjugate pairs (g5-hermiticity)
+  const std::vector<int> partner = la::pair_conjugates(lh);
   std::vector<cdouble> lam(k);
   for (int i = 0; i < k; ++i) lam[i] = 1.0 - std::sqrt(1.0 - lh[i]);
   std::vector<int> ord(k);
@@ -794,9 +787,7 @@ void es_pairs(lqcd_ctx *c, lqcd_defl *d, int Q) {
   d->es_lam.resize(Q);
   for (int q = 0; q < Q; ++q) {
     const int j = ord[q];
-    int pj = 0;
-    for (int i = 1; i < k; ++i)
-      if (std::abs(lh[i] - std::conj(lh[j])) < std::abs(lh[pj] - std::conj(lh[j]))) pj = i;
+    const int pj = partner[j];
     d->es_lam[q] = lam[j];
     for (int i = 0; i < k; ++i) {
       SR(i, q) = Sr(i, j);
