@@ -387,11 +387,13 @@ lqcd_status lqcd_batch_destroy(lqcd_batch *batch);
 /* Workgroups of the persistent batched stencil launch (default 8192). */
 lqcd_status lqcd_batch_set_grid(lqcd_batch *batch, int workgroups);
 /* Form of the batched stencil: 0 (default) = one persistent launch over the
- * slot table (every slot reads its own links); 16, 32 or 64 = the
- * link-tiled stencil with tiles of that many sites, one launch per run of
- * consecutive slots that hold one lattice (its links staged once per tile
- * for all of them; the captured cycle is recorded again when a refill of
- * the slots changes these runs).  EINVAL for other values. */
+ * slot table (every slot reads its own links); 16, 32 or 64 = one launch of
+ * the single-lattice stencil per run of consecutive slots that hold one
+ * lattice (its links loaded once for all of them; the captured cycle is
+ * recorded again when a refill of the slots changes these runs).  The three
+ * values are one form unless a context takes the link-tiled stencil
+ * (LQCD_TUNE_HOP_LEGS), whose tiles then have that many sites.  EINVAL for
+ * other values. */
 lqcd_status lqcd_batch_set_tile(lqcd_batch *batch, int tile_sites);
 
 /* Deflated GMRES-Proj solves (Sec. 7) of every lattice's right-hand sides
@@ -399,8 +401,8 @@ lqcd_status lqcd_batch_set_tile(lqcd_batch *batch, int tile_sites);
  * LQCD_F32), all lattices in lockstep: right-hand sides are taken
  * params->rhs_block at a time from one queue over the lattices (uneven
  * counts and sizes mix in a block); each inner operator application is
- * one persistent launch over all of them or one link-tiled launch per
- * lattice among them (lqcd_batch_set_tile), the Gram-Schmidt and
+ * one persistent launch over all of them or one launch per lattice
+ * among them (lqcd_batch_set_tile), the Gram-Schmidt and
  * projection kernels are batched over all of them, and with use_graph != 0
  * each GMRES(m - k) cycle (or proj_m) runs as a captured hipGraph.  b[l], x[l]: device
  * complex128 LEX [nrhs[l]][12 V_l]; defl[l]: deflation space of lattice l's
@@ -414,8 +416,10 @@ lqcd_status batch_solve(lqcd_batch *batch, const lqcd_solve_params *params, cons
 /* Autotuner: times trial batch_solve runs (captured cycles) for rhs_block
  * in {4, 8, 16, 32} and the stencil forms of lqcd_batch_set_tile {0, 16,
  * 32, 64}, each on one block of right-hand sides drawn evenly from the
- * lattices, and returns the fastest pair (best_tile as for
- * lqcd_batch_set_tile).  rate_host: optional host double [16] receiving
+ * lattices and after an untimed run of that block size, and returns the
+ * fastest pair (best_tile as for lqcd_batch_set_tile).  Where 16, 32 and 64
+ * are one form it is timed once for all three, and 16 returned for it.
+ * rate_host: optional host double [16] receiving
  * the trial rates (right-hand sides per second, order: rhs_block major,
  * tile minor; 0 for skipped pairs).  The batch's tile setting is left
  * unchanged. */

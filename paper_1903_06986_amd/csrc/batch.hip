@@ -510,7 +510,7 @@ struct lqcd_batch {
   hipGraphExec_t exec = nullptr;
   hipGraph_t graph = nullptr;
   int hop_grid = 8192;  // persistent stencil workgroups per launch (tunable)
-  int tile = 0;         // 0: one persistent slot-table stencil launch; 16/32/64: link tiles per lattice group
+  int tile = 0;         // 0: one persistent slot-table stencil launch; 16/32/64: one launch per lattice group
   // Capture needs a stream other than the legacy null stream; the graph
   // is recorded on this private one (default priority) and launched on
   // the contexts' stream.
@@ -538,8 +538,7 @@ inline unsigned grid_n(size_t n) { return unsigned(std::min<size_t>((n + kBlock 
 
 // A run of consecutive slots that hold right-hand sides of one lattice:
 // their vectors lie at one stride from each other, so the single-lattice
-// link-tiled stencil serves them in one launch (links staged once per tile
-// for all of them).
+// stencil serves them in one launch (links loaded once for all of them).
 struct Group {
   lqcd_ctx *c;
   int s0, G;
@@ -561,8 +560,9 @@ std::vector<Group> lattice_groups(const std::vector<lqcd_ctx *> &ctx, const std:
 }
 
 // Launches of a context's stencil on the batch's current stream (the
-// capture stream while a cycle is being recorded) with the batch's tile
-// size and the context's event timer off; restored on exit.
+// capture stream while a cycle is being recorded) with the batch's tile size
+// (read by the link-tiled form only) and the context's event timer off;
+// restored on exit.
 struct OnBatchStream {
   lqcd_ctx *c;
   hipStream_t keep;
@@ -583,10 +583,10 @@ struct OnBatchStream {
 
 // Device work of the batched inner solve, shared by the eager and the
 // captured paths.  B slots, basis length p, longest vector nmax.  The
-// stencil is one persistent launch over the slot table (tile == 0) or,
-// with link tiles, one launch of the link-tiled stencil per lattice group
-// (its groups are fixed while a block of slots is in flight; inactive
-// slots of a group are computed and ignored).
+// stencil is one persistent launch over the slot table (tile == 0) or one
+// launch of the single-lattice stencil per lattice group (the groups are
+// fixed while a block of slots is in flight; inactive slots of a group are
+// computed and ignored).
 struct Engine {
   lqcd_batch *b;
   int B, p;
@@ -763,7 +763,7 @@ void run_batch(lqcd_batch *b, const lqcd_solve_params &prm, const void *const *b
     }
   }
   // the captured inner cycle (kernel arguments are the fixed buffers
-  // above; with link tiles also the lattice groups of the block in flight,
+  // above; with launches per lattice also the lattice groups of the block in flight,
   // so it is recorded again whenever a refill changes them)
   struct GraphGuard {
     hipGraph_t g = nullptr;
@@ -1126,6 +1126,10 @@ extern "C" lqcd_status batch_autotune(lqcd_batch *b, const lqcd_solve_params *pa
       if (nrhs[l] > 0) xp[l] = xs[l].ensure(size_t(nrhs[l]) * full_len(b->ctx[l]->g) * sizeof(cdouble));
     const int blocks[kTuneBlocks] = {4, 8, 16, 32};
     const int tiles[kTuneTiles] = {0, 16, 32, 64};
+    // contexts on the leg-split stencil have one form per lattice, whatever
+    // the tile size: it is timed once for all sizes
+    bool sizes = false;
+    for (const lqcd_ctx *c : b->ctx) sizes = sizes || !use_legs(c);
     const int keep_tile = b->tile;
     struct Restore {
       lqcd_batch *b;
@@ -1134,32 +1138,36 @@ extern "C" lqcd_status batch_autotune(lqcd_batch *b, const lqcd_solve_params *pa
     } restore{b, keep_tile};
     double best = -1;
     int bi = 0;
-    for (int ib = 0; ib < kTuneBlocks; ++ib)
+    for (int ib = 0; ib < kTuneBlocks; ++ib) {
+      // a trial solves one block of right-hand sides, taken evenly from the lattices
+      std::vector<int> nt(nl, 0);
+      const int ns = std::min(blocks[ib], total);
+      for (int left = ns; left > 0;)
+        for (int l = 0; l < nl && left > 0; ++l)
+          if (nt[l] < nrhs[l]) {
+            ++nt[l];
+            --left;
+          }
+      lqcd_solve_params pr = *params;
+      pr.rhs_block = blocks[ib];
+      auto trial = [&](int tile) {
+        b->tile = tile;
+        int nonconv = 0;
+        LQCD_HIP(hipStreamSynchronize(b->stream));
+        const auto t0 = std::chrono::steady_clock::now();
+        run_batch(b, pr, bvec, xp.data(), nt.data(), defl, true, nullptr, &nonconv);
+        LQCD_HIP(hipStreamSynchronize(b->stream));
+        return ns / std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+      };
+      const bool fits = blocks[ib] <= std::max(4, total);
+      // the first run of a block size pays for the buffers' growth (8 lattices
+      // of 8^4, 4 right-hand sides each, block 32: 2156 solves/s against 2615 of
+      // the next run), which must not count against the form that comes first
+      if (fits) (void)trial(tiles[0]);
+      double rate = 0;
       for (int it = 0; it < kTuneTiles; ++it) {
-        double rate = 0;
-        if (blocks[ib] <= std::max(4, total)) {
-          // a trial solves one block of right-hand sides, taken evenly from the lattices
-          std::vector<int> nt(nl, 0);
-          int left = std::min(blocks[ib], total);
-          while (left > 0)
-            for (int l = 0; l < nl && left > 0; ++l)
-              if (nt[l] < nrhs[l]) {
-                ++nt[l];
-                --left;
-              }
-          lqcd_solve_params pr = *params;
-          pr.rhs_block = blocks[ib];
-          b->tile = tiles[it];
-          int nonconv = 0;
-          LQCD_HIP(hipStreamSynchronize(b->stream));
-          const auto t0 = std::chrono::steady_clock::now();
-          run_batch(b, pr, bvec, xp.data(), nt.data(), defl, true, nullptr, &nonconv);
-          LQCD_HIP(hipStreamSynchronize(b->stream));
-          const double dt = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
-          int ns = 0;
-          for (int v : nt) ns += v;
-          rate = ns / dt;
-        }
+        if (!fits) rate = 0;
+        else if (it < 2 || sizes) rate = trial(tiles[it]);
         if (rate_host) rate_host[bi] = rate;
         ++bi;
         if (rate > best) {
@@ -1168,6 +1176,7 @@ extern "C" lqcd_status batch_autotune(lqcd_batch *b, const lqcd_solve_params *pa
           *best_tile = tiles[it];
         }
       }
+    }
   });
 }
 

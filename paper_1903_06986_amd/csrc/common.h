@@ -170,6 +170,13 @@ inline size_t half_len(const Geom &g) { return size_t(12) * g.Vh; }
 inline size_t full_len(const Geom &g) { return size_t(12) * g.V; }
 
 // dslash.hip ------------------------------------------------------------
+// Whether the context's stencil launches take the leg-split form: by default
+// unless a launch shape of the other forms was set, and while a field's 16-byte
+// granules can be addressed by 32-bit offsets.
+inline bool use_legs(const lqcd_ctx *c) {
+  if (double(c->g.Vh) * 16.0 >= 4294967295.0) return false;
+  return c->hop_legs >= 0 ? c->hop_legs != 0 : !c->hop_shaped;
+}
 // Generic stencil on even/odd fields of real type R (double or float):
 //   out_p = G_out( alpha * G_in(self_p) + beta * D_{p,1-p} G_in(in_{1-p}) )
 // for output parity p (out, self, in are half fields of Vh sites, in of the

@@ -857,14 +857,6 @@ struct SrcBytes<SrcHalf<K>> {
   static constexpr double v = 52.0;
 };
 
-// Whether a launch takes the leg-split form: by default unless a launch shape
-// of the other forms was set, and while a field's 16-byte granules can be
-// addressed by 32-bit offsets.
-bool use_legs(const lqcd_ctx *c) {
-  if (double(c->g.Vh) * 16.0 >= 4294967295.0) return false;
-  return c->hop_legs >= 0 ? c->hop_legs != 0 : !c->hop_shaped;
-}
-
 template <class OT>
 struct LegOut;
 template <class R>

@@ -551,7 +551,8 @@ class Batch:
 
     def set_tile(self, tile_sites):
         """Batched stencil form: 0 = persistent slot-table launch, 16/32/64 =
-        link tiles of that many sites per lattice group."""
+        one launch per lattice group (with link tiles of that many sites on
+        contexts whose leg-split stencil is off)."""
         _check(lib().lqcd_batch_set_tile(self.handle, int(tile_sites)))
 
     def wilson_apply(self, xs):

@@ -110,3 +110,49 @@ def test_batch_autotune():
     assert all(v > 0 for (b, t), v in table.items() if b <= 12)
     with pytest.raises(Exception):
         batch.set_tile(24)
+
+
+def test_autotune_times_each_form_once():
+    """Tile sizes 16, 32 and 64 are one form on contexts that take the leg-split
+    stencil: one trial, the same rate for all three, and the first of them
+    named if it wins.  On contexts that do not, each size is timed by itself."""
+    require_gpu()
+    from paper_1903_06986_amd import Batch
+    ctxs, Us, defls, etas = _setup(LATS)
+    batch = Batch(ctxs)
+    say("batch autotune, leg-split")
+    blk, tile, table = batch.autotune([to_gpu(e) for e in etas], defls, tol=1e-10)
+    assert all(table[(b, 16)] == table[(b, 32)] == table[(b, 64)] for b in Batch.TUNE_BLOCKS)
+    assert tile in (0, 16) and table[(blk, tile)] == max(table.values())
+    for ctx in ctxs:
+        ctx.tune(hop_legs=0)
+    say("batch autotune, link tiles")
+    blk, tile, table = batch.autotune([to_gpu(e) for e in etas], defls, tol=1e-10)
+    assert any(len({table[(b, t)] for t in (16, 32, 64)}) == 3 for b in Batch.TUNE_BLOCKS)
+    assert table[(blk, tile)] == max(table.values())
+
+
+@pytest.mark.parametrize("tile", [16, 32, 64])
+def test_batch_link_tiles_equal_the_leg_split_form(tile):
+    """One launch per lattice, on contexts with the leg-split stencil off (link
+    tiles of the given size) and on: the same FP32 sums in the same order, so
+    the same bits, for lattices of four and more right-hand sides (partial,
+    ragged and whole tiles of each size)."""
+    require_gpu()
+    from paper_1903_06986_amd import Batch
+    lats = [((2, 2, 2, 4), 0.12, 4, 1001), ((6, 4, 2, 8), 0.13, 5, 1002), ((8, 4, 4, 8), 0.125, 7, 1003)]
+    rng = np.random.default_rng(9)
+    ctxs, xs = [], []
+    for dims, kappa, nr, seed in lats:
+        ctxs.append(context(dims, 0.3, seed, kappa)[0])
+        xs.append(to_gpu(rng.standard_normal((nr,) + ctxs[-1].shape) + 1j * rng.standard_normal((nr,) + ctxs[-1].shape)))
+    batch = Batch(ctxs)
+    batch.set_tile(tile)
+    out = {}
+    for legs in (0, -1):
+        for ctx in ctxs:
+            ctx.tune(hop_legs=legs)
+        say("batch stencil per lattice, tile", tile, "legs", legs)
+        out[legs] = [to_host(y) for y in batch.wilson_apply(xs)]
+    for a, b in zip(out[0], out[-1]):
+        assert np.array_equal(a, b)
