@@ -1219,7 +1219,8 @@ __global__ void __launch_bounds__(kBlock)
 // right-hand sides whose flag is clear): out slot m (out + r out_rs + m
 // out_vs) = sum_{l <= m} F[l][m] y_l, F = f[r][S][S]; w is not written.  Else
 // (flag set): w_k = y_k in place, with the per-workgroup Gram partials of the
-// stored y_k in part (or not).
+// stored y_k in part (or not).  out may be w: a lane holds its elements of all
+// S vectors before it stores.
 template <class R, int S, int U, bool DIRECT>
 __global__ void __launch_bounds__(kBlock)
     k_maxpys(const cx<R> *__restrict__ V, size_t ldv, size_t V_rs, int J, const cx<double> *__restrict__ coef,
@@ -1310,10 +1311,10 @@ __global__ void __launch_bounds__(kBlock)
 }
 
 // Slot m = sum_{l <= m} F[l][m] w_l for the right-hand sides whose flag is
-// set (the explicit path's store).
+// set (the explicit path's store; out may be w).
 template <class R, int S>
 __global__ void __launch_bounds__(kBlock)
-    k_sstore(const cx<R> *__restrict__ w, size_t w_vs, size_t w_rs, const cx<double> *__restrict__ f, cx<R> *out,
+    k_sstore(const cx<R> *w, size_t w_vs, size_t w_rs, const cx<double> *__restrict__ f, cx<R> *out,
              size_t out_vs, size_t out_rs, size_t n, const int *__restrict__ flag) {
   const int r = blockIdx.y;
   if (flag[r] == 0) return;

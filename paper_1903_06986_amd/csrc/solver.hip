@@ -693,7 +693,10 @@ void arnoldi_hs(lqcd_ctx *c, const Op<float> &A, void *W, size_t n, size_t ldv, 
 
 // The s-step form on a plain basis of precision R (FP64 or FP32; even/odd
 // operator): as sstep_block, the powers and the basis both held in R, every
-// sum in FP64.  S <= 4: the update holds S vectors' elements in FP64 registers.
+// sum in FP64.  The powers z_1 .. z_S take the places of v_{j+1} .. v_{j+S},
+// which the update stores over them (a lane reads its elements of all S before
+// it writes any), so a block needs no vectors beside the basis.  S <= 4: the
+// update holds S vectors' elements in FP64 registers.
 // The one-step form reads the basis twice per step (half of the time of an
 // FP64 solve) and takes ten launches per step beside the operator's two, this
 // one 14 per block.  Ten FP64 solves on 16^3 x 32: 55.9 -> 34.2 ms, 32 on
@@ -701,7 +704,7 @@ void arnoldi_hs(lqcd_ctx *c, const Op<float> &A, void *W, size_t n, size_t ldv, 
 // 15.7 -> 8.2 ms; same matrix-vector products.
 template <class R, int S>
 void sstep_block_plain(lqcd_ctx *c, const Op<R> &A, cx<R> *Wb, size_t n, size_t Wrs, int j, int m, int nb, Small &s,
-                       double eta2, cx<R> *wt) {
+                       double eta2) {
   constexpr double kSigma = 1.0;
   constexpr int NG = S * S;
   const size_t ldc = size_t(S) * (m + 1);
@@ -714,13 +717,11 @@ void sstep_block_plain(lqcd_ctx *c, const Op<R> &A, cx<R> *Wb, size_t n, size_t 
   double *G = reinterpret_cast<double *>(f + size_t(NG) * nb), *part = G + size_t(NG) * nb;
   double *gpart = part + size_t(nb) * nblk * NG;
   double *dpart = static_cast<double *>(c->red.ensure(size_t(nb) * nblk * 2 * S * J * sizeof(double)));
-  const size_t wvs = size_t(nb) * n;  // vector k of the block, right-hand side r at wt + k wvs + r n
-  cx<R> *out = Wb + size_t(J) * n;
+  cx<R> *z = Wb + size_t(J) * n;  // vector k of the block, right-hand side r at z + k n + r Wrs
   const cx<double> *C1d = reinterpret_cast<const cx<double> *>(C1), *C2d = reinterpret_cast<const cx<double> *>(C2);
   cx<double> *Hd = reinterpret_cast<cx<double> *>(s.Hd), *fd = reinterpret_cast<cx<double> *>(f);
-  A.apply_dd_plain(Wb + size_t(j) * n, Wrs, wt, n, nb);
-  for (int k = 1; k < S; ++k) A.apply_dd_plain(wt + (k - 1) * wvs, n, wt + k * wvs, n, nb);
-  multi_dots_part<R, S>(c, Wb, n, Wrs, J, wt, wvs, n, n, nb, dpart, gpart, nullptr);
+  for (int k = 0; k < S; ++k) A.apply_dd_plain(Wb + size_t(j + k) * n, Wrs, z + size_t(k) * n, Wrs, nb);
+  multi_dots_part<R, S>(c, Wb, n, Wrs, J, z, n, Wrs, n, nb, dpart, gpart, nullptr);
   if (nblk <= kMidBlocks) {
     hipLaunchKernelGGL(k_sstep_mid<S>, dim3(nb), dim3(kBlock), 0, c->stream, dpart, gpart, nblk,
                        reinterpret_cast<cx<double> *>(C1), ldc, G, s.flag, s.reorth, eta2, Hd, s.Hrs, m + 1, j,
@@ -734,32 +735,32 @@ void sstep_block_plain(lqcd_ctx *c, const Op<R> &A, cx<R> *Wb, size_t n, size_t 
                        ldc, part, nblk, G, s.flag, kSigma, fd);
   }
   LQCD_HIP(hipGetLastError());
-  multi_axpys_store<R, S>(c, Wb, n, Wrs, J, C1, ldc, wt, wvs, n, n, nb, s.flag, f, out, n, Wrs);
+  multi_axpys_store<R, S>(c, Wb, n, Wrs, J, C1, ldc, z, n, Wrs, n, nb, s.flag, f, z, n, Wrs);
   // explicit path (flagged right-hand sides)
-  multi_axpys<R, S>(c, Wb, n, Wrs, J, C1, ldc, wt, wvs, n, n, nb, nullptr, s.flag);
-  multi_dots_part<R, S>(c, Wb, n, Wrs, J, wt, wvs, n, n, nb, dpart, nullptr, s.flag);
+  multi_axpys<R, S>(c, Wb, n, Wrs, J, C1, ldc, z, n, Wrs, n, nb, nullptr, s.flag);
+  multi_dots_part<R, S>(c, Wb, n, Wrs, J, z, n, Wrs, n, nb, dpart, nullptr, s.flag);
   sum_dots(c, dpart, nblk, S * J, nb, C2, ldc, s.flag);
-  multi_axpys<R, S>(c, Wb, n, Wrs, J, C2, ldc, wt, wvs, n, n, nb, part, s.flag);
+  multi_axpys<R, S>(c, Wb, n, Wrs, J, C2, ldc, z, n, Wrs, n, nb, part, s.flag);
   hipLaunchKernelGGL((k_sstep_finish<S, true>), dim3(nb), dim3(64), 0, c->stream, Hd, s.Hrs, m + 1, j, C1d, C2d, ldc,
                      part, nblk, G, s.flag, kSigma, fd);
   LQCD_HIP(hipGetLastError());
-  sstore<R, S>(c, wt, wvs, n, f, out, n, Wrs, n, nb, s.flag);
+  sstore<R, S>(c, z, n, Wrs, f, z, n, Wrs, n, nb, s.flag);
 }
 
 constexpr int kMaxPlainSteps = 4;
 
 template <class R>
 void arnoldi_s(lqcd_ctx *c, const Op<R> &A, void *W, size_t n, size_t Wrs, int m, int nb, Small &s, double eta2,
-               void *wt, int steps) {
-  cx<R> *Wb = static_cast<cx<R> *>(W), *w = static_cast<cx<R> *>(wt);
+               int steps) {
+  cx<R> *Wb = static_cast<cx<R> *>(W);
   for (int j = 0; j < m;) {
     const int b = std::min(steps, m - j);
     if (b == 4)
-      sstep_block_plain<R, 4>(c, A, Wb, n, Wrs, j, m, nb, s, eta2, w);
+      sstep_block_plain<R, 4>(c, A, Wb, n, Wrs, j, m, nb, s, eta2);
     else if (b == 3)
-      sstep_block_plain<R, 3>(c, A, Wb, n, Wrs, j, m, nb, s, eta2, w);
+      sstep_block_plain<R, 3>(c, A, Wb, n, Wrs, j, m, nb, s, eta2);
     else if (b == 2)
-      sstep_block_plain<R, 2>(c, A, Wb, n, Wrs, j, m, nb, s, eta2, w);
+      sstep_block_plain<R, 2>(c, A, Wb, n, Wrs, j, m, nb, s, eta2);
     else
       arnoldi<R>(c, A, W, n, Wrs, j, m, nb, s, eta2);  // the one step left
     j += b;
@@ -1079,14 +1080,14 @@ bool gmres_dr(lqcd_ctx *c, const Op<double> &A, const void *S, void *X, const lq
 // cycle_cap cycles of this call, or when a cycle leaves the residual above
 // `stall` times the previous one: it only has to shrink the residual.
 // BK >= 0 (R = float only): the GMRES(p) basis W is stored in 16 bits
-// (half.h kind BK).  wt is scratch of nb vectors of precision R per Arnoldi
-// step of a block (null, plain bases only: one step at a time).
+// (half.h kind BK) and wt is FP32 scratch of nb vectors per Arnoldi step of a
+// block.  Plain bases take `steps` Arnoldi steps per block.
 template <class R, int BK = -1>
 void proj_solve(lqcd_ctx *c, const Op<R> &A, const void *Vdef, const lqcd_defl *d, int p, void *S,
                 void *X, void *Rr, void *W, int nb, std::vector<double> ref, double tol,
                 int max_cycles, std::vector<int> &matvecs, std::vector<int> &cycles,
                 std::vector<double> &resid, std::vector<int> &reorth, int cycle_cap = 0,
-                double stall = 0.0, void *wt = nullptr) {
+                double stall = 0.0, void *wt = nullptr, int steps = 1) {
   static_assert(BK < 0 || std::is_same<R, float>::value, "16-bit bases hold FP32 solves");
   const size_t n = A.n;
   const int k = d->k;
@@ -1186,8 +1187,8 @@ void proj_solve(lqcd_ctx *c, const Op<R> &A, const void *Vdef, const lqcd_defl *
     } else {
       axpby<R>(c, sc.data(), Rb, n, zs.data(), W, Wrs, n, na, true);
       const double eta2 = c->cycle_reorth ? kReorthAlways : kReorthCycle;
-      if (wt)
-        arnoldi_s<R>(c, A, W, n, Wrs, p, na, s, eta2, wt, std::min(c->arnoldi_steps, kMaxPlainSteps));
+      if (steps > 1)
+        arnoldi_s<R>(c, A, W, n, Wrs, p, na, s, eta2, steps);
       else
         arnoldi<R>(c, A, W, n, Wrs, 0, p, na, s, eta2);
     }
@@ -1415,9 +1416,8 @@ extern "C" lqcd_status gmresdr_solve(lqcd_ctx *c, lqcd_op op, const lqcd_solve_p
       void *Rr = w.R.ensure(n * nb * sizeof(cx<double>));
       if (p.inner == LQCD_F64) {
         void *W = w.W.ensure(size_t(p_cyc + 1) * n * nb * sizeof(cx<double>));
-        void *WT = ps > 1 ? w.WT.ensure(n * nb * sizeof(cx<double>) * size_t(ps)) : nullptr;
         proj_solve<double>(c, A64, d->V.ptr, d, p_cyc, w.S.ptr, X, Rr, W, nb, ref, p.tol,
-                           p.max_cycles, mv, cy, res, ro, 0, 0.0, WT);
+                           p.max_cycles, mv, cy, res, ro, 0, 0.0, nullptr, ps);
       } else {
         // FP64 refinement around FP32 deflated inner solves
         {
@@ -1435,10 +1435,9 @@ extern "C" lqcd_status gmresdr_solve(lqcd_ctx *c, lqcd_op op, const lqcd_solve_p
         const bool h16 = p.inner == LQCD_F16 || p.inner == LQCD_BF16;
         void *W32 = h16 ? w.W32.ensure(size_t(p_cyc + 1) * hvec_words(n / 12) * nb * sizeof(uint32_t))
                         : w.W32.ensure(size_t(p_cyc + 1) * n * nb * sizeof(cx<float>));
-        // FP32 work vectors of the Arnoldi steps (one per step of a block and
-        // right-hand side)
-        const size_t nw = h16 ? size_t(c->arnoldi_steps) : ps > 1 ? size_t(ps) : 0;
-        void *WT = nw ? w.WT.ensure(n * nb * sizeof(cx<float>) * nw) : nullptr;
+        // FP32 work vectors of the 16-bit Arnoldi steps (one per step of a block
+        // and right-hand side)
+        void *WT = h16 ? w.WT.ensure(n * nb * sizeof(cx<float>) * size_t(c->arnoldi_steps)) : nullptr;
         void *T = w.T.ensure(n * nb * sizeof(cx<double>));
         fill_zero(c, X, n * nb * sizeof(cx<double>));
         copy_dev(c, Rr, w.S.ptr, n * nb * sizeof(cx<double>));
@@ -1479,7 +1478,7 @@ extern "C" lqcd_status gmresdr_solve(lqcd_ctx *c, lqcd_op op, const lqcd_solve_p
                                  p.max_cycles, mv, cy, ires, ro, kInnerCycleCap, kInnerStall, WT);
           else
             proj_solve<float>(c, A32, d->V32.ptr, d, p_cyc, S32, X32, R32, W32, nb, iref, itol,
-                              p.max_cycles, mv, cy, ires, ro, kInnerCycleCap, kInnerStall, WT);
+                              p.max_cycles, mv, cy, ires, ro, kInnerCycleCap, kInnerStall, nullptr, ps);
           hipLaunchKernelGGL(k_acc_widen, dim3(std::min<size_t>(nblocks(n * nb), 8192)), dim3(kBlock),
                              0, c->stream, static_cast<const cx<float> *>(X32), static_cast<cx<double> *>(X),
                              n * nb);

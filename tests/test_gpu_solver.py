@@ -441,3 +441,30 @@ def test_dots_split_over_the_basis(dims, m, k):
         for r in range(4):
             assert rel_err(x[r], xref[r]) < 1e-9, (inner, r)
             assert st[r]["true_resid"] < 1e-11, (inner, r)
+
+
+@pytest.mark.parametrize("inner", ["f64", "f32"])
+def test_sstep_blocks_need_no_vectors_beside_the_basis(inner):
+    """Device memory of a solve with four Arnoldi steps per basis pass against
+    single steps: the powers of a block lie in the basis, so the two differ by
+    sums (16 MB here) and not by four vectors of every right-hand side (404 MB
+    in FP64, 202 MB in FP32): a solve that fits with single steps fits."""
+    require_gpu()
+    import torch
+    dims, nrhs = (16, 16, 16, 32), 9
+    half = 12 * int(np.prod(dims)) // 2 * (16 if inner == "f64" else 8)
+    used = {}
+    for steps in (1, 1, 4):  # the first pass fills torch's pool
+        torch.cuda.synchronize()
+        ctx, _ = context(dims, 0.25, 1002, 0.11)
+        free0 = torch.cuda.mem_get_info()[0]
+        ctx.tune(arnoldi_steps=steps)
+        say("solver memory", inner, steps)
+        x, _, st = ctx.gmresdr_solve(ctx.noise_z4(7, 0, nrhs), op="schur", m=30, k=10, tol=1e-8, inner=inner,
+                                     rhs_block=nrhs - 1)
+        torch.cuda.synchronize()
+        used[steps] = free0 - torch.cuda.mem_get_info()[0]
+        assert max(s["true_resid"] for s in st) < 2e-8
+        del x
+        ctx.close()
+    assert used[4] - used[1] < (nrhs - 1) * half, used
