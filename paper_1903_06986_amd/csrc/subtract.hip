@@ -99,11 +99,12 @@ cdouble spin_trace(int th, const SpinInt &S) {
   return t;
 }
 
-// One closed walk: its loop, the timeslices from its start to the loop's,
-// whether it runs the loop backwards, and tr(Theta S_w) for Theta = 1,
+// One closed walk: its loop's code, the timeslices from its start to the
+// loop's, whether it runs the loop backwards, and tr(Theta S_w) for Theta = 1,
 // g1..g4; point-split: +-tr(S_w) in the direction of its first step.
 struct Walk {
-  int loop, dt;
+  Code loop;
+  int dt;
   bool conj;
   cdouble coef[kNumOps];
 };
@@ -161,28 +162,21 @@ void each_walk(int len, const int L[4], int low, int depth, int disp[4], const S
   }
 }
 
-// The loops of length len in ascending order of their codes (depth-first):
-// those whose walks' last step does not undo the first and, if undone is set,
-// those whose walks' does.
-std::vector<Code> enumerate_loops(int len, const int L[4], bool undone) {
+// The loops of length len whose walks' last step does not undo the first, in
+// ascending order of their codes (depth-first).
+std::vector<Code> enumerate_loops(int len, const int L[4]) {
   std::vector<Code> loops;
   int disp[4] = {0, 0, 0, 0}, dirs[kMaxWalkLen];
-  auto take = [&](const int *w, bool un) {
-    if ((w[0] == (w[len - 1] ^ 1)) != un) return;
-    Code c = 0;
-    for (int i = 0; i < len; ++i) c = (c << 3) | Code(w[i]);
-    int dt;
-    bool conj;
-    if (loop_of(w, len, dt, conj) == c) loops.push_back(c);
-  };
-  // without an undone step a loop's code starts with a forward step in its
-  // lowest direction
+  // a loop's code starts with a forward step in its lowest direction
   for (int low = 0; low < 8; low += 2)
-    each_walk(len, L, low, 0, disp, kSpinOne, dirs, [&](const int *w, const SpinInt &) { take(w, false); });
-  if (undone) {
-    each_walk(len, L, -1, 0, disp, kSpinOne, dirs, [&](const int *w, const SpinInt &) { take(w, true); });
-    std::sort(loops.begin(), loops.end());
-  }
+    each_walk(len, L, low, 0, disp, kSpinOne, dirs, [&](const int *w, const SpinInt &) {
+      if (w[0] == (w[len - 1] ^ 1)) return;
+      Code c = 0;
+      for (int i = 0; i < len; ++i) c = (c << 3) | Code(w[i]);
+      int dt;
+      bool conj;
+      if (loop_of(w, len, dt, conj) == c) loops.push_back(c);
+    });
   return loops;
 }
 
@@ -550,18 +544,28 @@ void ensure_walk_traces(lqcd_ctx *c, bool need_len8) {
     // odd walks cannot close on even extents; a walk of length len gives the
     // local rows of order len and the point-split rows of order len - 1
     for (int len = 2; len <= kMaxWalkLen - 2; len += 2) {
-      const std::vector<Code> loops = enumerate_loops(len, g.L, true);
-      if (loops.empty()) continue;
-      const std::vector<cdouble> tr = loop_traces(c, loops, len);
+      std::vector<Walk> walks;
+      std::vector<Code> loops;
       int disp[4] = {0, 0, 0, 0}, dirs[kMaxWalkLen];
       each_walk(len, g.L, -1, 0, disp, kSpinOne, dirs, [&](const int *d, const SpinInt &S) {
         Walk w{};
-        for (int th = 0; th < kNumTheta; ++th) w.coef[th] = spin_trace(th, S);
+        bool any = false;
+        for (int th = 0; th < kNumTheta; ++th) {
+          w.coef[th] = spin_trace(th, S);
+          any = any || w.coef[th] != cdouble(0, 0);
+        }
+        if (!any) return;
         point_split(w, d[0], w.coef[0]);
-        const Code code = loop_of(d, len, w.dt, w.conj);
-        w.loop = int(std::lower_bound(loops.begin(), loops.end(), code) - loops.begin());
-        add(len, w, &tr[size_t(w.loop) * Lt]);
+        w.loop = loop_of(d, len, w.dt, w.conj);
+        walks.push_back(w);
+        loops.push_back(w.loop);
       });
+      if (walks.empty()) continue;
+      std::sort(loops.begin(), loops.end());
+      loops.erase(std::unique(loops.begin(), loops.end()), loops.end());
+      const std::vector<cdouble> tr = loop_traces(c, loops, len);
+      for (const Walk &w : walks)
+        add(len, w, &tr[size_t(std::lower_bound(loops.begin(), loops.end(), w.loop) - loops.begin()) * Lt]);
     }
   }
   if (need_len8) {
@@ -569,7 +573,7 @@ void ensure_walk_traces(lqcd_ctx *c, bool need_len8) {
     // of a loop, the conjugate for its reverse and zero for a walk with a
     // first step that its last one undoes
     const int len = kMaxWalkLen;
-    const std::vector<Code> loops = enumerate_loops(len, g.L, false);
+    const std::vector<Code> loops = enumerate_loops(len, g.L);
     const std::vector<cdouble> tr = loops.empty() ? std::vector<cdouble>() : loop_traces(c, loops, len);
     for (size_t l = 0; l < loops.size(); ++l) {
       Code seen[2 * kMaxWalkLen];
@@ -590,7 +594,7 @@ void ensure_walk_traces(lqcd_ctx *c, bool need_len8) {
           if (std::find(seen, seen + ns, code) == seen + ns) {
             seen[ns++] = code;
             Walk w{};
-            w.loop = int(l);
+            w.loop = loops[l];
             w.dt = -tk;
             w.conj = o != 0;
             point_split(w, r[k], o ? std::conj(trS) : trS);
