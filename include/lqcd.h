@@ -135,7 +135,8 @@ typedef struct {
   int matvecs;       /* applications of the solved operator (any precision) */
   int cycles;        /* restart cycles (GMRES-DR or GMRES(m-k) cycles of GMRES-Proj) */
   int refinements;   /* FP64 residual recomputations (mixed precision) */
-  int reorth;        /* Arnoldi steps whose Gram-Schmidt needed the second pass (DGKS test) */
+  int reorth;        /* Arnoldi steps whose Gram-Schmidt needed the second pass (DGKS test; on 16-bit
+                        bases blocks of LQCD_TUNE_ARNOLDI_STEPS steps) */
   double true_resid; /* final |b - A x| / |b| recomputed in FP64 on the full lattice */
 } lqcd_solve_stats;
 

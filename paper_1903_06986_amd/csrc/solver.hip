@@ -143,23 +143,30 @@ __device__ inline void gram_total(const double *__restrict__ part, int r, int nb
 constexpr int kSstepMaxJ = 256;  // basis vectors before a block (J <= m + 1 <= 251)
 // A block stores its basis vectors straight from the update pass only if
 // every Cholesky pivot of its Gram matrix (from the dot pass) keeps this
-// fraction of its diagonal entry: the difference Z^H Z - C^H C then loses
-// at most three digits to cancellation, well inside the 16-bit storage
-// rounding.
+// fraction of its diagonal entry.  The difference Z^H Z - C^H C then loses at
+// most the two digits of the DGKS test (kReorthCycle) and these three to
+// cancellation: the block is orthonormal to 1e5 roundings at worst, of FP64 on
+// an FP64 basis (1e-11), of the stored vectors on FP32 and 16-bit ones.  A
+// GMRES-Proj cycle needs no more: its least-squares solution is off the best
+// one by that fraction, the Hessenberg columns follow from the same
+// coefficients, and the residual that decides is computed anew after every
+// cycle.  In FP64 one cycle of 24, 60 or 120 steps leaves the residual of
+// single steps (3e-5, 5e-11 and 8e-16 of the source) to 4e-16 of the source.
 constexpr double kPivotMin = 1e-3;
 
-// s-step Arnoldi (16-bit basis), after the first dot pass: the Gram matrix
+// s-step Arnoldi, after the first dot pass: the Gram matrix
 // of the projected block Y = Z - V C follows from it as Z^H Z - C^H C (V
 // orthonormal; gpart holds the partials of Z^H Z).  The block takes the
 // direct path (flag clear; G[r] receives this Gram matrix, and the update
 // pass stores the orthonormalised vectors at once) when the DGKS test
 // passes on each vector (|y_k|^2 at least eta2 |z_k|^2) and each Cholesky
 // pivot keeps kPivotMin of its diagonal entry; otherwise the explicit path
-// (flag set, counted as a second pass): update in place, second block
-// pass, Gram matrix of the final vectors.  One wave per right-hand side r.
+// (flag set, counted as `count` second passes): update in place, second
+// block pass, Gram matrix of the final vectors.  One wave per right-hand
+// side r.
 template <int S>
 __device__ inline void sstep_plan(int r, const double *gpart, int nblk, const cx<double> *C, size_t ldc, int J,
-                                  double *G, int *flag, int *reorth_count, double eta2) {
+                                  double *G, int *flag, int *reorth_count, int count, double eta2) {
   constexpr int NG = S * S;
   constexpr int NPR = S * (S + 1) / 2;
   double g[NG];
@@ -212,13 +219,13 @@ __device__ inline void sstep_plan(int r, const double *gpart, int nblk, const cx
 #pragma unroll
   for (int q = 0; q < NG; ++q) G[size_t(r) * NG + q] = gp[q];
   flag[r] = need;
-  if (need) reorth_count[r] += 1;
+  if (need) reorth_count[r] += count;
 }
 template <int S>
 __global__ void k_sstep_plan(const double *__restrict__ gpart, int nblk, const cx<double> *__restrict__ C, size_t ldc,
                              int J, double *__restrict__ G, int *__restrict__ flag, int *__restrict__ reorth_count,
-                             double eta2) {
-  sstep_plan<S>(blockIdx.x, gpart, nblk, C, ldc, J, G, flag, reorth_count, eta2);
+                             int count, double eta2) {
+  sstep_plan<S>(blockIdx.x, gpart, nblk, C, ldc, J, G, flag, reorth_count, count, eta2);
 }
 
 // Columns j .. j + S - 1 of Hbar from the block z_k = B^k v_j, k = 1..S,
@@ -357,7 +364,7 @@ __global__ void __launch_bounds__(kBlock)
     C1[r * ldc + q] = mk(re, im);
   }
   __syncthreads();
-  if (threadIdx.x < 64) sstep_plan<S>(r, gpart, nblk, C1, ldc, J, G, flag, reorth_count, eta2);
+  if (threadIdx.x < 64) sstep_plan<S>(r, gpart, nblk, C1, ldc, J, G, flag, reorth_count, S, eta2);
   __syncthreads();
   sstep_finish<S, false>(r, Hd, Hrs, ldh, j, C1, C1, ldc, nullptr, 0, G, flag, sigma, f);
 }
@@ -629,7 +636,7 @@ void sstep_block(lqcd_ctx *c, const Op<float> &A, uint32_t *Wb, size_t n, size_t
   }
   hmulti_dots<BK, S, W16>(c, Wb, ldv, Wrs, J, wt, wvs, wrs, n, nb, C1, ldc, nullptr, gpart);
   hipLaunchKernelGGL(k_sstep_plan<S>, dim3(nb), dim3(64), 0, c->stream, gpart, nblk, C1d, ldc, J, G, s.flag,
-                     s.reorth, eta2);
+                     s.reorth, 1, eta2);
   LQCD_HIP(hipGetLastError());
   // direct path: Hessenberg columns and R^{-1} from the plan's Gram matrix,
   // then one update pass that stores the basis vectors
@@ -729,7 +736,7 @@ void sstep_block_plain(lqcd_ctx *c, const Op<R> &A, cx<R> *Wb, size_t n, size_t 
   } else {
     sum_dots(c, dpart, nblk, S * J, nb, C1, ldc, nullptr);
     hipLaunchKernelGGL(k_sstep_plan<S>, dim3(nb), dim3(64), 0, c->stream, gpart, nblk, C1d, ldc, J, G, s.flag,
-                       s.reorth, eta2);
+                       s.reorth, S, eta2);
     LQCD_HIP(hipGetLastError());
     hipLaunchKernelGGL((k_sstep_finish<S, false>), dim3(nb), dim3(64), 0, c->stream, Hd, s.Hrs, m + 1, j, C1d, C2d,
                        ldc, part, nblk, G, s.flag, kSigma, fd);

@@ -468,3 +468,44 @@ def test_sstep_blocks_need_no_vectors_beside_the_basis(inner):
         del x
         ctx.close()
     assert used[4] - used[1] < (nrhs - 1) * half, used
+
+
+@pytest.mark.parametrize("inner", ["f64", "f32"])
+@pytest.mark.parametrize("dims", [(6, 4, 2, 8), (16, 12, 12, 24)])
+def test_second_passes_are_counted_in_steps(inner, dims):
+    """With the second pass forced, every step of every cycle counts, also where
+    a block of steps takes it together (a last block of one, short sums in one
+    launch on the first lattice, the separate launches on the second)."""
+    require_gpu()
+    ctx, _ = context(dims, 0.3, 1001, 0.12)
+    eta = ctx.noise_z4(9, 0, 4)
+    for steps in (1, 2, 3, 4):
+        ctx.tune(arnoldi_steps=steps, cycle_reorth=1)
+        say("second passes", inner, dims, steps)
+        _, _, st = ctx.gmresdr_solve(eta, op="schur", m=23, k=10, tol=1e-8, inner=inner, inner_tol=1e-4, rhs_block=3)
+        for s in st[1:]:
+            assert s["reorth"] == 13 * s["cycles"] > 0, (steps, s)
+
+
+@pytest.mark.parametrize("p", [24, 60, 120])
+def test_one_long_cycle_of_blocks_reaches_the_residual_of_single_steps(p):
+    """One GMRES cycle of p steps on an FP64 basis, in blocks and step by step
+    from the same start: the residual is the smallest in the same Krylov space.
+    A basis orthonormal to d leaves it larger by d of itself (d <= 1e-11 p where a
+    block is stored without its second pass), and an Arnoldi relation off by 1e-15
+    per product, times 1e3 for the pivot bound, by 1e-12 of the source."""
+    require_gpu()
+    dims, kappa = (6, 4, 2, 8), 0.13
+    ctx, _ = context(dims, 0.3, 1001, kappa)
+    eta = to_gpu(z4_noise(2003, dims, 0, 4))
+    _, defl, _ = ctx.gmresdr_solve(eta[:1], op="schur", m=20, k=10, tol=1e-12, tol_super=1e-13)
+    res = {}
+    for steps in (1, 2, 3, 4):
+        ctx.tune(arnoldi_steps=steps)
+        say("one cycle", p, steps)
+        _, _, st = ctx.gmresdr_solve(eta, op="schur", m=20, k=10, tol=0.05, rhs_block=4, defl=defl, proj_m=p)
+        assert all(s["cycles"] == 1 and s["reorth"] == 0 for s in st), st
+        res[steps] = np.array([s["true_resid"] for s in st])
+    print("residuals after one cycle", res)
+    for steps in (2, 3, 4):
+        assert np.all(np.abs(res[steps] - res[1]) <= 1e-8 * res[1] + 1e-12), (steps, res)
