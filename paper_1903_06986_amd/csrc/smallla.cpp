@@ -131,7 +131,11 @@ std::vector<cd> lstsq(const Mat &A, const std::vector<cd> &b) {
   f.factor(A);
   std::vector<cd> y(b);
   f.apply_qh(y.data());
-  f.solve_r(y.data());
+  for (int i = A.cols - 1; i >= 0; --i) {
+    cd s = y[i];
+    for (int j = i + 1; j < A.cols; ++j) s -= f.qr(i, j) * y[j];
+    y[i] = f.tau[i] == cd(0, 0) ? cd(0, 0) : s / f.tau[i];
+  }
   y.resize(A.cols);
   return y;
 }

@@ -41,7 +41,9 @@ struct QR {
   Mat thin_q() const;                   // rows x cols orthonormal Q
 };
 
-// x = argmin |b - A x| (A rows x cols, rows >= cols, full column rank).
+// x = argmin |b - A x| (A rows x cols, rows >= cols, full column rank but for
+// columns of zeros, which get the coefficient 0: a Krylov basis that ends in an
+// invariant subspace has zero vectors behind it).
 std::vector<cd> lstsq(const Mat &A, const std::vector<cd> &b);
 
 // Solve A x = b (square) by LU with partial pivoting.

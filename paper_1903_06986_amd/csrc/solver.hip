@@ -243,9 +243,10 @@ __global__ void k_sstep_plan(const double *__restrict__ gpart, int nblk, const c
 // flag is set (c = C1 + C2, the second pass's coefficients added; Gram
 // matrix of the final vectors from the partials part).  f[r] = R^{-1} (S x
 // S, upper) turns the block into Q.  Where the Cholesky factor breaks down
-// at t < S (a pivot not positive), vectors t.. are zero: their F columns
-// vanish, column j + t has a zero subdiagonal entry, later columns are
-// zero.  Hbar's earlier columns must be Hessenberg (columns 0 .. j - 1 of
+// at t < S (a pivot not positive: the Krylov space ends there), vectors t..
+// are zero: their F columns vanish, column j + t has a zero subdiagonal entry,
+// later columns are zero, and the least-squares solution gives them the
+// coefficient zero.  Hbar's earlier columns must be Hessenberg (columns 0 .. j - 1 of
 // an Arnoldi process started at column 0).
 template <int S, bool EXPLICIT>
 __device__ inline void sstep_finish(int r, cx<double> *Hd, size_t Hrs, int ldh, int j, const cx<double> *C1,

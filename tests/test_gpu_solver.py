@@ -509,3 +509,51 @@ def test_one_long_cycle_of_blocks_reaches_the_residual_of_single_steps(p):
     print("residuals after one cycle", res)
     for steps in (2, 3, 4):
         assert np.all(np.abs(res[steps] - res[1]) <= 1e-8 * res[1] + 1e-12), (steps, res)
+
+
+@pytest.mark.parametrize("steps", [1, 2, 3, 4])
+@pytest.mark.parametrize("inner", ["f64", "f32"])
+@pytest.mark.parametrize("dims", [(2, 2, 2, 4), (4, 4, 2, 4)])
+def test_sstep_blocks_in_small_invariant_subspaces(dims, inner, steps):
+    """Sources whose Krylov space ends inside a block (the free operator on a
+    constant field, and on one that differs between the parities: exact
+    eigenvectors; a sum of eigenvectors of a random field: dimension 1 to 6), beside
+    noise in the same block: a Cholesky pivot vanishes and the rest of the block's
+    vectors are zero.  Solutions against LU, and eigenvectors take no more
+    cycles than noise."""
+    require_gpu()
+    kappas = (0.0625, 0.03125, 0.11)
+    for kappa in kappas:
+        for free in (True, False):
+            ctx, U = context(dims, 0.3, 1001, kappa, unit=free)
+            eta = z4_noise(3, dims, 0, 8).astype(np.complex128)
+            par = np.broadcast_to(W.parity_mask(dims) == 0, ctx.shape)
+            M = W.dense_M(U, kappa, dims)
+            if free:
+                eta[1] = 1.0
+                eta[2] = np.where(par, 1.0, 2.0)
+                eta[2][..., 0, 0] *= 3
+                eta[4] = np.where(par, 1.0, 0.0)
+                eta[5] = 0.0
+                eta[5][..., 1, 2] = 1.0
+                eta[6] = eta[4] + 1e-6 * eta[6]
+            else:
+                flat = par.reshape(-1)
+                E, O = np.flatnonzero(flat), np.flatnonzero(~flat)
+                lam, vec = np.linalg.eig(M[np.ix_(E, E)] - M[np.ix_(E, O)] @ M[np.ix_(O, E)])
+                order = np.argsort(-np.abs(lam))
+                for r, count in ((1, 1), (2, 2), (4, 3), (5, 4), (6, 6)):
+                    e = np.zeros(M.shape[0], complex)
+                    e[E] = vec[:, order[:count]].sum(1)
+                    eta[r] = e.reshape(ctx.shape)
+            xref = np.linalg.solve(M, eta.reshape(8, -1).T).T.reshape(eta.shape)
+            say("invariant subspaces", dims, inner, steps, kappa, "free" if free else "random")
+            _, defl, _ = ctx.gmresdr_solve(to_gpu(eta[:1]), op="schur", m=20, k=10, tol=1e-12)
+            ctx.tune(arnoldi_steps=steps)
+            x, _, st = ctx.gmresdr_solve(to_gpu(eta[1:]), op="schur", m=20, k=10, tol=1e-11, inner=inner,
+                                         inner_tol=1e-4, rhs_block=7, defl=defl, max_cycles=200)
+            x = to_host(x)
+            for r in range(7):
+                assert rel_err(x[r], xref[r + 1]) < 1e-9, (kappa, free, r)
+                assert st[r]["true_resid"] < 1e-11, (kappa, free, r, st[r])
+            assert st[0]["cycles"] <= st[2]["cycles"], (kappa, free, st)
