@@ -507,7 +507,9 @@ lqcd_status lqcd_timer_read(lqcd_ctx *ctx, int kclass, double *ms, double *bytes
  * LQCD_TUNE_HOP_LEGS: the leg-split stencil (the eight neighbour terms of a
  * site on eight waves): -1 (default) unless one of the LQCD_TUNE_HOP_ launch
  * shapes above was set on the context (they belong to the lane-grouped and the
- * link-tiled forms), 0 never, 1 always.
+ * link-tiled forms), 0 never, 1 always; in every setting wilson_apply runs
+ * calls of one to three FP32 or 16-bit right-hand sides, and such a rest of a
+ * longer LEX call's last block of 16, in the lane-grouped form.
  * Values are per context; EINVAL for other values. */
 typedef enum {
   LQCD_TUNE_HOP_NB64 = 0,

@@ -1231,9 +1231,12 @@ size_t prec_bytes(lqcd_prec p) { return p == LQCD_F64 ? 16 : 8; }
 
 constexpr size_t kLexInPlace = size_t(512) << 20;
 
-// Up to three FP32 right-hand sides of a wilson_apply call keep the
-// lane-grouped form, whose products round in another order, so that a call's
-// result does not depend on the size of the lattice.
+// Up to three FP32 or 16-bit right-hand sides of a wilson_apply call (or of its
+// last block of 16) keep the lane-grouped form at every setting of the switch:
+// its products round in another order than the leg-split form's, and such calls
+// give the bits that they always gave.  It is the slower one (8^4, one right-hand
+// side: 8 us per half hop against 3); the solvers, whose results are defined to
+// their tolerance, take the leg-split form for any number of right-hand sides.
 struct LegsForApply {
   lqcd_ctx *c;
   int keep;

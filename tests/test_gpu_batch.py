@@ -156,3 +156,31 @@ def test_batch_link_tiles_equal_the_leg_split_form(tile):
         out[legs] = [to_host(y) for y in batch.wilson_apply(xs)]
     for a, b in zip(out[0], out[-1]):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("tile", [16, 64])
+def test_leg_split_stencil_of_one_to_three_right_hand_sides(tile):
+    """The FP32 leg-split stencil at one, two and three right-hand sides (which
+    wilson_apply gives to another form): a right-hand side's result does not
+    depend on how many there are, so it is that of a call of four bit for bit,
+    and the oracle's to FP32 rounding.  Lattices of one ragged tile, ragged ones
+    and whole ones."""
+    require_gpu()
+    from paper_1903_06986_amd import Batch
+    lats = [((2, 2, 2, 4), 0.12, 1, 1001), ((6, 4, 2, 8), 0.13, 2, 1002), ((8, 4, 4, 8), 0.125, 3, 1003),
+            ((8, 6, 6, 20), 0.13, 1, 1004)]
+    rng = np.random.default_rng(10)
+    ctxs, Us, xs = [], [], []
+    for dims, kappa, nr, seed in lats:
+        ctx, U = context(dims, 0.3, seed, kappa)
+        ctxs.append(ctx)
+        Us.append(U)
+        xs.append(rng.standard_normal((4,) + ctx.shape) + 1j * rng.standard_normal((4,) + ctx.shape))
+    batch = Batch(ctxs)
+    batch.set_tile(tile)
+    say("leg-split stencil of few right-hand sides, tile", tile)
+    ys = batch.wilson_apply([to_gpu(x[:nr]) for x, (_, _, nr, _) in zip(xs, lats)])
+    for (dims, kappa, nr, seed), ctx, U, x, y in zip(lats, ctxs, Us, xs, ys):
+        four = to_host(ctx.wilson_apply("schur", to_gpu(x), prec="f32"))
+        assert np.array_equal(to_host(y), four[:nr]), dims
+        assert rel_err(four[:nr], W.apply_Mhat(U, kappa, x[:nr], dims)) < 5e-6, dims

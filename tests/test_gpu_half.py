@@ -199,3 +199,31 @@ def test_sstep_direct_and_explicit_paths_in_one_block(prec, z16):
         assert s[r]["true_resid"] < 1e-11, r
     assert s[2]["reorth"] > 0, s[2]
     assert s[1]["reorth"] == 0 and s[3]["reorth"] == 0, (s[1], s[3])
+
+
+@pytest.mark.parametrize("nrhs", [1, 2, 3])
+@pytest.mark.parametrize("prec", ["f16", "bf16"])
+def test_leg_split_cycles_of_one_to_three_right_hand_sides(prec, nrhs):
+    """16-bit cycles with one to three active right-hand sides, in the leg-split
+    stencil and in the lane-grouped one: a wrong operator would not bring the FP64
+    residual down; solutions reach LU, in about as many products."""
+    require_gpu()
+    dims, kappa = (6, 4, 2, 8), 0.13
+    ctx, U = context(dims, 0.3, 1001, kappa)
+    eta = z4_noise(2003, dims, 0, nrhs + 1)
+    M = W.dense_M(U, kappa, dims)
+    xref = np.linalg.solve(M, eta.reshape(nrhs + 1, -1).T).T.reshape(eta.shape)
+    _, defl, _ = ctx.gmresdr_solve(to_gpu(eta[:1]), op="schur", m=20, k=10, tol=1e-12, tol_super=1e-13)
+    mv = {}
+    for legs in (1, 0):
+        ctx.tune(hop_legs=legs)
+        say("16-bit cycles", prec, nrhs, "legs", legs)
+        x, _, st = ctx.gmresdr_solve(to_gpu(eta[1:]), op="schur", m=20, k=10, tol=1e-11, inner=prec, inner_tol=1e-3,
+                                     rhs_block=nrhs, defl=defl)
+        x = to_host(x)
+        for r in range(nrhs):
+            assert rel_err(x[r], xref[r + 1]) < 1e-9, (legs, r)
+            assert st[r]["true_resid"] < 1e-11, (legs, r)
+        mv[legs] = [s["matvecs"] for s in st]
+    for a, b in zip(mv[1], mv[0]):
+        assert abs(a - b) <= 2 * 11, mv  # two cycles of ten steps
