@@ -194,3 +194,27 @@ def test_leg_split_stencil_equals_the_other_forms(dims, nrhs):
                     assert rel_err(y[1], y[0]) < 1e-14, (op, layout)
                 else:
                     assert np.array_equal(y[1], y[0]), (prec, op, layout)
+
+
+@pytest.mark.parametrize("prec,nrhs", [("f64", 8), ("f32", 8), ("f16", 8)])
+def test_operators_on_fields_past_the_caches(prec, nrhs):
+    """Fields of 199 MB (the leg-split kernels load the links and store their
+    results past the caches above 96 MB): the other forms' results (FP64 to the
+    rounding of two sums, FP32 and 16-bit bit for bit), all operators; 2025 tiles
+    of 64 sites, of one parity 1012 and a half."""
+    require_gpu()
+    import torch
+    ctx, _ = context((18, 12, 20, 30), 0.3, 41, 0.13)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    x = torch.view_as_complex(torch.randn((nrhs,) + ctx.shape + (2,), generator=g, dtype=torch.float64, device="cuda"))
+    for op in (("schur",) if prec == "f16" else ("M", "Mdag", "MG5", "hop", "schur")):
+        y = {}
+        for legs in (0, 1):
+            ctx.tune(hop_legs=legs)
+            say("past the caches", prec, op, legs)
+            y[legs] = ctx.wilson_apply(op, x, prec=prec)
+        if prec == "f64":
+            assert float((y[0] - y[1]).abs().max()) < 1e-14 * float(y[0].abs().max()), op
+        else:
+            assert torch.equal(y[0], y[1]), op
