@@ -91,4 +91,13 @@ __device__ inline void stc_nt(cx<R> *p, cx<R> a) {
   __builtin_nontemporal_store(v, reinterpret_cast<v2 *>(p));
 }
 
+// v, or -v where mask is the sign bit (one register where a factor takes two).
+__device__ inline double flip(double v, unsigned mask) {
+  return __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, v) ^
+                                        (static_cast<unsigned long long>(mask) << 32));
+}
+__device__ inline float flip(float v, unsigned mask) {
+  return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, v) ^ mask);
+}
+
 }  // namespace lqcd

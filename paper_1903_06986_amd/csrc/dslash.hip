@@ -348,8 +348,11 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop
 // Sites are taken in blocks of tb timeslices (one block per XCD), z, t within
 // the block, y, x; the workgroups in flight on an XCD start together and stay
 // near the same right-hand side, so that its L2 holds that one's neighbours.
-// Bound at 16 right-hand sides by HBM: with the planes at the edges of what is
-// in flight read twice, 4.5 TB/s (a copy reaches 4.9).  us per half hop, tiled
+// Bound at 16 right-hand sides by the memory side of L2: neighbours that have
+// left it are fetched again, by the counters 1.77 times the links and fields in
+// FP64 and 1.74 times in FP32 pairs on 24^3 x 32 (1.35 in FP64 on 16^3 x 32, 10
+// right-hand sides), at 6.0, 5.6 and 5.2 TB/s with the hits of the last-level
+// cache among them (a copy reaches 4.9).  us per half hop, tiled
 // or lane-grouped -> this form: 24^3 x 32, 16 right-hand sides FP64 545 -> 481
 // (with a self term 632 -> 516), FP32 291 -> 270, FP32 pairs 259 -> 242, 16-bit
 // 186 -> 183; 10 right-hand sides FP64 398 -> 304, FP32 205 -> 170; 16^3 x 32,
@@ -620,22 +623,16 @@ __global__ void __launch_bounds__(8 * kLegSites) __attribute__((amdgpu_waves_per
 // lower half of a term is its upper one with signs and re / im exchanged, so
 // a lane reads the real and imaginary part it needs apart and adds them with
 // a sign.  Per right-hand side the arithmetic and its order are k_hop_legs's.
-// Bound by HBM and the latency of its phases: MG5 on 24^3 x 32, 16 right-hand
-// sides, FP64 2252 us (pack, hop, unpack) -> 1352 us, 2.4 TB/s of links and
-// fields; FP32 1676 -> 1014 us.  FP64 holds the next right-hand side's pieces in
-// registers and has one workgroup per CU; at two per CU without them it spills
-// (1839 us), with them more (3254 us).  FP32 fits two per CU without (1014 us;
-// with the pieces ahead 1374).
+// Bound by the memory side of L2: a field's pieces are loaded by eight
+// neighbours and the site itself and, by the counters, fetched 3.8 times (7.0 GB
+// a call, 2.2 times the links and fields, 5.0 TB/s; FP32 7.2 GB, 6.9 TB/s with
+// the last-level cache's hits).  MG5 on 24^3 x 32, 16 right-hand sides: FP64
+// 2252 us (pack, hop, unpack) -> 1352 us, FP32 1676 -> 1014 us.  FP64 holds the
+// next right-hand side's pieces in registers and has one workgroup per CU; at
+// two per CU without them it spills (1839 us), with them more (3254 us).  FP32
+// fits two per CU without (1014 us; with the pieces ahead 1374).
 constexpr int kLexStride = 7;                        // of a site's six products: distinct banks across sites
 constexpr int kLexRegion = kLegSites * kLexStride;   // one term
-// v, or -v where mask is the sign bit (one register where a factor takes two).
-__device__ inline double flip(double v, unsigned mask) {
-  return __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, v) ^
-                                        (static_cast<unsigned long long>(mask) << 32));
-}
-__device__ inline float flip(float v, unsigned mask) {
-  return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, v) ^ mask);
-}
 template <class R, bool G5IN, bool G5OUT, bool SELF>
 __global__ void __launch_bounds__(8 * kLegSites) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 2 : 4, 8)))
     k_hop_lex(Geom g, const cx<R> *__restrict__ U, const cx<double> *__restrict__ in, cx<double> *__restrict__ out,
@@ -876,7 +873,8 @@ void launch_hop_legs(lqcd_ctx *c, Timed &tm, int p, int npar, SI in, SS self, OT
   const Geom &g = c->g;
   const cx<R> *U = static_cast<const cx<R> *>(std::is_same<R, double>::value ? c->U64.ptr : c->U32.ptr);
   // Right-hand sides per workgroup: all of them (links loaded once) where the
-  // sites alone give the chip's 256 CUs three workgroups each, else fewer.
+  // sites alone give the chip's 256 CUs three workgroups each (what a CU holds
+  // in FP32; two in FP64), else fewer.
   const int ntile = (g.Vh + kLegSites - 1) / kLegSites * npar;
   const int ngr = std::min(nrhs, std::max(1, 768 / ntile)), rg = (nrhs + ngr - 1) / ngr;
   // Links and outputs past the caches where the fields exceed them (8 x 4 MiB

@@ -137,8 +137,10 @@ __global__ void __launch_bounds__(kBlock)
 // half a complex number: 64 contiguous bytes of each variant an instruction).
 //
 // Bound by HBM (eta, x and each xt once): 24^3 x 32, 16 right-hand sides, six
-// variants 7.9 ms (a local kernel for three variants a launch, and one that
-// staged x - xt of every variant in LDS) -> 3.7 ms, 2.9 TB/s.
+// variants, one without xt, 7.9 ms (a local kernel for three variants a launch,
+// and one that staged x - xt of every variant in LDS) -> 3.7 ms: 2.6 TB/s of
+// links and fields, by the counters 1.64 times that (eta is gathered at the
+// neighbours), 4.3 TB/s.
 // Two workgroups a CU (LDS, registers) hide the latency of the two phases of
 // each other only in part.
 constexpr int kPsSites = 64;             // sites per chunk
@@ -284,11 +286,6 @@ __device__ inline double swap_pair(double v) {
   const int lo = __builtin_amdgcn_update_dpp(0, int(b), 0xB1, 0xf, 0xf, true);
   const int hi = __builtin_amdgcn_update_dpp(0, int(b >> 32), 0xB1, 0xf, 0xf, true);
   return __builtin_bit_cast(double, (static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
-}
-// v, or -v where mask is the sign bit.
-__device__ inline double flip(double v, unsigned mask) {
-  return __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, v) ^
-                                        (static_cast<unsigned long long>(mask) << 32));
 }
 
 // Workgroup order: the right-hand side varies fastest within one XCD's
