@@ -53,7 +53,11 @@ __global__ void k_pack(Geom g, const cx<double> *__restrict__ lex, cx<R> *__rest
   }
 }
 
-// EVEN: the odd sites of lex are set to zero (eo holds even halves only).
+// EVEN: the odd sites of lex are set to zero (eo holds even halves only).  An
+// odd site's lane loads its even x neighbour's components (the same cache lines)
+// and drops them, so that the twelve loads go out together; under a condition
+// each waits for the one before (the FP16 even/odd operator on 24^3 x 32, 16
+// right-hand sides 2030 -> 1622 us a call; clearing the odd halves first 1800).
 template <class R, bool EVEN>
 __global__ void k_unpack(Geom g, const cx<R> *__restrict__ eo, cx<double> *__restrict__ lex,
                          size_t eo_stride) {
@@ -64,12 +68,12 @@ __global__ void k_unpack(Geom g, const cx<R> *__restrict__ eo, cx<double> *__res
   const int x = s % Lx, y = (s / Lx) % Ly, z = (s / (Lx * Ly)) % Lz, t = s / (Lx * Ly * Lz);
   const int p = (x + y + z + t) & 1;
   const size_t Vh = g.Vh;
-  const cx<R> *src = eo + rhs * eo_stride + p * 12 * Vh + (s >> 1);
+  const cx<R> *src = eo + rhs * eo_stride + (EVEN ? 0 : p * 12 * Vh) + (s >> 1);
   cx<double> *dst = lex + (rhs * g.V + s) * 12;
 #pragma unroll
   for (int c = 0; c < 12; ++c) {
-    cx<R> v = mk<R>(0, 0);
-    if (!EVEN || p == 0) v = ldc(src + c * Vh);
+    cx<R> v = ldc(src + c * Vh);
+    if (EVEN && p) v = mk<R>(0, 0);
     stc(dst + c, mk<double>(double(v.re), double(v.im)));
   }
 }
