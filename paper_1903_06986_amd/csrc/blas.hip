@@ -1487,13 +1487,15 @@ struct RUnit {
 
 // C = V^H X for J <= 16 RT basis vectors and nb <= 16 columns.  Lane (row or
 // column l % 16, k = l / 16) loads unit k of a group of four: four lanes take
-// 64 contiguous bytes of each of 16 vectors, kTnGroups groups go out together
-// (256 bytes a vector), and those of the next step are in flight while one is
-// multiplied.  Every wave sums its own steps (grid stride); a workgroup's four
+// 64 contiguous bytes of each of 16 vectors, kTnGroups groups go out together,
+// one vector's 256 bytes in a row (the two halves of a 128-byte line are then
+// asked for while L1 has it), and those of the next step are in flight while one
+// is multiplied.  Every wave sums its own steps (grid stride); a workgroup's four
 // waves add in LDS, in FP64, and a second kernel adds the workgroups.  V and X
 // are read once: 30 modes of 16^3 x 32 against 16 right-hand sides 2 x 306 (V
-// through LDS, 8 columns a launch) -> 350 us, 3.3 TB/s.  (V through plain loads:
-// streaming ones fetch the 128-byte lines once per 64-byte half, 404 us.)
+// through LDS, 8 columns a launch) -> 265 us, 4.4 TB/s (340 with the groups of
+// all vectors in turn).  V goes through plain loads: streaming ones fetch the
+// lines once per half.
 constexpr int kTnGroups = 4;
 template <class R, int RT>
 __global__ void __launch_bounds__(kBlock)
@@ -1510,17 +1512,18 @@ __global__ void __launch_bounds__(kBlock)
   const size_t nstep = (n + STEP - 1) / STEP, stride = size_t(gridDim.x) * kWaves;
   RUnit<R> v[RT][kTnGroups], x[kTnGroups];
   auto fetch = [&](size_t st) {
+    const size_t e0 = st * STEP + size_t(k) * EV;  // n is a multiple of EV
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int g = 0; g < kTnGroups; ++g) {
+        v[t][g].zero();
+        if (e0 + 4 * g * EV < n && 16 * t + l16 < J) v[t][g].load(V + size_t(16 * t + l16) * ldv + e0 + 4 * g * EV);
+      }
 #pragma unroll
     for (int g = 0; g < kTnGroups; ++g) {
-      const size_t e = st * STEP + size_t(4 * g + k) * EV;
-      const bool in = e < n;  // n is a multiple of EV
-#pragma unroll
-      for (int t = 0; t < RT; ++t) {
-        v[t][g].zero();
-        if (in && 16 * t + l16 < J) v[t][g].load(V + size_t(16 * t + l16) * ldv + e);
-      }
       x[g].zero();
-      if (in && l16 < nb) x[g].load(X + size_t(l16) * ldx + e);
+      if (e0 + 4 * g * EV < n && l16 < nb) x[g].load(X + size_t(l16) * ldx + e0 + 4 * g * EV);
     }
   };
   size_t st = size_t(blockIdx.x) * kWaves + wave;
@@ -1830,10 +1833,21 @@ void gemm_tn(lqcd_ctx *c, const void *V, size_t ldv, int J, const void *X, size_
              size_t n, cdouble *C, size_t ldc) {
   if (J <= 0 || nb <= 0) return;
   constexpr int EV = RUnit<R>::EV;
-  if (J > 64 || n < 64 || n % EV != 0 || ldv % EV != 0 || ldx % EV != 0) {
-    // outside the matrix-core tile: one multi-dot per column of X
+  if (nb == 1 || J > 64 || n < 64 || n % EV != 0 || ldv % EV != 0 || ldx % EV != 0) {
+    // outside the matrix-core tile: one multi-dot per column of X; so too a
+    // single column, which reads V in long runs (64 vectors of 16^3 x 32 with
+    // their V C 860 -> 565 us a call)
     multi_dot_impl<R>(c, V, ldv, 0, J, X, ldx, n, nb, C, ldc, LQCD_KC_GEMM,
                       double(J + nb) * n * sizeof(cx<R>));
+    return;
+  }
+  // In FP64 the fourth tile of rows leaves one wave per SIMD (316 registers):
+  // with few columns two halves of the vectors are faster, X being read twice
+  // (16^3 x 32, 56 vectors, 2 columns 427 -> 344 us; 8 columns 365 against 380).
+  if (sizeof(R) == 8 && J > 48 && nb <= 4 && n >= (size_t(1) << 19)) {
+    const int h = (J + 1) / 2;
+    gemm_tn<R>(c, V, ldv, h, X, ldx, nb, n, C, ldc);
+    gemm_tn<R>(c, static_cast<const cx<R> *>(V) + size_t(h) * ldv, ldv, J - h, X, ldx, nb, n, C + h, ldc);
     return;
   }
   // 16 columns per launch, the contraction split over up to 512 workgroups

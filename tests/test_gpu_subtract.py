@@ -281,3 +281,24 @@ def test_trace_corrections_of_links_that_are_not_unitary(dims, links):
                                   np.stack([PSO.trace_ps_dense(U, kappa, dims, mu, A) for mu in range(4)])])
             for op in range(9):
                 assert np.abs(corr[op] - ref[op]).max() < 1e-10 * np.abs(ref[1:]).max(), (order, op)
+
+
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (16, 16, 12, 16)])
+def test_projections_of_several_columns_equal_single_ones(dims):
+    """V^H X of 2 to 16 columns at once (matrix cores; 49 and more vectors of a
+    large field in two halves for up to four columns) against one column at a
+    time (dot passes over V), through the projection on 1 to 64 modes: the same
+    sums in another order, 1e-12."""
+    require_gpu()
+    ctx, _ = context(dims, 0.25, 17, 0.12)
+    eta = ctx.noise_z4(5, 0, 16)
+    say("deflation modes", dims)
+    _, hdefl, _ = ctx.gmresdr_solve(eta[:1].contiguous(), op="MG5", m=80, k=66, tol=0.3, tol_super=0.3,
+                                    method="minres-dr")
+    for Q in (1, 16, 17, 33, 48, 49, 56, 64):
+        ones = [to_host(ctx.deflate_project(hdefl, Q, eta[r:r + 1].contiguous(), thetas=(0,))[0])[0] for r in range(16)]
+        for n in (2, 4, 5, 16):
+            say("columns at once", dims, Q, n)
+            xt = to_host(ctx.deflate_project(hdefl, Q, eta[:n].contiguous(), thetas=(0,))[0])
+            for r in range(n):
+                assert np.abs(xt[r] - ones[r]).max() <= 1e-12 * np.abs(ones[r]).max(), (Q, n, r)
