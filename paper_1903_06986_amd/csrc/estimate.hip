@@ -6,6 +6,7 @@
 // s / sqrt(N) with the unbiased sample variance, for Re and Im separately.
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "cplx.h"
 #include "gamma.h"
@@ -202,10 +203,11 @@ __device__ inline void ps_colour(const cx<double> u[9], const cx<double> a[3], c
 
 // The rows of direction MU at the wave's 64 sites (lane = site, full index
 // s of parity par; on: inside the timeslice, else the rows are zero) into
-// reg.  sf, sb: index of the site's forward and backward neighbour.
-template <int MU>
+// reg.  sf, sb: index of the site's forward and backward neighbour.  mid() runs
+// once the neighbours' registers are free.
+template <int MU, class Mid>
 __device__ inline void ps_rows(const cx<double> *__restrict__ U, size_t Vh, const cx<double> *__restrict__ eta,
-                               double kappa, int s, int sf, int sb, int par, bool on, cx<double> *reg) {
+                               double kappa, int s, int sf, int sb, int par, bool on, cx<double> *reg, Mid &&mid) {
   const int lane = threadIdx.x & 63;
   cx<double> vb[12], vf[12], ub[9], uf[9];
 #pragma unroll
@@ -237,6 +239,7 @@ __device__ inline void ps_rows(const cx<double> *__restrict__ U, size_t Vh, cons
   ps_colour<true>(ub, a0, cf[0]);
   ps_colour<true>(ub, a1, cf[1]);
   put(vf);
+  mid();
   PsHalf<MU, false, 0>::at(own, a0);
   PsHalf<MU, false, 1>::at(own, a1);
   ps_colour<false>(uf, a0, cb[0]);
@@ -288,17 +291,27 @@ __device__ inline double swap_pair(double v) {
   return __builtin_bit_cast(double, (static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
 }
 
+// A single variant (ONE) takes v_mfma_f64_4x4x4, whose four blocks are the row
+// groups with the same four columns: a quarter of the products and the same bits
+// (rows and components lie in the lanes alike, and both instructions round
+// alike).  Its d goes through LDS, loaded in 1 KB runs while the rows are made:
+// straight from memory a load brings 64 bytes of one variant, and those loads
+// were half of the kernel's time.  24^3 x 32, 16 right-hand sides, all operators:
+// 2.19 ms a call (a local and a point-split kernel 2.98, the 16-column form 3.16).
+//
 // Workgroup order: the right-hand side varies fastest within one XCD's
 // contiguous range of logical workgroups (hardware workgroup h runs on XCD
 // h % 8), so the nrhs workgroups of one chunk of sites run back to back on
 // one XCD and read its links from that XCD's L2 (links are as many bytes as
 // one right-hand side's three fields).
+template <bool ONE>
 __global__ void __launch_bounds__(kBlock, 2)
     k_estimate_all(Geom g, const cx<double> *__restrict__ U, double kappa, const cx<double> *__restrict__ eta,
                    const cx<double> *__restrict__ x, XtSet xts, int nv, int nch, int nrhs, int xq,
                    double *__restrict__ out) {
   typedef double d4 __attribute__((ext_vector_type(4)));
-  __shared__ cx<double> reg[(1 + kNumPS) * kPsRegion];
+  using Acc = typename std::conditional<ONE, double, d4>::type;
+  __shared__ cx<double> reg[(1 + kNumPS + ONE) * kPsRegion];
   const int L = int(blockIdx.x % 8) * xq + int(blockIdx.x / 8);
   if (L >= g.L[3] * nch * nrhs) return;  // whole workgroup: padding of the grid
   const int r = L % nrhs, tch = L / nrhs;
@@ -308,10 +321,11 @@ __global__ void __launch_bounds__(kBlock, 2)
   const size_t Vh = size_t(g.Vh), base = size_t(r) * size_t(g.V) * 12;
   eta += base;
   const int lane = threadIdx.x & 63, q = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
-  // product: lane = row and column l % 16, components l / 16 of groups of four;
+  // product: lane = row l % 16 and column l % 16 (ONE: l % 4), components l / 16
+  // of groups of four;
   // gr, gi: places (in doubles) of the real and imaginary part of the row's
   // components and the signs they take
-  const int l16 = lane & 15, kq = lane >> 4;
+  const int l16 = lane & 15, kq = lane >> 4, lcol = ONE ? lane & 3 : l16;
   int gr[3], gi[3];
   unsigned sr[3], si[3];
 #pragma unroll
@@ -324,14 +338,14 @@ __global__ void __launch_bounds__(kBlock, 2)
     sr[j] = turns == 1 || turns == 2 ? 0x80000000u : 0u;
     si[j] = turns >= 2 ? 0x80000000u : 0u;
   }
-  const double *xp = reinterpret_cast<const double *>(x + base) + 2 * kq + (l16 & 1), *tp = nullptr;
+  const double *xp = reinterpret_cast<const double *>(x + base) + 2 * kq + (lcol & 1), *tp = nullptr;
 #pragma unroll
   for (int v = 0; v < kMaxVar; ++v)
-    if (v < nv && v == l16 >> 1) tp = reinterpret_cast<const double *>(xts.p[v]);
+    if (v < nv && v == lcol >> 1) tp = reinterpret_cast<const double *>(xts.p[v]);
   const double minus = tp ? -1.0 : 0.0;
-  tp = tp ? tp + 2 * base + 2 * kq + (l16 & 1) : xp;
-  const unsigned odd = (l16 & 1) ? 0x80000000u : 0u;
-  d4 tot = {0, 0, 0, 0};
+  tp = tp ? tp + 2 * base + 2 * kq + (lcol & 1) : xp;
+  const unsigned odd = (lcol & 1) ? 0x80000000u : 0u;
+  Acc tot = {};
   for (int i0 = ch * kPsSites; i0 < Vs; i0 += nch * kPsSites) {
     const int i = i0 + lane;
     const bool on = i < Vs;
@@ -357,43 +371,75 @@ __global__ void __launch_bounds__(kBlock, 2)
       }
     }
     cx<double> *mine = reg + (1 + q) * kPsRegion;
-    if (q == 0) ps_rows<0>(U, Vh, eta, kappa, s, sf, sb, par, on, mine);
-    else if (q == 1) ps_rows<1>(U, Vh, eta, kappa, s, sf, sb, par, on, mine);
-    else if (q == 2) ps_rows<2>(U, Vh, eta, kappa, s, sf, sb, par, on, mine);
-    else ps_rows<3>(U, Vh, eta, kappa, s, sf, sb, par, on, mine);
-    // products of the wave's 16 sites, two at a time, the next ones' d in
-    // flight (sites past the end, whose rows are zero, read the last one)
-    constexpr int NS = kPsSites / kWaves, BS = 2;
-    double xv[2][3 * BS], tv[2][3 * BS];
-    const int w0 = i0 + q * NS;
-    auto fetch = [&](int b, double *px, double *pt) {
+    cx<double> xr[3], tr[3];  // ONE: x and xt at the sites, pieces as eta's
+    const cx<double> *x1 = x + base, *t1 = ONE && xts.p[0] ? xts.p[0] + base : nullptr;
+    auto mid = [&] {
+      if constexpr (ONE)
 #pragma unroll
-      for (int u = 0; u < BS; ++u) {
-        const size_t o = (size_t(t) * Vs + std::min(w0 + BS * b + u, Vs - 1)) * 24;
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-          px[3 * u + j] = xp[o + 8 * j];
-          pt[3 * u + j] = tp[o + 8 * j];
+        for (int u = 0; u < 3; ++u) {
+          const int j = threadIdx.x + u * kBlock;
+          const size_t o = (size_t(t) * Vs + i0) * 12 + (i0 + j / 12 < Vs ? j : 0);
+          xr[u] = ldc(x1 + o);
+          tr[u] = t1 ? ldc(t1 + o) : mk(0.0, 0.0);
         }
+    };
+    if (q == 0) ps_rows<0>(U, Vh, eta, kappa, s, sf, sb, par, on, mine, mid);
+    else if (q == 1) ps_rows<1>(U, Vh, eta, kappa, s, sf, sb, par, on, mine, mid);
+    else if (q == 2) ps_rows<2>(U, Vh, eta, kappa, s, sf, sb, par, on, mine, mid);
+    else ps_rows<3>(U, Vh, eta, kappa, s, sf, sb, par, on, mine, mid);
+    constexpr int NS = kPsSites / kWaves, BS = 2;
+    Acc acc0 = {}, acc1 = {};  // of this chunk: short chains of sums round less
+    const double *rd = reinterpret_cast<const double *>(reg);
+    auto product = [&](int site, int j, double d) {
+      const double a0 = flip(rd[gr[j] + site], sr[j]), a1 = flip(rd[gi[j] + site], si[j]);
+      const double e = flip(swap_pair(d), odd);
+      if constexpr (ONE) {
+        acc0 = __builtin_amdgcn_mfma_f64_4x4x4f64(a0, d, acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f64_4x4x4f64(a1, e, acc1, 0, 0, 0);
+      } else {
+        acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, d, acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, e, acc1, 0, 0, 0);
       }
     };
-    fetch(0, xv[0], tv[0]);
-    __syncthreads();
-    const double *rd = reinterpret_cast<const double *>(reg);
-    d4 acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};  // of this chunk: short chains of sums round less
+    if constexpr (ONE) {
+      cx<double> *ds = reg + (1 + kNumPS) * kPsRegion;
 #pragma unroll
-    for (int b = 0; b < NS / BS; ++b) {
-      if (b + 1 < NS / BS) fetch(b + 1, xv[(b + 1) & 1], tv[(b + 1) & 1]);
+      for (int u = 0; u < 3; ++u) {
+        const int j = threadIdx.x + u * kBlock;
+        ds[j / 12 * kPsStride + j % 12] = i0 + j / 12 < Vs ? xr[u] - tr[u] : mk(0.0, 0.0);
+      }
+      __syncthreads();
+      const double *dd = reinterpret_cast<const double *>(ds + q * NS * kPsStride) + 2 * kq + (lcol & 1);
 #pragma unroll
-      for (int u = 0; u < BS; ++u) {
+      for (int u = 0; u < NS; ++u)
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-          const int site = 2 * (BS * b + u) * kPsStride;
-          const double d = fma(minus, tv[b & 1][3 * u + j], xv[b & 1][3 * u + j]);
-          acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(flip(rd[gr[j] + site], sr[j]), d, acc0, 0, 0, 0);
-          acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(flip(rd[gi[j] + site], si[j]), flip(swap_pair(d), odd), acc1, 0,
-                                                      0, 0);
+        for (int j = 0; j < 3; ++j) product(2 * u * kPsStride, j, dd[2 * u * kPsStride + 8 * j]);
+    } else {
+      // products of the wave's 16 sites, two at a time, the next ones' d in
+      // flight (sites past the end, whose rows are zero, read the last one)
+      double xv[2][3 * BS], tv[2][3 * BS];
+      const int w0 = i0 + q * NS;
+      auto fetch = [&](int b, double *px, double *pt) {
+#pragma unroll
+        for (int u = 0; u < BS; ++u) {
+          const size_t o = (size_t(t) * Vs + std::min(w0 + BS * b + u, Vs - 1)) * 24;
+#pragma unroll
+          for (int j = 0; j < 3; ++j) {
+            px[3 * u + j] = xp[o + 8 * j];
+            pt[3 * u + j] = tp[o + 8 * j];
+          }
         }
+      };
+      fetch(0, xv[0], tv[0]);
+      __syncthreads();
+#pragma unroll
+      for (int b = 0; b < NS / BS; ++b) {
+        if (b + 1 < NS / BS) fetch(b + 1, xv[(b + 1) & 1], tv[(b + 1) & 1]);
+#pragma unroll
+        for (int u = 0; u < BS; ++u)
+#pragma unroll
+          for (int j = 0; j < 3; ++j)
+            product(2 * (BS * b + u) * kPsStride, j, fma(minus, tv[b & 1][3 * u + j], xv[b & 1][3 * u + j]));
       }
     }
     tot += acc0 + acc1;
@@ -401,8 +447,12 @@ __global__ void __launch_bounds__(kBlock, 2)
   // the four waves' sums, in order
   __syncthreads();
   double *sh = reinterpret_cast<double *>(reg);
+  if constexpr (ONE) {
+    sh[q * 256 + (4 * ((lane >> 2) & 3) + kq) * 16 + lcol] = tot;
+  } else {
 #pragma unroll
-  for (int u = 0; u < 4; ++u) sh[q * 256 + (kq + 4 * u) * 16 + l16] = tot[u];
+    for (int u = 0; u < 4; ++u) sh[q * 256 + (kq + 4 * u) * 16 + l16] = tot[u];
+  }
   __syncthreads();
   const int row = threadIdx.x >> 4, col = threadIdx.x & 15, v = col >> 1;
   if (row < kPsRows && v < nv) {
@@ -470,8 +520,8 @@ void launch_all(lqcd_ctx *c, const void *eta, const void *x, const XtSet &xts, i
                 int nch) {
   const Geom &g = c->g;
   const int xq = (g.L[3] * nch * nrhs + 7) / 8;  // logical workgroups per XCD (grid padded to 8 xq)
-  hipLaunchKernelGGL(k_estimate_all, dim3(8 * xq), dim3(kBlock), 0, c->stream, g,
-                     static_cast<const cx<double> *>(c->U64.ptr), c->kappa, static_cast<const cx<double> *>(eta),
+  hipLaunchKernelGGL(nv == 1 ? k_estimate_all<true> : k_estimate_all<false>, dim3(8 * xq), dim3(kBlock), 0, c->stream,
+                     g, static_cast<const cx<double> *>(c->U64.ptr), c->kappa, static_cast<const cx<double> *>(eta),
                      static_cast<const cx<double> *>(x), xts, nv, nch, nrhs, xq, d);
   LQCD_HIP(hipGetLastError());
 }

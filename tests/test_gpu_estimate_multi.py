@@ -131,3 +131,34 @@ def test_columns_of_the_product_stand_alone(dims):
     got, ref = dirty[1][2][1][:, :4], clean[1][2][1][:, :4]
     assert not np.isfinite(got[hit]).any()
     np.testing.assert_array_equal(got[~hit], ref[~hit])
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 4), (4, 4, 4, 4), (10, 6, 2, 4), (10, 14, 2, 4), (6, 4, 2, 8)])
+def test_a_single_variant_gives_the_bits_of_a_group(dims):
+    """One subtracted vector, or none, has a product of its own (four columns,
+    d through LDS): the same bits as in a group of six, for all operators and
+    for point-split ones alone, on timeslices below a chunk of 64 sites, of
+    one, and ragged; and a NaN stays in its noise vector and timeslice."""
+    require_gpu()
+    ctx, _ = context(dims, 0.3, 9, 0.12)
+    n = 3
+    eta, x, xts, _ = _fields(ctx, dims, n, 6, 31)
+    eg, xg = to_gpu(eta), to_gpu(x)
+    xtg = [None if t is None else to_gpu(t) for t in xts]
+    assert any(t is None for t in xtg)
+    for ops in (ALL, (5, 6, 7, 8), (8, 0)):
+        say("single variant", dims, ops)
+        group = ctx.loop_estimate_multi(eg, xg, xtg, None, ops, samples=True)
+        for v in range(6):
+            one = ctx.loop_estimate(eg, xg, xtg[v], None, ops, samples=True)
+            for a, b in zip(one, group[v]):
+                np.testing.assert_array_equal(a, b)
+    bad = x.copy()
+    bad[1, 2, -1, -1, -1, 0, 0] = np.nan
+    clean = ctx.loop_estimate(eg, xg, xtg[1], None, ALL, samples=True)[2]
+    dirty = ctx.loop_estimate(eg, to_gpu(bad), xtg[1], None, ALL, samples=True)[2]
+    hit = np.zeros(dirty.shape, bool)
+    hit[1, :8, 2] = hit[1, 8, [1, 3]] = True
+    hit[1, :, -1] = True  # the totals
+    assert not np.isfinite(dirty[hit]).any()
+    np.testing.assert_array_equal(dirty[~hit], clean[~hit])
